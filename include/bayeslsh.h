@@ -425,9 +425,12 @@ int bayeslsh_exact_similarity(blsh_ctx *ctx, const blsh_candidates *cand, const 
  * device uint32[capacity].  *n_pairs_host receives the number of pairs; the
  * call waits for `stream`.  More pairs than capacity: the first `capacity` are
  * written and BLSH_ETRUNCATED is returned; order_tile other than 0 or 16
- * gives BLSH_EINVAL.  Uses the context workspace (about 8 * n_obj * (n_bands
- * + 6) bytes) and, with tiles, a context buffer of 48 bytes per tile of the
- * largest band. */
+ * gives BLSH_EINVAL.  Uses the context workspace: all bands at once take about
+ * 40 * n_obj * n_bands bytes, used while that is at most 4 GiB; 8 * n_obj *
+ * (n_bands + 6) bytes are enough (fixed workspaces and larger inputs: fewer
+ * bands at a time, the same output).  The tiled order of pairs also uses a
+ * context buffer of 40 bytes per tile of the bands taken together (at most
+ * 1 GiB, or one band). */
 int bayeslsh_band_candidates(blsh_ctx *ctx, const blsh_sigs *band_sigs, int32_t n_bands, int32_t band_bits,
                              int32_t max_bucket, int32_t order_tile, uint32_t *x_out, uint32_t *y_out,
                              int64_t capacity, int64_t *n_pairs_host, void *stream);

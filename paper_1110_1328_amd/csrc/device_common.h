@@ -314,6 +314,7 @@ constexpr int kDppQuadXor1 = 0xB1;     // quad_perm [1,0,3,2]
 constexpr int kDppQuadXor2 = 0x4E;     // quad_perm [2,3,0,1]
 constexpr int kDppRowMirror = 0x140;   // lane i <- 15 - i within a row of 16
 constexpr int kDppHalfMirror = 0x141;  // lane i <- 7 - i within each half row
+constexpr int kDppRowRor12 = 0x12C;    // lane i <- (i - 12) mod 16 within a row of 16
 
 template <int CTRL>
 __device__ inline uint32_t dpp(uint32_t v) {

@@ -77,3 +77,57 @@ def test_banding_truncation_empty_and_invalid(ctx, bits, tile):
     mh = sigs_tensor(np.zeros((10, 64), np.uint32), P.JACCARD, P.OBJECT_MAJOR)
     with pytest.raises(P.BayesLSHError):
         run(ctx, mh, 4, 8, 16)
+
+
+@pytest.mark.parametrize("nb,b,n,max_bucket,fixed", [
+    (17, 16, 1500, 0, False),    # two keys to a word, an odd number of them, one more word than the registers hold
+    (16, 16, 1500, 33, False),   # the last word in registers; a bucket cap of two tiles and one member
+    (9, 17, 1500, 0, False),     # keys of more than 16 bits, eight words of earlier bands
+    (12, 20, 1500, 0, False),    # the same, more words than the registers hold
+    (64, 2, 300, 0, False),      # the most bands
+    (1, 1, 257, 0, False),       # one band, two buckets
+    (3, 32, 1500, 0, False),     # full-word keys: one band at a time
+    (8, 8, 3000, 0, True),       # a workspace that holds some of the bands at a time
+])
+def test_banding_key_rows_and_groups(ctx, nb, b, n, max_bucket, fixed):
+    """The earlier-band test over every row shape, and the bands in one group
+    or several: pairs in both orders and the tile descriptors, against the
+    oracle's pairs."""
+    print("banding rows nb=%d b=%d n=%d cap=%d" % (nb, b, n, max_bucket), flush=True)
+    rng = np.random.default_rng(G.SEED_BASE + 63 + nb * b)
+    words = (nb * b + 31) // 32
+    base = rng.integers(0, 2, size=(n // 60 + 1, words * 32), dtype=np.uint8)
+    flip = rng.random((n, words * 32)) < 0.02
+    bits = G.pack_bits((base[rng.integers(0, len(base), n)] ^ flip).astype(np.uint8))
+    S = sigs_tensor(bits, P.COSINE, P.OBJECT_MAJOR)
+    own = P.bayeslsh_create(0) if fixed else ctx
+    try:
+        if fixed:
+            P.bayeslsh_reserve_workspace(own, 8 * n * (nb + 6) + (128 << 10), fixed=True)
+        for tile in (0, 16):
+            wx, wy = R.band_candidates(bits, nb, b, max_bucket, tile=tile)
+            assert len(wx) > 100
+            gx, gy, got, trunc = run(own, S, nb, b, len(wx) + 7, max_bucket, tile)
+            assert got == len(wx) and not trunc
+            np.testing.assert_array_equal(gx, wx)
+            np.testing.assert_array_equal(gy, wy)
+        # the descriptors list the tiled order's pairs; a short buffer gets its first tiles
+        buf, nt, got, trunc = P.bayeslsh_band_tiles(own, S, nb, b, 1 << 16, max_bucket=max_bucket)
+        assert got == len(wx) and not trunc
+        t = down(buf)[:24 * nt].reshape(nt, 24)
+        first, keep, ids = t[:, 0], np.ascontiguousarray(t[:, 2:6]), np.ascontiguousarray(t[:, 6:22]).view(np.uint32)
+        on = np.unpackbits(keep.view(np.uint8), axis=1, bitorder="little").astype(bool)
+        np.testing.assert_array_equal(first, np.cumsum(on.sum(1)) - on.sum(1))
+        tile_of, pos = np.nonzero(on)
+        np.testing.assert_array_equal(ids[tile_of, pos // 16], wx)
+        np.testing.assert_array_equal(ids[tile_of, 16 + pos % 16], wy)
+        assert not t[:, 22:].any()
+        short = torch.full((24 * nt,), -1, dtype=torch.int64, device="cuda")
+        _, nt2, got2, trunc = P.bayeslsh_band_tiles(own, S, nb, b, nt // 2, max_bucket=max_bucket, tiles_out=short)
+        assert trunc == (nt > nt // 2) and nt2 == nt and got2 == got
+        s = down(short).reshape(nt, 24)
+        np.testing.assert_array_equal(s[:nt // 2], t[:nt // 2])
+        assert (s[nt // 2:] == -1).all()
+    finally:
+        if fixed:
+            own.close()

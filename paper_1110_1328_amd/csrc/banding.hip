@@ -317,13 +317,6 @@ __device__ inline int64_t first_strip(const StripArgs &a) {
 }
 __device__ inline int64_t strip_step() { return int64_t(gridDim.x) * (kBandBlock / kWave); }
 
-// v with x (wave-uniform) in lane L.
-template <int L>
-__device__ inline uint32_t write_lane(uint32_t x, uint32_t v) {
-  asm("v_writelane_b32 %0, %1, %2" : "+v"(v) : "s"(__builtin_amdgcn_readfirstlane(int(x))), "n"(L));
-  return v;
-}
-
 // The tiles of one strip, NW key words in registers (NW < 0: rows of more
 // words than that, read again for every tile).  Lane l holds column l % 16 and
 // rows 4 i + l / 16, i < 4, so that ballot i is word i of the tile's mask.  A
@@ -638,12 +631,14 @@ int band_candidates(blsh_ctx *ctx, const uint32_t *sig, int64_t n_obj, int32_t r
   int group = n_bands, rc = BLSH_OK;
   for (;; group = (group + 1) / 2) {
     const bool ok = key_bits_of(group) <= 32 && int64_t(group) * n_obj <= kGroupPositions;
-    if (group == 1 || ok) {
-      if ((rc = band_layout(n, group, key_bits_of(group), stride, tiled, s, &l))) return rc;
-      if (group == 1 || l.total <= most) break;
-    }
+    if (group > 1 && !ok) continue;
+    if ((rc = band_layout(n, group, key_bits_of(group), stride, tiled, s, &l))) return rc;
+    if (group > 1 && l.total > most) continue;
+    rc = ensure_workspace(ctx, l.total);
+    if (rc != BLSH_ENOMEM || group == 1) break;
+    (void)hipGetLastError();   // not enough device memory for these bands together: fewer
   }
-  if ((rc = ensure_workspace(ctx, l.total))) return rc;
+  if (rc) return rc;
   char *ws = static_cast<char *>(ctx->ws);
   auto u32 = [&](size_t o) { return reinterpret_cast<uint32_t *>(ws + o); };
   auto i64 = [&](size_t o) { return reinterpret_cast<int64_t *>(ws + o); };
@@ -697,9 +692,10 @@ int band_candidates(blsh_ctx *ctx, const uint32_t *sig, int64_t n_obj, int32_t r
       int64_t at[2 * (64 + 1)];   // strips and tiles before each band
       BLSH_HIP(hipMemcpyAsync(at, meta, size_t(2) * (g + 1) * 8, hipMemcpyDeviceToHost, s));
       BLSH_HIP(hipStreamSynchronize(s));
+      int64_t buf_bytes = kTileBufBytes;
       for (int b0 = 0, b1; b0 < g; b0 = b1) {
         b1 = b0 + 1;
-        while (b1 < g && (to || (at[2 * (b1 + 1) + 1] - at[2 * b0 + 1]) * kTileRec * 8 <= kTileBufBytes)) ++b1;
+        while (b1 < g && (to || (at[2 * (b1 + 1) + 1] - at[2 * b0 + 1]) * kTileRec * 8 <= buf_bytes)) ++b1;
         const int64_t n_strips = at[2 * b1] - at[2 * b0], n_tiles = at[2 * b1 + 1] - at[2 * b0 + 1];
         if (n_tiles == 0) continue;
         a.s_begin = at[2 * b0];
@@ -709,7 +705,14 @@ int band_candidates(blsh_ctx *ctx, const uint32_t *sig, int64_t n_obj, int32_t r
           a.out = to->tiles + std::min(tiles_total, to->tile_cap);
           a.out_n = std::max<int64_t>(0, to->tile_cap - tiles_total);
         } else {
-          if ((rc = ensure_tile_buf(ctx, size_t(n_tiles) * kTileRec * 8))) return rc;
+          rc = ensure_tile_buf(ctx, size_t(n_tiles) * kTileRec * 8);
+          if (rc == BLSH_ENOMEM && b1 > b0 + 1) {   // one band at a time
+            (void)hipGetLastError();
+            buf_bytes = 0;
+            b1 = b0;
+            continue;
+          }
+          if (rc) return rc;
           a.rec = static_cast<uint64_t *>(ctx->tile_buf);
         }
         const dim3 sg(unsigned(std::min(kStripBlocks, (n_strips + kBandBlock / kWave - 1) / (kBandBlock / kWave))));

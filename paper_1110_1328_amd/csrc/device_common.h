@@ -309,6 +309,15 @@ __device__ inline void wave_lds_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// v with x (wave-uniform) in lane L: the compiler's writelane, so that it keeps
+// the wait states the hardware wants between a vector compare's mask and its use
+// (written as an instruction of its own it read masks too early).
+extern "C" __device__ int blsh_writelane(int x, int lane, int v) __asm("llvm.amdgcn.writelane.i32");
+template <int L>
+__device__ inline uint32_t write_lane(uint32_t x, uint32_t v) {
+  return uint32_t(blsh_writelane(int(x), L, int(v)));
+}
+
 // DPP lane permutations (GFX9 encodings).
 constexpr int kDppQuadXor1 = 0xB1;     // quad_perm [1,0,3,2]
 constexpr int kDppQuadXor2 = 0x4E;     // quad_perm [2,3,0,1]

@@ -324,8 +324,11 @@ enum {
 
 /* Sign random projections (Section 4.2): bit h of object i is 1 iff r_h . x_i >= 0,
  * packed LSB-first (hash h -> word h/32, bit h%32) in `layout`.
- *   DENSE vectors: planes = float R[dim][n_bits] (device); projections by an
- *     FP32 MFMA product.
+ *   DENSE vectors: planes = float R[dim][n_bits] (device); the signs are those
+ *     of an FP32 MFMA product (larger calls decide most of them from a cheaper
+ *     product with an error bound and work out the rest in FP32, in the context
+ *     workspace: about 8 dim n_bits + n_obj n_bits / 64 bytes; a fixed workspace
+ *     that is smaller, and a stream under capture, take the plain product).
  *   CSR vectors: planes = NULL; plane entries are generated on the fly:
  *     g(term, h) = float(z), z from Box-Muller in FP64 on the Philox-4x32-10
  *     words of counter (term, h/4, 0, 0) and key (seed lo32, seed hi32),

@@ -13,7 +13,11 @@
 //                      (v_mfma_f32_32x32x2f32); each wave keeps 32 rows of X in
 //                      registers, the block stages a 32-plane slice of R in LDS, and
 //                      the sign of every accumulator is packed with a wave ballot.
+//   k_srp_dense_filter, k_srp_dense_settle  the same bits: bf16 products decide the signs
+//                      that their error bound allows, the fp32 instructions the rest.
+#include <algorithm>
 #include <type_traits>
+#include <utility>
 
 #include "device_common.h"
 
@@ -274,6 +278,14 @@ __global__ __launch_bounds__(256) void k_srp_sparse(const int64_t *offsets, cons
 // ---------------------------------------------------------------------------
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 
+// The 32 x 32 product's ballots by row: row 8 (v / 4) + v % 4 of the low half
+// of ballot v and the row 4 further of its high half go to their rows' lanes.
+template <int... V>
+__device__ inline void write_rows(uint32_t &word, const uint64_t (&b)[16], std::integer_sequence<int, V...>) {
+  ((word = write_lane<8 * (V >> 2) + (V & 3)>(uint32_t(b[V]), word)), ...);
+  ((word = write_lane<8 * (V >> 2) + (V & 3) + 4>(uint32_t(b[V] >> 32), word)), ...);
+}
+
 // X: [n_rows][D] fp32, R: [D][n_bits] fp32.  Block = 4 waves = 128 rows; the
 // D dimension is split between the two half-waves: lanes 0..31 cover
 // d in [0, D/2) and lanes 32..63 cover [D/2, D), so that each lane's A
@@ -351,6 +363,346 @@ __global__ __launch_bounds__(256, 2) void k_srp_dense_mfma(const float *X, int64
 }
 
 // ---------------------------------------------------------------------------
+// Dense SRP, filtered: the same signs as k_srp_dense_mfma from bf16 matrix
+// products, with every sign they leave open taken from the fp32 chain itself.
+//
+// Rows and planes are scaled by powers of two (no sign changes) and split into
+// two bf16 terms, x = xh + xl + ex with |ex| <= 2^-18 |x|.  xh rh and xh rl + xl
+// rh are accumulated apart in fp32.  Against the exact product the sum S of
+// the two is off by at most
+//   3 (1 + 2^-7) 2^-18 ||x|| ||r||   the terms left out (Cauchy-Schwarz)
+//   + (D + 16) 2^-23 ||x|| ||r||     the additions of xh rh, each within 2^-23 of
+//                                    a partial sum (twice rounding to nearest;
+//                                    those of the smaller products are 2^-8 of that),
+// and k_srp_dense_mfma's fp32 chain by at most D 2^-23 ||x|| ||r||.  Where |S|
+// exceeds the sum of these (kFilter), S, the exact product and the chain have
+// one sign.  The other signs (about 1 in 1000 for Gaussian planes at D = 256),
+// and rows or planes whose scale lets the chain under- or overflow, are listed
+// per wave and worked out by k_srp_dense_settle with the chain's own instructions in
+// the chain's own order, so the bits are k_srp_dense_mfma's, every one.
+// ---------------------------------------------------------------------------
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+
+template <int D>
+constexpr float kFilter = 3.1f / 262144.f + float(2 * D + 32) / 8388608.f;
+constexpr int kScaleLo = -40, kScaleHi = 60;   // exponents of a row's or plane's norm for which the chain neither under- nor overflows
+constexpr uint32_t kOpenCol = (1u << 26) - 1;  // an open sign: row in the wave << 27 | sign of S << 26 | plane
+
+// Scale of a vector with largest element mx: the power of two 2^-e that takes
+// its norm into [0.75, 1.5), found from the sum of squares of the elements
+// scaled by `first` (a power of two that takes mx into [1, 2)).  ok: e is in
+// the range above (false for zero, infinite or NaN).
+__device__ inline float first_scale(float mx) { return mx > 0.f && mx < INFINITY ? ldexpf(1.f, -ilogbf(mx)) : 1.f; }
+__device__ inline float norm_scale(float mx, float first, float sumsq, float &norm, bool &ok) {
+  ok = mx > 0.f && mx < INFINITY && sumsq < INFINITY;
+  if (!ok) { norm = 0.f; return 1.f; }
+  const float n = sqrtf(sumsq);                       // of the elements times `first`: in [1, 2 sqrt(D))
+  const int e = ilogbf(n * (4.f / 3.f));
+  norm = ldexpf(n, -e) * (1.f + 1.f / 1024.f);        // (covers the rounding of the sum of squares)
+  const int total = e + ilogbf(mx);
+  ok = total >= kScaleLo && total <= kScaleHi;
+  return ok ? ldexpf(1.f, -total) : 1.f;
+}
+
+// Planes for the filter, one block per 32 of them: the scaled bf16 terms in
+// the order the matrix instruction takes them, Bf[tile][k / 16][term][lane] (8
+// values: plane lane % 32, k % 16 = 8 (lane / 32) ..), their scaled norms (NaN
+// where every sign has to be settled), and the planes by rows for the chain.
+template <int D>
+__global__ __launch_bounds__(256) void k_srp_planes(const float *R, int32_t n_bits, uint4 *Bf, float *norms, float *Rt) {
+  __shared__ float s[D][33];
+  __shared__ float s_scale[32], s_part[8][32];
+  const int col0 = int(blockIdx.x) * 32, j = threadIdx.x % 32, part = threadIdx.x / 32;
+  for (int i = threadIdx.x; i < D * 32; i += 256) s[i / 32][i % 32] = R[size_t(i / 32) * n_bits + col0 + i % 32];
+  __syncthreads();
+  // plane j's largest element, then its sum of squares, by 8 threads
+  float mx = 0.f, sum = 0.f;
+  for (int d = part; d < D; d += 8) {
+    const float v = fabsf(s[d][j]);
+    mx = v == v ? fmaxf(mx, v) : INFINITY;   // (NaN: refused as infinite)
+  }
+  s_part[part][j] = mx;
+  __syncthreads();
+  for (int q = 0; q < 8; ++q) mx = fmaxf(mx, s_part[q][j]);
+  const float f = first_scale(mx);
+  for (int d = part; d < D; d += 8) { const float v = s[d][j] * f; sum += v * v; }
+  __syncthreads();
+  s_part[part][j] = sum;
+  __syncthreads();
+  if (part == 0) {
+    for (int q = 1; q < 8; ++q) sum += s_part[q][j];
+    float norm;
+    bool ok;
+    s_scale[j] = norm_scale(mx, f, sum, norm, ok);
+    norms[col0 + j] = ok ? norm : __builtin_nanf("");
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < D * 32; i += 256) Rt[size_t(col0) * D + i] = s[i % D][i / D];
+  for (int i = threadIdx.x; i < D / 16 * 64; i += 256) {
+    const int kb = i / 64, lane = i % 64, j = lane & 31, k0 = 16 * kb + 8 * (lane >> 5);
+    bf16x8 hi, lo;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const float v = s[k0 + q][j] * s_scale[j];
+      hi[q] = __bf16(v);
+      lo[q] = __bf16(v - float(hi[q]));
+    }
+    uint4 *to = Bf + (size_t(blockIdx.x) * (D / 16) + kb) * 128 + lane;
+    to[0] = __builtin_bit_cast(uint4, hi);
+    to[64] = __builtin_bit_cast(uint4, lo);
+  }
+}
+
+// Block = 4 waves = 128 rows, each wave's 32 rows held as bf16 terms in
+// registers; tile by tile of 32 planes (the split's share of them), the terms of the
+// next tile are copied to LDS while a tile's products run.  Bound by the
+// matrix cores: 1M rows, 1024 planes, D = 256 are 1.61e12 operations in three products,
+// 1.43 ms or 1.13e15 a second (what a large bf16 product reaches on this card);
+// with the settling and the planes' preparation 1.76 ms, against 4.09 ms of
+// k_srp_dense_mfma (131e12 a second of the 157e12 that fp32 instructions allow).
+template <int D>
+__global__ __launch_bounds__(256, 2) void k_srp_dense_filter(const float *X, int64_t n_rows, const uint4 *Bf,
+                                                             const float *norms, int32_t n_bits, int32_t n_splits,
+                                                             int32_t word_major, uint32_t *out, uint32_t *open,
+                                                             uint32_t *n_open, int32_t cap) {
+  constexpr int KB = D / 16;
+  __shared__ uint4 s_b[2][KB * 128];
+  const int lane = lane_id(), wv = threadIdx.x >> 6, h = lane >> 5, i = lane & 31;
+  const int64_t rb = blockIdx.x / unsigned(n_splits);
+  const int sp = int(blockIdx.x % unsigned(n_splits)), W = n_bits / 32;
+  const int t0 = int(int64_t(sp) * W / n_splits), t1 = int(int64_t(sp + 1) * W / n_splits);
+  const int64_t row0 = rb * 128 + wv * 32, region = (rb * 4 + wv) * n_splits + sp;
+  auto stage = [&](int tile, int b) {   // wave wv copies its quarter of the tile's fragments
+#pragma unroll
+    for (int u = 0; u < KB / 2; ++u) {
+      const int at = (u * 4 + wv) * 64;
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(Bf + size_t(tile) * KB * 128 + at + lane),
+                                       (__attribute__((address_space(3))) void *)(s_b[b] + at), 16, 0, 0);
+    }
+  };
+  stage(t0, 0);
+  bf16x8 xh[KB], xl[KB];
+  float xmax;
+  {
+    float x[KB][8];
+    const bool in = row0 + i < n_rows;
+    const float4 *src = reinterpret_cast<const float4 *>(X + size_t(in ? row0 + i : 0) * D + 8 * h);
+    float mx = 0.f, sum = 0.f;
+    bool num = true;
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb) {
+      const float4 u = src[4 * kb], v = src[4 * kb + 1];
+      const float t[8] = {u.x, u.y, u.z, u.w, v.x, v.y, v.z, v.w};
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        x[kb][q] = t[q];
+        mx = fmaxf(mx, fabsf(t[q]));
+        num = num && t[q] == t[q];
+      }
+    }
+    mx = fmaxf(mx, __shfl_xor(mx, 32));
+    const float f = first_scale(mx);
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+      for (int q = 0; q < 8; ++q) { const float v = x[kb][q] * f; sum += v * v; }
+    sum += __shfl_xor(sum, 32);
+    float norm;
+    bool ok;
+    float scale = norm_scale(mx, f, sum, norm, ok);
+    ok = ok && num && in;
+    const bool other = __shfl_xor(int(ok), 32) != 0;
+    ok = ok && other;
+    if (!ok) scale = __builtin_nanf("");   // every sign of the row open
+    xmax = ok ? norm : 0.f;
+#pragma unroll
+    for (int o = 16; o > 0; o >>= 1) xmax = fmaxf(xmax, __shfl_xor(xmax, o));
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        const float v = x[kb][q] * scale;
+        xh[kb][q] = __bf16(v);
+        xl[kb][q] = __bf16(v - float(xh[kb][q]));
+      }
+  }
+  const float bound = kFilter<D> * xmax;
+  float norm = norms[t0 * 32 + i];   // of this lane's plane (the next tile's is requested with its fragments)
+  uint32_t n = 0;   // open signs of the wave (wave-uniform)
+  uint32_t *list = open + size_t(region) * cap;
+  __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): the copies to LDS have arrived
+  __syncthreads();
+  for (int tile = t0; tile < t1; ++tile) {
+    const int b = (tile - t0) & 1;
+    if (tile + 1 < t1) stage(tile + 1, b ^ 1);
+    const float T = bound * norm;
+    norm = norms[min(tile + 1, t1 - 1) * 32 + i];
+    floatx16 ah = {}, al = {};
+    // (the fragments of a step are read while the step before it multiplies;
+    // left to itself the compiler reads them right before their use)
+    uint4 bh = s_b[b][lane], bl = s_b[b][64 + lane];
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb) {
+      uint4 nh = bh, nl = bl;
+      if (kb + 1 < KB) {
+        nh = s_b[b][(kb + 1) * 128 + lane];
+        nl = s_b[b][(kb + 1) * 128 + 64 + lane];
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      al = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xl[kb], __builtin_bit_cast(bf16x8, bh), al, 0, 0, 0);
+      ah = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xh[kb], __builtin_bit_cast(bf16x8, bh), ah, 0, 0, 0);
+      al = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xh[kb], __builtin_bit_cast(bf16x8, bl), al, 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+      bh = nh;
+      bl = nl;
+    }
+    // value v of lane l: row 8 (v / 4) + 4 (l / 32) + v % 4 of the wave, plane l % 32
+    uint32_t word = 0;
+    bool sure = true;
+    {
+      uint64_t neg[16];
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        ah[v] += al[v];
+        neg[v] = __ballot(ah[v] < 0.f);
+        sure = sure && fabsf(ah[v]) > T;
+      }
+      write_rows(word, neg, std::make_integer_sequence<int, 16>{});
+      word = ~word;
+    }
+    const int64_t r = row0 + i;
+    if (lane < 32 && r < n_rows) {
+      if (word_major) out[size_t(tile) * n_rows + r] = word;
+      else out[size_t(r) * W + tile] = word;
+    }
+    if (__ballot(!sure)) {
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const int row = 8 * (v >> 2) + 4 * h + (v & 3);
+        const bool mine = !(fabsf(ah[v]) > T) && row0 + row < n_rows;
+        const uint64_t mask = __ballot(mine);
+        if (mask == 0) continue;
+        const uint32_t at = n + lanes_below(mask);
+        if (mine && at < uint32_t(cap))
+          list[at] = uint32_t(row) << 27 | uint32_t(!(ah[v] < 0.f)) << 26 | uint32_t(tile * 32 + i);
+        n += uint32_t(__popcll(mask));
+      }
+    }
+    // buffer b ^ 1 was last read before the barrier that ended the previous tile
+    __builtin_amdgcn_s_waitcnt(0x0F70);
+    __syncthreads();
+  }
+  if (lane == 0) n_open[region] = n;
+}
+
+// Four steps of k_srp_dense_mfma's chain.
+__device__ inline floatx16 chain4(floatx16 acc, const float4 &a, const float4 &b) {
+  acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x, b.x, acc, 0, 0, 0);
+  acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.y, b.y, acc, 0, 0, 0);
+  acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.z, b.z, acc, 0, 0, 0);
+  acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.w, b.w, acc, 0, 0, 0);
+  return acc;
+}
+
+// The open signs of four waves' lists, 32 at a time: open sign t as row t and
+// plane t of the chain's own matrix product, whose value (t, t) is its sign's.
+// The 64 vectors of a batch go through LDS in chunks of 2 C elements (C of
+// either half, the order of the chain), read 64 bytes at a time; four blocks to
+// a CU cover the reads.  (Rows and planes read by the lanes that multiply them:
+// 64 lines per load, 0.57 ms for 1M rows, 1024 planes, D = 256.  Copies straight to
+// LDS gave wrong values now and then when read after the wave's own wait
+// alone, without a barrier.)
+// A list that overflowed stands for all signs of its wave's rows and planes.
+template <int D>
+__global__ __launch_bounds__(256) void k_srp_dense_settle(const float *X, int64_t n_rows, const float *Rt,
+                                                             int32_t n_bits, int32_t n_splits, int32_t word_major,
+                                                             uint32_t *out, const uint32_t *open,
+                                                             const uint32_t *n_open, int32_t cap, int64_t n_regions) {
+  constexpr int HD = D / 2, C = 16, NC = HD / C;
+  constexpr int NL = 8;   // loads per chunk: 8 vectors each, 8 lanes of 16 bytes to a vector
+  // [vector][piece]: vectors 0..31 rows, 32..63 planes; piece p (p < 4: of the
+  // first half) of vector v sits at p ^ (v % 8), so that 8 vectors' reads of one
+  // piece spread over the banks
+  __shared__ float4 s_v[4][64 * 8];
+  const int lane = lane_id(), wv = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6), h = lane >> 5, i = lane & 31;
+  const int W = n_bits / 32, my_v = 4 * (i >> 3) + (i & 3), my_h = (i >> 2) & 1;
+  const int64_t reg0 = int64_t(blockIdx.x) * 4;
+  uint32_t cnt[4], total = 0;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    cnt[q] = reg0 + q < n_regions ? n_open[reg0 + q] : 0u;
+    total += cnt[q] <= uint32_t(cap) ? cnt[q] : 0u;
+  }
+  auto word_at = [&](int64_t row, int w) -> uint32_t * {
+    return word_major ? out + size_t(w) * n_rows + row : out + size_t(row) * W + w;
+  };
+  for (uint32_t e0 = 32u * wv; e0 < total; e0 += 128) {   // wave-uniform
+    const bool act = e0 + i < total;
+    uint32_t k = act ? e0 + i : e0;   // entry k of the lists one after another
+    int q = 0;
+#pragma unroll
+    for (int x = 0; x < 3; ++x) {
+      const uint32_t c = cnt[x] <= uint32_t(cap) ? cnt[x] : 0u;
+      if (q == x && k >= c) { k -= c; ++q; }
+    }
+    const uint32_t e = open[size_t(reg0 + q) * cap + k];
+    const int64_t row = (reg0 + q) / n_splits * 32 + (e >> 27);
+    const uint32_t col = e & kOpenCol;
+    // load u: vectors 8 u + lane / 8
+    const int piece = (lane & 7) ^ (lane >> 3), off = (piece >> 2) * HD + (piece & 3) * 4;
+    const float *src[NL];
+#pragma unroll
+    for (int u = 0; u < NL; ++u) {
+      const int v = (8 * u + (lane >> 3)) & 31;
+      if (u < NL / 2) src[u] = X + size_t(__shfl(row, v)) * D + off;
+      else src[u] = Rt + size_t(uint32_t(__shfl(int(col), v))) * D + off;
+    }
+    floatx16 acc = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+    for (int c = 0; c < NC; ++c) {
+      float4 st[NL];
+#pragma unroll
+      for (int u = 0; u < NL; ++u) st[u] = *reinterpret_cast<const float4 *>(src[u] + c * C);
+#pragma unroll
+      for (int u = 0; u < NL; ++u) s_v[wv][64 * u + lane] = st[u];
+      wave_lds_sync();
+#pragma unroll
+      for (int s = 0; s < C / 4; ++s) {
+        const int at = (4 * h + s) ^ (i & 7);
+        acc = chain4(acc, s_v[wv][8 * i + at], s_v[wv][8 * (32 + i) + at]);
+      }
+      wave_lds_sync();
+    }
+    float d = 0.f;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) d = my_v == v ? acc[v] : d;
+    // (a word's signs may sit in several lanes: only those that change it do, atomically)
+    if (act && h == my_h && uint32_t(d >= 0.f) != ((e >> 26) & 1u)) atomicXor(word_at(row, int(col >> 5)), 1u << (col & 31));
+  }
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    if (cnt[q] <= uint32_t(cap)) continue;
+    const int64_t row0 = (reg0 + q) / n_splits * 32;
+    const int sp = int((reg0 + q) % n_splits);
+    const int t0 = int(int64_t(sp) * W / n_splits), t1 = int(int64_t(sp + 1) * W / n_splits);
+    for (int tile = t0 + wv; tile < t1; tile += 4) {
+      floatx16 acc = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+      const float4 *x4 = reinterpret_cast<const float4 *>(X + size_t(min(row0 + i, n_rows - 1)) * D + h * HD);
+      const float4 *r4 = reinterpret_cast<const float4 *>(Rt + size_t(tile * 32 + i) * D + h * HD);
+#pragma unroll 4
+      for (int s = 0; s < HD / 4; ++s) acc = chain4(acc, x4[s], r4[s]);
+      uint32_t word = 0;
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const uint64_t mk = __ballot(acc[v] >= 0.f);
+        if (my_v == v) word = my_h ? uint32_t(mk >> 32) : uint32_t(mk);
+      }
+      if (lane < 32 && row0 + i < n_rows) *word_at(row0 + i, tile) = word;
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------
 // Launchers
 // ---------------------------------------------------------------------------
 int launch_minhash(blsh_ctx *ctx, const int64_t *offsets, const uint32_t *elems, int64_t n_sets, const uint32_t *a,
@@ -421,9 +773,70 @@ int launch_srp_sparse(blsh_ctx *ctx, const int64_t *offsets, const uint32_t *ind
   return fail(BLSH_EINVAL, "srp (sparse): n_bits %d > 2048", n_bits);
 }
 
+// Where the filtered product is the faster one.  Its planes are prepared and
+// its open signs settled by two small kernels, about 15 us beside the main one,
+// but it splits the planes over blocks when rows alone do not fill the chip:
+// from 512 planes (and 2^15 plane elements) on it wins at any number of rows
+// (1000 x 256 x 1024: 138 us plain, 34 filtered; 64 x 512, 16000 rows: 25.7 and
+// 24.4), with 128 planes from 2^32 multiply-adds on (300,000 x 128 x 128: 107 and 85
+// us; 65,536 x 128 x 128: 26 and 39; 300,000 x 256 x 64: 126 and 142).
+static bool filter_pays(int64_t n_rows, int64_t dim, int64_t n_bits) {
+  return (n_bits >= 512 && dim * n_bits >= (1 << 15)) ||
+         (n_bits >= 128 && double(n_rows) * double(dim) * double(n_bits) >= 4294967296.0);
+}
+constexpr int kOpenShare = 256;   // a wave's list holds 1 in kOpenShare of its signs (Gaussian planes leave 1 in 1000 open)
+
+template <int D>
+static int launch_srp_filter(blsh_ctx *ctx, const float *X, int64_t n_rows, const float *R, int n_bits, bool word_major,
+                             uint32_t *out, hipStream_t s, bool *done) {
+  *done = false;
+  const int W = n_bits / 32;
+  const int64_t rb = (n_rows + 127) / 128;
+  // rows alone may not fill the chip (two blocks per CU): split the planes too
+  const int64_t want = (int64_t(ctx->n_cu) * 4 + rb - 1) / rb;
+  const int splits = int(std::max<int64_t>(1, std::min<int64_t>(want, W / 2)));
+  const int64_t regions = rb * 4 * splits;
+  const int cap = std::max(32, 32 * (n_bits / splits) / kOpenShare);
+  auto align = [](size_t b) { return (b + 255) & ~size_t(255); };
+  const size_t b_bf = align(size_t(n_bits) * D * 4), b_rt = align(size_t(n_bits) * D * 4), b_n = align(size_t(n_bits) * 4),
+               b_cnt = align(size_t(regions) * 4), b_open = align(size_t(regions) * cap * 4);
+  const size_t need = b_bf + b_rt + b_n + b_cnt + b_open;
+  if (need > ctx->ws_bytes) {
+    if (ctx->ws_fixed) return BLSH_OK;
+    if (ensure_workspace(ctx, need) != BLSH_OK) {
+      (void)hipGetLastError();
+      return BLSH_OK;
+    }
+  }
+  char *p = static_cast<char *>(ctx->ws);
+  uint4 *Bf = reinterpret_cast<uint4 *>(p);
+  float *Rt = reinterpret_cast<float *>(p + b_bf), *norms = reinterpret_cast<float *>(p + b_bf + b_rt);
+  uint32_t *cnt = reinterpret_cast<uint32_t *>(p + b_bf + b_rt + b_n), *open = cnt + b_cnt / 4;
+  LaunchScope ls(ctx, s, "srp_dense_mfma");
+  hipLaunchKernelGGL(k_srp_planes<D>, dim3(W), dim3(256), 0, s, R, n_bits, Bf, norms, Rt);
+  hipLaunchKernelGGL(k_srp_dense_filter<D>, dim3(unsigned(rb * splits)), dim3(256), 0, s, X, n_rows, Bf, norms, n_bits,
+                     splits, int(word_major), out, open, cnt, cap);
+  hipLaunchKernelGGL(k_srp_dense_settle<D>, dim3(unsigned((regions + 3) / 4)), dim3(256), 0, s, X, n_rows, Rt, n_bits,
+                     splits, int(word_major), out, open, cnt, cap, regions);
+  *done = true;
+  return hipGetLastError() == hipSuccess ? BLSH_OK : BLSH_EDEVICE;
+}
+
 int launch_srp_dense(blsh_ctx *ctx, const float *X, int64_t n_rows, int64_t dim, const float *R, int n_bits,
                      bool word_major, uint32_t *out, hipStream_t s) {
   const int64_t nb = (n_rows + 127) / 128;
+  // a call under capture keeps to the plain kernel: it neither grows the
+  // workspace nor leaves its address in a graph
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (filter_pays(n_rows, dim, n_bits) && uint32_t(n_bits) <= kOpenCol &&
+      hipStreamIsCapturing(s, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone) {
+    bool done = false;
+    int rc = BLSH_OK;
+#define BLSH_DF(DD) if (dim == DD) rc = launch_srp_filter<DD>(ctx, X, n_rows, R, n_bits, word_major, out, s, &done);
+    BLSH_DF(32) BLSH_DF(64) BLSH_DF(128) BLSH_DF(256)
+#undef BLSH_DF
+    if (rc || done) return rc;
+  }
   LaunchScope ls(ctx, s, "srp_dense_mfma");
 #define BLSH_DN(DD) if (dim == DD) { hipLaunchKernelGGL(k_srp_dense_mfma<DD>, dim3(nb), dim3(256), 0, s, X, n_rows, R, n_bits, int(word_major), out); return hipGetLastError() == hipSuccess ? BLSH_OK : BLSH_EDEVICE; }
   BLSH_DN(32) BLSH_DN(64) BLSH_DN(128) BLSH_DN(256)

@@ -18,7 +18,8 @@
 //                     one candidate's k hashes with one 16-byte load per lane and
 //                     per side, then sums the agreements with DPP; lane l owns
 //                     candidate l of the wave's tile of 64.
-//   k_exact_*         exact similarity on Lite survivors (one wave per pair).
+//   k_exact           exact similarity on Lite survivors (one wave per pair).
+//   k_exact_pairs, k_exact_dense_pairs  exact similarity of every candidate.
 //   k_exhaustive_*    the comparator: all n_max hashes of both object-major rows,
 //                     per-level counts, prefix sums, then the decision sequence
 //                     of Algorithm 1/2 replayed (or the classical m/n estimate).
@@ -30,6 +31,7 @@
 // for a whole launch would serialise every wave's atomic.
 #include <map>
 #include <mutex>
+#include <type_traits>
 
 #include "device_common.h"
 
@@ -624,24 +626,252 @@ __global__ __launch_bounds__(kBlock) void k_verify_tail(VerifyArgs a) {
   }
 }
 
-// Exact similarity of every candidate in [c_begin, c_end), one wave per pair,
-// written to out[c] in FP64 (bad ids: NaN and BLSH_EBADID).
+// Sum over aligned groups of G lanes (G = 16 or 64), in every lane of the group.
+template <int CTRL>
+__device__ inline double dpp_f64(double v) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  return __builtin_bit_cast(double, uint64_t(dpp<CTRL>(uint32_t(u))) | uint64_t(dpp<CTRL>(uint32_t(u >> 32))) << 32);
+}
+template <int G>
+__device__ inline double group_sum_f64(double v) {
+  v += dpp_f64<kDppQuadXor1>(v);
+  v += dpp_f64<kDppQuadXor2>(v);
+  v += dpp_f64<kDppHalfMirror>(v);
+  v += dpp_f64<kDppRowMirror>(v);
+  if constexpr (G == 64) {
+    v += __shfl_xor(v, 16);
+    v += __shfl_xor(v, 32);
+  }
+  return v;
+}
+
+// Exact similarity of every candidate in [c_begin, c_end), written to out[c] in
+// FP64 (bad ids: NaN and BLSH_EBADID).  Sparse rows and sets: a wave takes 64
+// consecutive candidates, x by x (lists, bucket-major pairs and all pairs hold
+// runs of one x): x's row goes into a hash table in LDS, and each of its
+// candidates' rows is looked up there by 16 lanes, four candidates at a time (a
+// single one by all 64).  An x row that the table does not hold goes pair by
+// pair through exact_wave.
+// Bound by VALU issue (120 instructions a pair) and the chain from ids over
+// offsets and rows to the table: 4M pairs of rows of 100 terms (16 x 16 tiled
+// order) in 1.22 ms; 3.79 ms with a wave, a staged row, a binary search of 7 steps
+// per entry and 18 shuffles to a pair.
+constexpr int kHashSlots = kExactLds;           // 4-byte keys and values, one table per wave
+constexpr int kHashRow = kHashSlots * 3 / 4;    // longest row in the table
+constexpr uint32_t kHashEmpty = 0xFFFFFFFFu;    // (a term of this number is kept beside the table)
+
+__device__ inline uint32_t hash_slot(uint32_t key) { return (key * 0x9E3779B1u) >> 23; }
+static_assert(kHashSlots == 1 << (32 - 23), "slot bits of the hash");
+
+// Entries [at, at + n) of a row summed over the group of G lanes: products with
+// the table's values and squares (CSR), or the number of entries found.
+struct RowSums {
+  double dot, sq;
+  uint32_t found;
+};
+template <bool CSR, int G>
+__device__ __forceinline__ RowSums probe_row(const VerifyArgs &a, int64_t at, int64_t n, const uint32_t *keys,
+                                             const float *vals, bool has_top, float top) {
+  double dot = 0.0, sq = 0.0;
+  uint32_t found = 0;
+  // entries per lane and step, 4 consecutive ones to a load; all loads, then
+  // all first lookups, are issued together
+  constexpr int U = G == 64 ? 4 : 8;
+  typedef uint32_t keys4 __attribute__((ext_vector_type(4), aligned(4)));
+  typedef float vals4 __attribute__((ext_vector_type(4), aligned(4)));
+  const int r = lane_id() & (G - 1);
+  const uint32_t *idx = a.ex_indices + at;
+  const float *val = CSR ? a.ex_values + at : nullptr;
+  for (int64_t e0 = 0; e0 < n; e0 += G * U) {
+    uint32_t key[U], got[U], slot[U];
+    float v[U];
+    bool in[U];
+#pragma unroll
+    for (int q = 0; q < U / 4; ++q) {
+      const int64_t e = e0 + (q * G + r) * 4;
+      if (e + 4 <= n) {
+        const keys4 k4 = *reinterpret_cast<const keys4 *>(idx + e);
+        vals4 v4 = {0.f, 0.f, 0.f, 0.f};
+        if constexpr (CSR) v4 = *reinterpret_cast<const vals4 *>(val + e);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) { key[4 * q + u] = k4[u]; v[4 * q + u] = v4[u]; }
+      } else {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          key[4 * q + u] = e + u < n ? idx[e + u] : 0u;
+          v[4 * q + u] = CSR && e + u < n ? val[e + u] : 0.f;
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        in[4 * q + u] = e + u < n;
+        slot[4 * q + u] = hash_slot(key[4 * q + u]);
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) got[u] = keys[slot[u]];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      bool is_top = key[u] == kHashEmpty;
+      while (in[u] && !is_top && got[u] != key[u] && got[u] != kHashEmpty) {
+        slot[u] = (slot[u] + 1) & (kHashSlots - 1);
+        got[u] = keys[slot[u]];
+      }
+      const bool hit = in[u] && (is_top ? has_top : got[u] == key[u]);
+      if constexpr (CSR) {
+        const double d = v[u];
+        sq += d * d;
+        if (hit) dot += d * double(is_top ? top : vals[slot[u]]);
+      } else {
+        found += hit;
+      }
+    }
+  }
+  if constexpr (CSR) {
+    dot = group_sum_f64<G>(dot);
+    sq = group_sum_f64<G>(sq);
+  } else {
+    found = group_sum<16>(found);
+    if constexpr (G == 64) {
+      found += __shfl_xor(found, 16);
+      found += __shfl_xor(found, 32);
+    }
+  }
+  return RowSums{dot, sq, found};
+}
+
+template <bool CSR>
 __global__ __launch_bounds__(kBlock) void k_exact_pairs(VerifyArgs a, double *out) {
-  __shared__ uint32_t s_idx[kBlock / kWave][kExactLds];
-  __shared__ float s_val[kBlock / kWave][kExactLds];
-  const int w = threadIdx.x >> 6;
+  __shared__ uint32_t s_keys[kBlock / kWave][kHashSlots];
+  __shared__ float s_vals[kBlock / kWave][kHashSlots];
+  const int lane = lane_id(), w = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6), grp = lane >> 4;
+  uint32_t *keys = s_keys[w];
+  float *vals = s_vals[w];
   const int64_t waves = int64_t(gridDim.x) * (kBlock / kWave);
-  for (int64_t c = a.c_begin + int64_t(blockIdx.x) * (kBlock / kWave) + w; c < a.c_end; c += waves) {
-    uint32_t xi, yi;
-    if (!fetch_candidate(a, c, xi, yi)) {
-      if (lane_id() == 0) {
+  for (int64_t c0 = a.c_begin + (int64_t(blockIdx.x) * (kBlock / kWave) + w) * kWave; c0 < a.c_end; c0 += waves * kWave) {
+    const int64_t c = c0 + lane;
+    uint32_t xi = 0, yi = 0;
+    bool ok = false;
+    if (c < a.c_end) {
+      ok = fetch_candidate(a, c, xi, yi);
+      if (!ok) {
         out[c] = __builtin_nan("");
         raise_status(a.status, BLSH_EBADID);
       }
-      continue;
     }
-    const double sim = exact_wave(a, xi, yi, s_idx[w], s_val[w]);
-    if (lane_id() == 0) out[c] = sim;
+    int64_t ys = 0, yn = 0;
+    if (ok) {
+      ys = a.ex_offsets[yi];
+      yn = a.ex_offsets[yi + 1] - ys;
+    }
+    uint64_t left = __ballot(ok);
+    while (left) {
+      // the candidates of the first x left
+      const uint32_t x = uint32_t(__builtin_amdgcn_readlane(int(xi), __ffsll((unsigned long long)left) - 1));
+      uint64_t run = left & __ballot(xi == x);
+      left &= ~run;
+      const int64_t xs = a.ex_offsets[x], xn = a.ex_offsets[x + 1] - xs;
+      if (xn > kHashRow) {
+        for (; run; run &= run - 1) {
+          const int l = __ffsll((unsigned long long)run) - 1;
+          const double sim = exact_wave(a, x, uint32_t(__builtin_amdgcn_readlane(int(yi), l)), keys, vals);
+          if (lane == 0) out[c0 + l] = sim;
+        }
+        continue;
+      }
+      wave_lds_sync();   // the table before was read
+#pragma unroll
+      for (int q = 0; q < kHashSlots / (4 * kWave); ++q)
+        reinterpret_cast<uint4 *>(keys)[q * kWave + lane] = make_uint4(kHashEmpty, kHashEmpty, kHashEmpty, kHashEmpty);
+      wave_lds_sync();
+      double xsq = 0.0;
+      bool has_top = false;
+      float top = 0.f;
+      for (int64_t e = lane; e < xn; e += kWave) {
+        const uint32_t key = a.ex_indices[xs + e];
+        const float v = CSR ? a.ex_values[xs + e] : 0.f;
+        if constexpr (CSR) xsq += double(v) * double(v);
+        if (key == kHashEmpty) {
+          has_top = true;
+          top = v;
+        } else {
+          uint32_t slot = hash_slot(key);
+          for (;;) {   // (at most kHashRow of the slots are taken: one is free)
+            const uint32_t old = atomicCAS(&keys[slot], kHashEmpty, key);
+            if (old == kHashEmpty) break;
+            slot = (slot + 1) & (kHashSlots - 1);
+          }
+          if constexpr (CSR) vals[slot] = v;
+        }
+      }
+      const uint64_t tops = __ballot(has_top);
+      has_top = tops != 0;
+      if (CSR && tops) top = __shfl(top, __ffsll((unsigned long long)tops) - 1);
+      if constexpr (CSR) xsq = group_sum_f64<64>(xsq);
+      wave_lds_sync();
+      while (run) {
+        // one candidate by all lanes, or the next four by 16 each
+        const bool one = (run & (run - 1)) == 0;
+        int mine = -1;   // the candidate of this lane's group
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          if (run && (one || grp == q)) mine = __ffsll((unsigned long long)run) - 1;
+          run &= run - 1;   // (0 stays 0)
+        }
+        const int64_t at = __shfl(ys, mine & 63), yl = __shfl(yn, mine & 63);   // (every lane takes part)
+        const int64_t n = mine < 0 ? 0 : yl;
+        const RowSums t = one ? probe_row<CSR, 64>(a, at, n, keys, vals, has_top, top)
+                              : probe_row<CSR, 16>(a, at, n, keys, vals, has_top, top);
+        double sim;
+        if constexpr (CSR) {
+          sim = (xsq > 0 && t.sq > 0) ? t.dot / (sqrt(xsq) * sqrt(t.sq)) : 0.0;
+        } else {
+          const int64_t uni = xn + n - int64_t(t.found);
+          sim = uni > 0 ? double(t.found) / double(uni) : 0.0;
+        }
+        if (mine >= 0 && (lane & (one ? 63 : 15)) == 0) out[c0 + mine] = sim;
+      }
+    }
+  }
+}
+
+// The same for dense rows: 16 lanes per candidate, V floats per lane and load
+// (4 for 16-byte aligned rows).
+template <int V>
+__global__ __launch_bounds__(kBlock) void k_exact_dense_pairs(VerifyArgs a, double *out) {
+  typedef float vec __attribute__((ext_vector_type(V)));
+  const int lane = lane_id(), r = lane & 15;
+  const int64_t groups = int64_t(gridDim.x) * (kBlock / 16);
+  const int64_t g0 = int64_t(blockIdx.x) * (kBlock / 16) + (threadIdx.x >> 4);
+  const int64_t n = a.c_end - a.c_begin;
+  const int64_t last = (n + groups - 1) / groups;
+  for (int64_t q = 0; q < last; ++q) {   // (every lane of the wave stays in the loop)
+    const int64_t c = a.c_begin + q * groups + g0;
+    uint32_t xi = 0, yi = 0;
+    const bool in = c < a.c_end, ok = in && fetch_candidate(a, c, xi, yi);
+    double nx = 0.0, ny = 0.0, dot = 0.0;
+    if (ok) {
+      const vec *u = reinterpret_cast<const vec *>(a.ex_dense + size_t(xi) * a.ex_dim);
+      const vec *v = reinterpret_cast<const vec *>(a.ex_dense + size_t(yi) * a.ex_dim);
+#pragma unroll 4
+      for (int64_t d = r; d < a.ex_dim / V; d += 16) {
+        const vec p = u[d], s = v[d];
+#pragma unroll
+        for (int e = 0; e < V; ++e) {
+          const double pe = p[e], se = s[e];
+          nx += pe * pe;
+          ny += se * se;
+          dot += pe * se;
+        }
+      }
+    }
+    nx = group_sum_f64<16>(nx);
+    ny = group_sum_f64<16>(ny);
+    dot = group_sum_f64<16>(dot);
+    if (r == 0 && in) {
+      out[c] = !ok ? __builtin_nan("") : (nx > 0 && ny > 0) ? dot / (sqrt(nx) * sqrt(ny)) : 0.0;
+      if (!ok) raise_status(a.status, BLSH_EBADID);
+    }
   }
 }
 
@@ -1561,9 +1791,18 @@ int launch_tiles_flush(blsh_ctx *ctx, const VerifyArgs &a, int64_t grid_waves, i
 int launch_exact_pairs(blsh_ctx *ctx, const VerifyArgs &a, double *out, hipStream_t s) {
   const int64_t n = a.c_end - a.c_begin;
   if (n <= 0) return BLSH_OK;
-  const int64_t nb = std::min<int64_t>(blocks_for(n, kBlock / kWave), int64_t(ctx->n_cu) * 16);
   LaunchScope ls(ctx, s, "exact_pairs");
-  hipLaunchKernelGGL(k_exact_pairs, dim3(nb), dim3(kBlock), 0, s, a, out);
+  if (a.ex_kind == BLSH_DENSE) {
+    const dim3 nb(unsigned(std::min<int64_t>(blocks_for(n, kBlock / 16), int64_t(ctx->n_cu) * 32)));
+    if (a.ex_dim % 4 == 0 && (uintptr_t(a.ex_dense) & 15) == 0)
+      hipLaunchKernelGGL(k_exact_dense_pairs<4>, nb, dim3(kBlock), 0, s, a, out);
+    else
+      hipLaunchKernelGGL(k_exact_dense_pairs<1>, nb, dim3(kBlock), 0, s, a, out);
+  } else {
+    const dim3 nb(unsigned(std::min<int64_t>(blocks_for(n, kBlock), int64_t(ctx->n_cu) * 64)));
+    if (a.ex_kind == BLSH_CSR) hipLaunchKernelGGL(k_exact_pairs<true>, nb, dim3(kBlock), 0, s, a, out);
+    else hipLaunchKernelGGL(k_exact_pairs<false>, nb, dim3(kBlock), 0, s, a, out);
+  }
   return hipGetLastError() == hipSuccess ? BLSH_OK : BLSH_EDEVICE;
 }
 

@@ -1,0 +1,106 @@
+"""Exact similarities over every shape of the kernels: runs of one x (lists, all
+pairs) and lone pairs, rows around the table's and the loads' sizes, empty
+rows, the largest term number, dense rows with and without 16-byte loads."""
+import numpy as np
+import pytest
+import torch
+
+import paper_1110_1328_amd as P
+
+from gpu_util import down, up
+
+pytestmark = pytest.mark.gpu
+
+TOP = (1 << 32) - 1
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    c = P.bayeslsh_create(0)
+    yield c
+    c.close()
+
+
+def rows(rng, spread):
+    """Sorted unique rows from `spread` terms; some with the top term, some empty."""
+    sizes = [0, 1, 3, 4, 5, 15, 16, 63, 64, 65, 100, 127, 128, 129, 255, 256, 257, 383, 384, 385, 511, 512, 513, 700]
+    sizes += [int(v) for v in rng.integers(1, 150, 40)]
+    out = []
+    for i, n in enumerate(sizes):
+        r = np.sort(rng.choice(spread, size=n, replace=False)).astype(np.int64)
+        if i % 3 == 0 and n:
+            r[-1] = TOP
+        out.append(r)
+    return out
+
+
+def reference(rs, vs, x, y):
+    got = np.zeros(len(x))
+    for i, (p, q) in enumerate(zip(x, y)):
+        common, a, b = np.intersect1d(rs[p], rs[q], assume_unique=True, return_indices=True)
+        if vs is None:
+            union = len(rs[p]) + len(rs[q]) - len(common)
+            got[i] = len(common) / union if union else 0.0
+        else:
+            u, v = vs[p].astype(np.float64), vs[q].astype(np.float64)
+            norm = np.sqrt((u * u).sum()) * np.sqrt((v * v).sum())
+            got[i] = (u[a] * v[b]).sum() / norm if norm > 0 else 0.0
+    return got
+
+
+@pytest.mark.parametrize("kind", ["csr", "sets"])
+@pytest.mark.parametrize("spread", [900, 100_000])
+def test_sparse_similarity_shapes(ctx, kind, spread):
+    print("similarity shapes %s spread %d" % (kind, spread), flush=True)
+    rng = np.random.default_rng(spread)
+    rs = rows(rng, spread)
+    n = len(rs)
+    vs = [rng.normal(size=len(r)).astype(np.float32) for r in rs] if kind == "csr" else None
+    off = np.zeros(n + 1, np.int64)
+    np.cumsum([len(r) for r in rs], out=off[1:])
+    idx = np.concatenate(rs).astype(np.uint32)
+    vecs = (P.csr_vectors(up(off), up(idx), up(np.concatenate(vs)), 1 << 32) if kind == "csr"
+            else P.set_vectors(up(off), up(idx), 1 << 32))
+    # lone pairs, all pairs (runs that cross waves), lists of 1, 2, 5 and 70 ids
+    x, y = rng.integers(0, n, 1001), rng.integers(0, n, 1001)
+    y[0], x[1] = n, n + 5                                    # bad ids
+    got = down(P.bayeslsh_exact_similarity(ctx, P.pairs(up(x.astype(np.uint32)), up(y.astype(np.uint32))), vecs))
+    with pytest.raises(P.BayesLSHError):
+        P.bayeslsh_sync(ctx)
+    assert np.isnan(got[:2]).all()
+    np.testing.assert_allclose(got[2:], reference(rs, vs, x[2:], y[2:]), rtol=0, atol=1e-12)
+    ax, ay = np.triu_indices(n, 1)
+    got = down(P.bayeslsh_exact_similarity(ctx, P.all_pairs(n), vecs))[:len(ax)]
+    P.bayeslsh_sync(ctx)
+    np.testing.assert_allclose(got, reference(rs, vs, ax, ay), rtol=0, atol=1e-12)
+    lens = np.array([1, 2, 5, 70, 3])
+    q, o = rng.integers(0, n, len(lens)), np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    c = rng.integers(0, n, int(o[-1]))
+    got = down(P.bayeslsh_exact_similarity(ctx, P.query_lists(up(q.astype(np.uint32)), up(o), up(c.astype(np.uint32)),
+                                                              int(o[-1])), vecs))[:int(o[-1])]
+    P.bayeslsh_sync(ctx)
+    np.testing.assert_allclose(got, reference(rs, vs, np.repeat(q, lens), c), rtol=0, atol=1e-12)
+
+
+@pytest.mark.parametrize("dim", [1, 5, 64, 100, 130, 256])
+def test_dense_similarity_dims(ctx, dim):
+    print("dense similarity dim %d" % dim, flush=True)
+    rng = np.random.default_rng(dim)
+    v = rng.normal(size=(300, dim)).astype(np.float32)
+    v[7] = 0
+    x, y = rng.integers(0, 300, 777), rng.integers(0, 300, 777)
+    x[5], y[9] = 7, 300
+    d = v.astype(np.float64)
+    for shift in (0, 1):   # rows from an address that 16-byte loads may start at, and one they may not
+        buf = torch.zeros(v.size + 4, device="cuda")
+        buf[shift:shift + v.size] = torch.from_numpy(v.reshape(-1)).cuda()
+        vecs = P.dense_vectors(buf[shift:shift + v.size].view(300, dim))
+        got = down(P.bayeslsh_exact_similarity(ctx, P.pairs(up(x.astype(np.uint32)), up(y.astype(np.uint32))), vecs))
+        with pytest.raises(P.BayesLSHError):
+            P.bayeslsh_sync(ctx)
+        assert np.isnan(got[9])
+        ok = np.arange(777) != 9
+        a, b = d[x[ok]], d[y[ok]]
+        norm = np.sqrt((a * a).sum(1)) * np.sqrt((b * b).sum(1))
+        want = np.where(norm > 0, (a * b).sum(1) / np.where(norm > 0, norm, 1), 0)
+        np.testing.assert_allclose(got[ok], want, rtol=0, atol=1e-12)

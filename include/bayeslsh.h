@@ -316,8 +316,7 @@ enum {
    * middle of its cell, (c + 0.5) * 16 / 2^16 - 8, so |used - g| <= 2^-13
    * (about 1.22e-4; the paper prints 1e-4 for this encoding, which its cell
    * width of 2.44e-4 does not allow).  A generated entry never leaves
-   * (-6.8, 6.8), so no entry saturates.  The plane table, when one is built,
-   * holds the codes: 2 bytes per entry instead of 4.  The signature bits can
+   * (-6.8, 6.8), so no entry saturates.  The signature bits can
    * differ from the unflagged ones only where |r . x| <= 2^-13 sum |x_i|. */
   BLSH_SRP_PLANES_Q16 = 1
 };
@@ -333,13 +332,16 @@ enum {
  *     g(term, h) = float(z), z from Box-Muller in FP64 on the Philox-4x32-10
  *     words of counter (term, h/4, 0, 0) and key (seed lo32, seed hi32),
  *     u_i = (w_i + 0.5)/2^32, (z0,z1) = BoxMuller(u0,u1), (z2,z3) = BoxMuller(u2,u3),
- *     entry = z_{h mod 4}; projections accumulated in FP64.  The call reads
- *     the nonzero count (offsets[n_obj]) back, waiting for `stream`; when it
- *     exceeds 2 * dim and dim * n_bits * 4 bytes (2 with BLSH_SRP_PLANES_Q16)
- *     fit in 16 GiB, the entries of every term < dim are drawn once into a
- *     table in the context workspace and read from there (the same values;
- *     an index >= dim, outside the CSR contract, is drawn as it occurs rather
- *     than read past the table).
+ *     entry = z_{h mod 4}; a bit is the sign of the projection accumulated in
+ *     FP64.  Most signs are decided from approximate entries with an error
+ *     bound, the others (and every one without room for 32 rows' masks) from
+ *     the entries themselves: the same bits.  The call reads the nonzero count
+ *     (offsets[n_obj]) back, waiting for `stream`; when it exceeds 2 * dim and
+ *     dim * n_bits * 2 bytes fit in 16 GiB, the approximate entries of every
+ *     term < dim are drawn once into a table in the context workspace (an index
+ *     >= dim, outside the CSR contract, is drawn as it occurs rather than read
+ *     past the table).  The workspace also holds n_obj * n_bits / 8 bytes of
+ *     masks (of fewer rows at a time when it is fixed smaller).
  * flags: 0 or BLSH_SRP_PLANES_Q16 (CSR only; with DENSE vectors it is
  * BLSH_EINVAL).  n_bits must be a multiple of 32 (DENSE: of 64). */
 int bayeslsh_srp_sigs(blsh_ctx *ctx, const blsh_vectors *vecs, const float *planes, int32_t n_bits,

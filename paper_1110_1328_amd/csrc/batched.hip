@@ -108,14 +108,6 @@ __device__ inline uint4 spill_entry(int64_t pos, uint32_t list, uint32_t m, uint
   return make_uint4(uint32_t(pos), uint32_t(uint64_t(pos) >> 32), list, m | (next_level << 16));
 }
 
-// Read-only data (signatures, tables, list descriptors: nothing the kernels
-// write) read through the constant address space, so that a wave-uniform
-// address becomes one scalar load.
-template <typename T>
-__device__ inline T ld_uniform(const T *p) {
-  return *(const __attribute__((address_space(4))) T *)(p);
-}
-
 __device__ inline BatchList ld_list(const BatchList *p) {
   BatchList r;
   r.offset = ld_uniform(&p->offset);

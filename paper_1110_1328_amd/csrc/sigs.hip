@@ -3,12 +3,11 @@
 //   k_minhash          one wave per set, lanes over hash functions; each lane keeps
 //                      the running minimum of (a_h e + b_h) mod (2^31 - 1) over the
 //                      set's elements (Section 4.1).
-//   k_srp_sparse       one wave per sparse row, lanes over groups of 4 hashes; plane
-//                      entries come from Philox-4x32-10 + Box-Muller (FP64), the
-//                      projections accumulate in FP64, and the sign bits are packed
-//                      32 to a word with DPP (Section 4.2).  Optionally every entry
-//                      is stored in 2 bytes (Section 4.3): a table of codes then
-//                      takes half the bytes of the fp32 one.
+//   k_srp_sparse, k_srp_settle  signs of sparse rows' projections (Section 4.2): most
+//                      from approximate plane entries (Philox-4x32-10 + Box-Muller in
+//                      fp32, a table of 2-byte codes where terms repeat) with an error
+//                      bound, the others from FP64 sums of the entries themselves,
+//                      optionally as stored in 2 bytes (Section 4.3).
 //   k_srp_dense_mfma   dense rows times a Gaussian plane matrix on the matrix cores
 //                      (v_mfma_f32_32x32x2f32); each wave keeps 32 rows of X in
 //                      registers, the block stages a 32-plane slice of R in LDS, and
@@ -105,20 +104,15 @@ __device__ inline uint4 philox4x32_10(uint4 c, uint32_t k0, uint32_t k1) {
   return c;
 }
 
-// The four plane entries for hashes 4q..4q+3 at coordinate `term`.
-__device__ inline void srp_gauss4(uint32_t term, uint32_t q, uint32_t k0, uint32_t k1, double g[4]) {
-  const uint4 w = philox4x32_10(make_uint4(term, q, 0u, 0u), k0, k1);
+// The plane entry of hash h at coordinate `term`.
+__device__ inline double srp_gauss1(uint32_t term, uint32_t h, uint32_t k0, uint32_t k1) {
+  const uint4 w = philox4x32_10(make_uint4(term, h >> 2, 0u, 0u), k0, k1);
   const double two32 = 4294967296.0, two_pi = 6.283185307179586476925286766559;
-  const double u0 = (double(w.x) + 0.5) / two32, u1 = (double(w.y) + 0.5) / two32;
-  const double u2 = (double(w.z) + 0.5) / two32, u3 = (double(w.w) + 0.5) / two32;
-  const double r0 = sqrt(-2.0 * log(u0)), r1 = sqrt(-2.0 * log(u2));
-  double s1, c1, s3, c3;   // one argument reduction for each sine-cosine pair
-  sincos(two_pi * u1, &s1, &c1);
-  sincos(two_pi * u3, &s3, &c3);
-  g[0] = double(float(r0 * c1));
-  g[1] = double(float(r0 * s1));
-  g[2] = double(float(r1 * c3));
-  g[3] = double(float(r1 * s3));
+  const double u = (double(h & 2 ? w.z : w.x) + 0.5) / two32, a = (double(h & 2 ? w.w : w.y) + 0.5) / two32;
+  double sn, cs;
+  sincos(two_pi * a, &sn, &cs);
+  const double radius = sqrt(-2.0 * log(u));
+  return double(float(radius * (h & 1 ? sn : cs)));
 }
 
 // 2-byte storage of a plane entry (Section 4.3): g in (-8, 8) becomes the
@@ -154,151 +148,259 @@ __global__ __launch_bounds__(256) void k_fill_u8(uint8_t *p, int64_t n) {
   for (int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x; i < n; i += int64_t(gridDim.x) * 256) p[i] = 0;
 }
 
-// Plane entries of the terms < dim that occur (used[term] != 0),
-// table[term][n_bits] of fp32 (Q16: of 2-byte codes): one thread per (term,
-// quad of hashes).  Used when each term occurs in several rows, so that an
-// entry is drawn once instead of once per occurrence.
-template <bool Q16>
+// ---------------------------------------------------------------------------
+// Sparse projections: signs from approximate plane entries, open ones settled
+// with the entries themselves.
+//
+// A bit is the sign of sum_t v_t g(term_t, h), summed in FP64 over the row's
+// nonzeros in order (srp_settle below).  Its entries cost two FP64 Box-Muller
+// pairs per four hashes, far more than the sum, so the sign is first looked for
+// with entries g' that cost a fraction: the same Philox words through the
+// hardware's fp32 logarithm, square root, sine and cosine, |g' - g| <= kFastErr,
+// and, where terms repeat, a table of them as 16-bit multiples of 1 / kUnit.
+// With S = sum v g' in fp32, the sum has S's sign wherever |S| exceeds
+//   sum |v| (kFastErr + half a unit [table] + 2^-13 [2-byte entries])
+//   + the fp32 additions' rounding;
+// every other bit (about 1 in 1000 with the table and rows of 100 terms, 1 in
+// 30,000 without) is marked open and worked out from g in FP64.  So the bits are those of
+// the FP64 sums, every one.
+// ---------------------------------------------------------------------------
+// |g' - g| over every Philox word: the radius is off by at most 5.8e-7 and the sine
+// and cosine by 2.7e-7 (each measured over all 2^32 words), the radius is below 6.77, and the product
+// and the entry's own rounding to fp32 add at most 8.2e-7.
+constexpr float kFastErr = 0x1p-18f;
+constexpr float kUnit = 4800.f;          // |g| < 6.77: codes within 16 bits
+constexpr int kSumBlock = 32;            // nonzeros summed before they are added to the row's sum
+
+__device__ inline float srp_fast_radius(uint32_t w) {
+  // sqrt(-2 ln u), u = (w + 0.5) 2^-32; near 1 from t = 1 - u, which fp32 holds to its last bit
+  const float u = __builtin_fmaf(float(w), 0x1p-32f, 0x1p-33f), t = __builtin_fmaf(float(~w), 0x1p-32f, 0x1p-33f);
+  const float near_one = t * (1.f + t * (0.5f + t * (1.f / 3.f + t * (0.25f + t * (0.2f + t * (1.f / 6.f))))));
+  const float l = t < 0.0625f ? near_one : -0.69314718f * __builtin_amdgcn_logf(u);
+  return __builtin_amdgcn_sqrtf(2.f * l);
+}
+
+// About the entries of hashes 4 q .. 4 q + 3 at coordinate `term`.
+__device__ inline void srp_fast4(uint32_t term, uint32_t q, uint32_t k0, uint32_t k1, float g[4]) {
+  const uint4 w = philox4x32_10(make_uint4(term, q, 0u, 0u), k0, k1);
+  const float r0 = srp_fast_radius(w.x), r1 = srp_fast_radius(w.z);
+  const float a0 = __builtin_fmaf(float(w.y), 0x1p-32f, 0x1p-33f), a1 = __builtin_fmaf(float(w.w), 0x1p-32f, 0x1p-33f);
+  // (the hardware's sine and cosine take revolutions)
+  g[0] = r0 * __builtin_amdgcn_cosf(a0);
+  g[1] = r0 * __builtin_amdgcn_sinf(a0);
+  g[2] = r1 * __builtin_amdgcn_cosf(a1);
+  g[3] = r1 * __builtin_amdgcn_sinf(a1);
+}
+
+// Codes of the entries of the terms < dim that occur (used[term] != 0),
+// table[term][n_bits]: a wave takes 64 terms, those that occur one by one (the
+// term is wave-uniform, and with it Philox's first multiplications).  Used when each term
+// occurs in several rows, so that an entry is drawn once instead of once per
+// occurrence.  Bound by VALU (Philox's multiplications first): 1.37e9 entries of
+// 668,880 terms in 1.35 ms, against 4.41 ms of FP64 logarithms, sines and cosines.
 __global__ __launch_bounds__(256) void k_srp_table(int64_t dim, int32_t n_bits, uint32_t k0, uint32_t k1,
-                                                   const uint8_t *used, void *table) {
-  const int Q = n_bits / 4;
-  const int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x;
-  if (i >= dim * Q) return;
-  const int64_t term = i / Q;
-  if (!used[term]) return;
-  const int q = int(i % Q);
-  double g[4];
-  srp_gauss4(uint32_t(term), uint32_t(q), k0, k1, g);
-  const size_t at = size_t(term) * n_bits + 4 * q;
-  if constexpr (Q16) {
-    const uint2 w = make_uint2(q16_code(g[0]) | q16_code(g[1]) << 16, q16_code(g[2]) | q16_code(g[3]) << 16);
-    *reinterpret_cast<uint2 *>(static_cast<uint16_t *>(table) + at) = w;
-  } else {
-    *reinterpret_cast<float4 *>(static_cast<float *>(table) + at) =
-        make_float4(float(g[0]), float(g[1]), float(g[2]), float(g[3]));
-  }
-}
-
-// The four entries of hashes 4q..4q+3 at `term`, read from the table row or
-// drawn (terms >= dim); Q16: as their 2-byte codes read back.
-template <bool Q16>
-__device__ inline void srp_entry4(const void *table, int64_t dim, int32_t n_bits, uint32_t term, int q, uint32_t k0,
-                                  uint32_t k1, double g[4]) {
-  srp_gauss4(term, uint32_t(q), k0, k1, g);
-  if constexpr (Q16) {
+                                                   const uint8_t *used, int16_t *table) {
+  const int Q = n_bits / 4, lane = lane_id();
+  const int64_t n_groups = (dim + kWave - 1) / kWave;   // 64 terms at a time: their flags by one load
+  for (int64_t gr = int64_t(blockIdx.x) * 4 + __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6); gr < n_groups;
+       gr += int64_t(gridDim.x) * 4) {
+    const int64_t t = gr * kWave + lane;
+    for (uint64_t left = __ballot(t < dim && used[t] != 0); left; left &= left - 1) {
+      const uint32_t term = uint32_t(gr * kWave) + uint32_t(__ffsll((unsigned long long)left) - 1);   // wave-uniform
+      for (int q = lane; q < Q; q += kWave) {
+        float g[4];
+        srp_fast4(term, uint32_t(q), k0, k1, g);
+        int c[4];
 #pragma unroll
-    for (int c = 0; c < 4; ++c) g[c] = q16_value(q16_code(g[c]));
-  }
-  (void)table; (void)dim; (void)n_bits;
-}
-
-// TABLE: entries of terms < dim come from the table (the same values the
-// generator gives, since every entry is rounded to fp32, or the same codes),
-// others are drawn.  Q16: every entry is the value its 2-byte code stands for.
-// With a table the row's nonzeros are taken U at a time: the U table rows are
-// requested before any is used, so that U dependent fetches overlap (a batch
-// with a term outside the table leaves the rest of the row to the loop that
-// takes one nonzero at a time).
-// A wave takes one row and 64 QPL consecutive quads of its hashes (a slice;
-// rows of more hashes take several waves).
-template <int QPL, bool TABLE, bool Q16>  // quads (4 hashes) per lane
-__global__ __launch_bounds__(256) void k_srp_sparse(const int64_t *offsets, const uint32_t *indices,
-                                                    const float *values, int64_t n_rows, int32_t n_bits,
-                                                    int32_t n_slices, uint32_t k0, uint32_t k1, int32_t word_major,
-                                                    uint32_t *out, const void *table, int64_t dim) {
-  constexpr int U = TABLE ? (Q16 ? 4 : 2) : 1;
-  using Entry = typename std::conditional<Q16, uint2, float4>::type;
-  const int lane = lane_id();
-  const int64_t wid = int64_t(blockIdx.x) * 4 + (threadIdx.x >> 6);
-  const int64_t row = wid / n_slices;
-  if (row >= n_rows) return;  // wave-uniform
-  const int q0 = int(wid % n_slices) * kWave * QPL;   // first quad of the slice
-  const int Q = n_bits / 4, W = n_bits / 32;
-  double acc[QPL][4];
-#pragma unroll
-  for (int i = 0; i < QPL; ++i)
-#pragma unroll
-    for (int c = 0; c < 4; ++c) acc[i][c] = 0.0;
-  const int64_t s = offsets[row], e = offsets[row + 1];
-  auto fma4 = [&](int i, double v, const double g[4]) {
-#pragma unroll
-    for (int c = 0; c < 4; ++c) acc[i][c] += v * g[c];
-  };
-  auto decode = [&](const Entry &x, double g[4]) {
-    if constexpr (Q16) {
-      g[0] = q16_value(x.x & 0xFFFFu); g[1] = q16_value(x.x >> 16);
-      g[2] = q16_value(x.y & 0xFFFFu); g[3] = q16_value(x.y >> 16);
-    } else {
-      g[0] = x.x; g[1] = x.y; g[2] = x.z; g[3] = x.w;
-    }
-  };
-  int64_t t = s;
-  if constexpr (TABLE) {
-    for (; t + U <= e; t += U) {
-      uint32_t term[U];
-      double v[U];
-      bool in_table = true;
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        term[u] = indices[t + u];
-        v[u] = values[t + u];
-        in_table = in_table && int64_t(term[u]) < dim;
+        for (int e = 0; e < 4; ++e) c[e] = int(__builtin_rintf(g[e] * kUnit));
+        *reinterpret_cast<uint2 *>(table + size_t(term) * n_bits + 4 * q) =
+            make_uint2(uint32_t(c[0] & 0xFFFF) | uint32_t(c[1]) << 16, uint32_t(c[2] & 0xFFFF) | uint32_t(c[3]) << 16);
       }
-      if (!in_table) break;   // a term outside the table: the rest of the row one nonzero at a time
-      Entry ent[U][QPL];
-#pragma unroll
-      for (int u = 0; u < U; ++u)
-#pragma unroll
-        for (int i = 0; i < QPL; ++i) {
-          const int q = q0 + lane + kWave * i;
-          if (q < Q)
-            ent[u][i] = *reinterpret_cast<const Entry *>(static_cast<const typename std::conditional<
-                            Q16, uint16_t, float>::type *>(table) + size_t(term[u]) * n_bits + 4 * q);
-        }
-#pragma unroll
-      for (int u = 0; u < U; ++u)
-#pragma unroll
-        for (int i = 0; i < QPL; ++i) {
-          const int q = q0 + lane + kWave * i;
-          if (q < Q) {
-            double g[4];
-            decode(ent[u][i], g);
-            fma4(i, v[u], g);
-          }
-        }
     }
   }
-  for (; t < e; ++t) {
-    const uint32_t term = indices[t];
-    const double v = values[t];
+}
+
+// S of rows [row0, row1) in units of 1 / kUnit and the bits it decides.  A wave
+// takes one row and one slice of 64 QPL quads of its hashes (QPL consecutive
+// quads per lane: 16-byte loads with two).  The whole grid goes slice by slice (4
+// of 512 of 2048 hashes), so that every L2 holds one slice of the frequent terms'
+// entries, not every slice of fewer terms, and the last-level cache more of the rest.
+// Bound by table rows out of the caches: 1.0e7 nonzeros x 4 KB in 2.40 ms, 17 TB/s
+// (slices of 256 hashes, 8-byte loads, a slice to an XCD: 3.25 ms; slices of 512
+// over XCDs: 2.56 ms; 8 KB of fp32 entries, 1024 hashes per wave, FP64 sums: 6.6 ms).
+// TABLE: entries of terms < dim are codes from the table, the rows of U
+// nonzeros requested before any is used; others are drawn.
+// err: the most an entry is off, in units.
+template <bool TABLE, int QPL>
+__global__ __launch_bounds__(256) void k_srp_sparse(const int64_t *offsets, const uint32_t *indices,
+                                                    const float *values, int64_t n_rows, int64_t row0, int64_t row1,
+                                                    int32_t n_bits, int32_t n_slices, uint32_t k0, uint32_t k1,
+                                                    int32_t word_major, uint32_t *out, uint32_t *open,
+                                                    const int16_t *table, int64_t dim, float err) {
+  constexpr int U = TABLE ? 8 : 1;
+  typedef uint32_t codes __attribute__((ext_vector_type(2 * QPL), aligned(8)));
+  const int lane = lane_id();
+  const int64_t row_blocks = int64_t(gridDim.x) / n_slices;
+  const int slice = int(blockIdx.x / row_blocks);
+  const int64_t row = row0 + (blockIdx.x % row_blocks) * 4 + __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
+  if (row >= row1) return;  // wave-uniform
+  const int Q = n_bits / 4, W = n_bits / 32, q = (slice * kWave + lane) * QPL;   // (Q is a multiple of QPL)
+  const int qc = min(q, Q - QPL);   // (lanes past the last quad repeat it)
+  const int64_t s = ld_uniform(offsets + row), e = ld_uniform(offsets + row + 1);
+  float acc[4 * QPL], sum[4 * QPL];
+#pragma unroll
+  for (int c = 0; c < 4 * QPL; ++c) acc[c] = sum[c] = 0.f;
+  auto drawn = [&](uint32_t term, float v) {
 #pragma unroll
     for (int i = 0; i < QPL; ++i) {
-      const int q = q0 + lane + kWave * i;
-      if (q < Q) {
-        double g[4];
-        if (TABLE && int64_t(term) < dim) {
-          decode(*reinterpret_cast<const Entry *>(static_cast<const typename std::conditional<
-                     Q16, uint16_t, float>::type *>(table) + size_t(term) * n_bits + 4 * q), g);
-        } else {
-          srp_entry4<Q16>(table, dim, n_bits, term, q, k0, k1, g);
+      float g[4];
+      srp_fast4(term, uint32_t(qc + i), k0, k1, g);
+#pragma unroll
+      for (int c = 0; c < 4; ++c) acc[4 * i + c] = __builtin_fmaf(v * kUnit, g[c], acc[4 * i + c]);
+    }
+  };
+  auto coded = [&](const codes &x, float v) {
+#pragma unroll
+    for (int i = 0; i < 2 * QPL; ++i) {
+      acc[2 * i] = __builtin_fmaf(v, float(int16_t(x[i])), acc[2 * i]);
+      acc[2 * i + 1] = __builtin_fmaf(v, float(int32_t(x[i]) >> 16), acc[2 * i + 1]);
+    }
+  };
+  const uint32_t lane_off = uint32_t(qc) * 8u;
+  auto entry = [&](uint32_t term) {
+    return *reinterpret_cast<const codes *>(reinterpret_cast<const char *>(table + size_t(term) * uint32_t(n_bits)) + lane_off);
+  };
+  for (int64_t t0 = s; t0 < e; t0 += kSumBlock) {
+    const int64_t t1 = min(e, t0 + kSumBlock);
+    int64_t t = t0;
+    if constexpr (TABLE) {
+      for (; t + U <= t1; t += U) {
+        uint32_t term[U];
+        float v[U];
+        bool in_table = true;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          term[u] = ld_uniform(indices + t + u);
+          v[u] = ld_uniform(values + t + u);
+          in_table = in_table && int64_t(term[u]) < dim;
         }
-        fma4(i, v, g);
+        if (!in_table) break;   // the rest of the block one nonzero at a time
+        codes ent[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) ent[u] = entry(term[u]);
+#pragma unroll
+        for (int u = 0; u < U; ++u) coded(ent[u], v[u]);
       }
     }
-  }
-#pragma unroll
-  for (int i = 0; i < QPL; ++i) {
-    const int q = q0 + lane + kWave * i;
-    uint32_t nib = 0;
-#pragma unroll
-    for (int c = 0; c < 4; ++c) nib |= uint32_t(acc[i][c] >= 0.0) << c;
-    uint32_t word = group_or<8>(q < Q ? nib << (4 * (lane & 7)) : 0u);
-    const int w = q >> 3;
-    if ((lane & 7) == 0 && w < W) {
-      if (word_major) out[size_t(w) * n_rows + row] = word;
-      else out[size_t(row) * W + w] = word;
+    for (; t < t1; ++t) {
+      const uint32_t term = ld_uniform(indices + t);
+      const float v = ld_uniform(values + t);
+      if (TABLE && int64_t(term) < dim) coded(entry(term), v);
+      else drawn(term, v);
     }
+#pragma unroll
+    for (int c = 0; c < 4 * QPL; ++c) { sum[c] += acc[c]; acc[c] = 0.f; }
   }
+  // the mass sum |v|
+  float mass = 0.f;
+  for (int64_t t = s + lane; t < e; t += kWave) mass += fabsf(values[t]);
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) mass += __shfl_xor(mass, o);
+  // roundings: one per nonzero of a block's sum (a drawn entry's product with
+  // the unit: one more of its own term), one per block, each 2^-24 of at most
+  // 2^15 units of the mass; and those of the mass itself
+  const float n = float(e - s);
+  const float T = mass * (err + (kSumBlock + n / kSumBlock + 4.f) * 0x1p-9f) * (1.f + n * 0x1p-23f) * 1.001f;
+  uint32_t nib = 0, unsure = 0;
+#pragma unroll
+  for (int c = 0; c < 4 * QPL; ++c) {
+    nib |= uint32_t(sum[c] >= 0.f) << c;
+    unsure |= uint32_t(!(fabsf(sum[c]) > T && fabsf(sum[c]) < INFINITY)) << c;   // (an overflow decides nothing)
+  }
+  constexpr int G = 8 / QPL;   // lanes per word
+  const int sh = 4 * QPL * (lane & (G - 1)), w = q >> 3;
+  const uint32_t word = group_or<G>(q < Q ? nib << sh : 0u), mask = group_or<G>(q < Q ? unsure << sh : 0u);
+  if ((lane & (G - 1)) == 0 && w < W) {
+    if (word_major) out[size_t(w) * n_rows + row] = word;
+    else out[size_t(row) * W + w] = word;
+    open[size_t(row - row0) * W + w] = mask;
+  }
+}
+
+// The open bits of rows [rows0, rows1) (open = null: every bit), worked out:
+// the FP64 sum of v g over the row's nonzeros in order, g rounded to fp32 (Q16:
+// the value of its 2-byte code).  A block lists the open bits of its 32 rows in
+// LDS, 256 words at a time while they fit; then 8 lanes take a bit: each draws
+// every eighth nonzero's entry, and all 8 sum the products in order.
+constexpr int kSettleList = 8192, kSettleRows = 32;
+static_assert(kSettleList >= 256 * 32, "one round of words fits the list");
+
+template <bool Q16>
+__global__ __launch_bounds__(256) void k_srp_settle(const int64_t *offsets, const uint32_t *indices,
+                                                    const float *values, int64_t n_rows, int64_t rows0, int64_t rows1,
+                                                    int32_t n_bits, uint32_t k0, uint32_t k1, int32_t word_major,
+                                                    uint32_t *out, const uint32_t *open) {
+  __shared__ uint32_t s_bit[kSettleList];   // (row - row0) n_bits + hash (at most 32 x 2048)
+  __shared__ uint32_t s_wave[4];
+  const int W = n_bits / 32, lane = lane_id(), wv = threadIdx.x >> 6, r = lane & 7;
+  const int64_t row0 = rows0 + int64_t(blockIdx.x) * kSettleRows;
+  const int words = int(min<int64_t>(kSettleRows, rows1 - row0)) * W;
+  uint32_t count = 0;   // entries of the list (block-uniform)
+  auto settle = [&]() {
+    __syncthreads();
+    for (uint32_t i0 = 0; i0 < count; i0 += 32) {   // block-uniform
+      const uint32_t i = i0 + (threadIdx.x >> 3);
+      const bool act = i < count;
+      const uint32_t b = act ? s_bit[i] : 0u;
+      const int64_t row = row0 + b / uint32_t(n_bits);
+      const uint32_t h = b % uint32_t(n_bits);
+      const int64_t s = offsets[row], e = act ? offsets[row + 1] : s;
+      double acc = 0.0;
+      for (int64_t t = s; __ballot(t < e) != 0; t += 8) {
+        double v = 0.0, g = 0.0;
+        if (t + r < e) {
+          v = values[t + r];
+          g = srp_gauss1(indices[t + r], h, k0, k1);
+          if constexpr (Q16) g = q16_value(q16_code(g));
+        }
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          const double vj = __shfl(v, j, 8), gj = __shfl(g, j, 8);
+          if (t + j < e) acc = __builtin_fma(vj, gj, acc);
+        }
+      }
+      if (act && r == 0) {
+        uint32_t *word = word_major ? out + size_t(h >> 5) * n_rows + row : out + size_t(row) * W + (h >> 5);
+        const uint32_t bit = 1u << (h & 31);
+        if (acc >= 0.0) atomicOr(word, bit);
+        else atomicAnd(word, ~bit);
+      }
+    }
+    __syncthreads();
+    count = 0;
+  };
+  for (int w0 = 0; w0 < words; w0 += 256) {
+    const int w = w0 + threadIdx.x;
+    uint32_t mask = w >= words ? 0u : open ? open[size_t(row0 - rows0) * W + w] : 0xFFFFFFFFu;
+    const uint32_t mine = uint32_t(__popc(mask));
+    uint32_t before = mine;
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {
+      const uint32_t u = __shfl_up(before, o);
+      if (lane >= o) before += u;
+    }
+    __syncthreads();
+    if (lane == kWave - 1) s_wave[wv] = before;
+    __syncthreads();
+    const uint32_t total = s_wave[0] + s_wave[1] + s_wave[2] + s_wave[3];
+    before -= mine;
+    for (int x = 0; x < wv; ++x) before += s_wave[x];
+    if (count + total > uint32_t(kSettleList)) settle();
+    uint32_t at = count + before;
+    for (; mask; mask &= mask - 1) s_bit[at++] = uint32_t(w) * 32u + uint32_t(__ffs(int(mask)) - 1);
+    count += total;
+  }
+  if (count) settle();
 }
 
 // ---------------------------------------------------------------------------
@@ -746,60 +848,67 @@ int launch_minhash(blsh_ctx *ctx, const int64_t *offsets, const uint32_t *elems,
 }
 
 constexpr size_t kSrpTableMaxBytes = size_t(16) << 30;
+constexpr int64_t kSrpRows = int64_t(1) << 22;   // rows per launch (8 slices of 64 lanes each: 2^31 work-items)
 
 int launch_srp_sparse(blsh_ctx *ctx, const int64_t *offsets, const uint32_t *indices, const float *values,
                       int64_t n_rows, int64_t dim, int n_bits, uint64_t seed, bool word_major, bool q16,
                       uint32_t *out, hipStream_t s) {
-  // quads per lane: up to 4 (1024 hashes per wave); longer rows in slices of 1024
-  const int quads = n_bits / 4;
-  const int qpl_all = (quads + kWave - 1) / kWave;
-  if (qpl_all > 8) return fail(BLSH_EINVAL, "srp (sparse): n_bits %d > 2048", n_bits);
-  const int qpl = std::min(qpl_all, 4);
-  const int n_slices = (qpl_all + qpl - 1) / qpl;
-  const int64_t nb = (n_rows * n_slices + 3) / 4;
+  if (n_bits > 2048) return fail(BLSH_EINVAL, "srp (sparse): n_bits %d > 2048", n_bits);
+  // two quads per lane with the table (16-byte loads) when they fill a wave; drawn
+  // entries go one quad per lane (more waves)
   const uint32_t k0 = uint32_t(seed), k1 = uint32_t(seed >> 32);
   // a table of plane entries pays when terms repeat: more nonzeros than twice the dimension
   int64_t nnz = 0;
   BLSH_HIP(hipMemcpyAsync(&nnz, offsets + n_rows, sizeof(int64_t), hipMemcpyDeviceToHost, s));
   BLSH_HIP(hipStreamSynchronize(s));
-  const size_t entry_bytes = q16 ? sizeof(uint16_t) : sizeof(float);
-  const size_t table_bytes = size_t(std::max<int64_t>(dim, 0)) * size_t(n_bits) * entry_bytes;
-  // (a context whose workspace is fixed too small for the table draws the
-  // entries per nonzero instead: the same values)
-  const bool use_table = dim > 0 && nnz > 2 * dim && table_bytes <= kSrpTableMaxBytes &&
-                         (!ctx->ws_fixed || table_bytes + size_t(dim) <= ctx->ws_bytes);
-  void *table = nullptr;
-  uint8_t *used = nullptr;   // one byte per term after the table
-  if (use_table) {
-    if (int rc = ensure_workspace(ctx, table_bytes + size_t(dim))) return rc;
-    table = ctx->ws;
-    used = static_cast<uint8_t *>(ctx->ws) + table_bytes;
+  // workspace: the table, a byte per term, and the masks of as many rows' open
+  // bits as one launch takes.  A context whose workspace is fixed too small for the table
+  // draws the entries per nonzero instead, masks that do not all fit go in
+  // several launches, and without room for 32 rows' masks every bit is
+  // worked out (the same bits each time).
+  auto align = [](size_t b) { return (b + 255) & ~size_t(255); };
+  const size_t mask_row = size_t(n_bits / 32) * 4;
+  const size_t table_bytes = align(size_t(std::max<int64_t>(dim, 0)) * size_t(n_bits) * sizeof(int16_t));
+  const size_t used_bytes = align(size_t(std::max<int64_t>(dim, 0)));
+  const size_t fewest = mask_row * size_t(std::min<int64_t>(n_rows, kSettleRows));
+  const int64_t most = std::min<int64_t>(n_rows, kSrpRows);
+  bool use_table = dim > 0 && nnz > 2 * dim && table_bytes <= kSrpTableMaxBytes &&
+                   (!ctx->ws_fixed || table_bytes + used_bytes + fewest <= ctx->ws_bytes);
+  size_t table_room = use_table ? table_bytes + used_bytes : 0;
+  if (!ctx->ws_fixed && ensure_workspace(ctx, table_room + mask_row * size_t(most)) != BLSH_OK) {
+    (void)hipGetLastError();   // no memory for it: what there is, without the table
+    use_table = false;
+    table_room = 0;
   }
+  const int64_t chunk = std::min<int64_t>(most, int64_t((ctx->ws_bytes - table_room) / mask_row));
+  int16_t *table = static_cast<int16_t *>(ctx->ws);
+  uint8_t *used = static_cast<uint8_t *>(ctx->ws) + table_bytes;
+  uint32_t *open = reinterpret_cast<uint32_t *>(static_cast<char *>(ctx->ws) + table_room);
   LaunchScope ls(ctx, s, "srp_sparse");
   if (use_table) {
-    // draw the entries of the terms that occur
+    // the codes of the terms that occur
     const unsigned gz = unsigned(std::min<int64_t>((dim + 255) / 256, 4096));
     hipLaunchKernelGGL(k_fill_u8, dim3(gz), dim3(256), 0, s, used, dim);
     const unsigned gm = unsigned(std::min<int64_t>((nnz + 255) / 256, 8192));
     hipLaunchKernelGGL(k_srp_mark, dim3(gm), dim3(256), 0, s, indices, nnz, dim, used);
-    const int64_t items = dim * (n_bits / 4);
-    const dim3 g(unsigned((items + 255) / 256));
-    if (q16) hipLaunchKernelGGL(k_srp_table<true>, g, dim3(256), 0, s, dim, n_bits, k0, k1, used, table);
-    else hipLaunchKernelGGL(k_srp_table<false>, g, dim3(256), 0, s, dim, n_bits, k0, k1, used, table);
+    hipLaunchKernelGGL(k_srp_table, dim3(unsigned(std::min<int64_t>((dim + 255) / 256, int64_t(ctx->n_cu) * 64))), dim3(256), 0, s,
+                       dim, n_bits, k0, k1, used, table);
   }
-  auto go = [&](auto kern) {
-    hipLaunchKernelGGL(kern, dim3(nb), dim3(256), 0, s, offsets, indices, values, n_rows, n_bits, n_slices, k0, k1,
-                       int(word_major), out, static_cast<const void *>(table), dim);
-    return hipGetLastError() == hipSuccess ? BLSH_OK : BLSH_EDEVICE;
-  };
-#define BLSH_SP(N)                                                           \
-  if (qpl <= N) {                                                            \
-    if (use_table) return q16 ? go(k_srp_sparse<N, true, true>) : go(k_srp_sparse<N, true, false>); \
-    return q16 ? go(k_srp_sparse<N, false, true>) : go(k_srp_sparse<N, false, false>);              \
+  const int qpl = use_table && n_bits > 256 ? 2 : 1;
+  const int n_slices = (n_bits / 4 + kWave * qpl - 1) / (kWave * qpl);
+  const float err = kUnit * kFastErr + (use_table ? 0.5f : 0.f) + (q16 ? kUnit / 8192.f : 0.f);
+  const bool filter = chunk >= std::min<int64_t>(n_rows, kSettleRows);
+  for (int64_t r0 = 0, r1; r0 < n_rows; r0 = r1) {
+    r1 = std::min(n_rows, r0 + (filter ? chunk : kSrpRows));
+    if (filter)
+      hipLaunchKernelGGL((!use_table ? k_srp_sparse<false, 1> : qpl == 2 ? k_srp_sparse<true, 2> : k_srp_sparse<true, 1>),
+                         dim3(unsigned((r1 - r0 + 3) / 4 * n_slices)), dim3(256), 0, s, offsets, indices, values, n_rows,
+                         r0, r1, n_bits, n_slices, k0, k1, int(word_major), out, open, table, dim, err);
+    hipLaunchKernelGGL(q16 ? k_srp_settle<true> : k_srp_settle<false>,
+                       dim3(unsigned((r1 - r0 + kSettleRows - 1) / kSettleRows)), dim3(256), 0, s, offsets, indices,
+                       values, n_rows, r0, r1, n_bits, k0, k1, int(word_major), out, filter ? open : nullptr);
   }
-  BLSH_SP(1) BLSH_SP(2) BLSH_SP(4)
-#undef BLSH_SP
-  return fail(BLSH_EINVAL, "srp (sparse): n_bits %d > 2048", n_bits);
+  return hipGetLastError() == hipSuccess ? BLSH_OK : BLSH_EDEVICE;
 }
 
 // Where the filtered product is the faster one.  Its planes are prepared and

@@ -1,0 +1,92 @@
+"""Sparse sign random projections: the bits are those of the FP64 sums whatever
+decides most of them -- a table of codes, entries drawn per nonzero, masks in
+one launch or several, or (no workspace) the sums alone."""
+import numpy as np
+import pytest
+import torch
+
+import paper_1110_1328_amd as P
+
+from gpu_util import down, up
+
+pytestmark = pytest.mark.gpu
+
+
+def corpus(rng, n_rows, dim, odd):
+    lens = rng.integers(1, 90, n_rows)
+    if odd:
+        lens[:8] = [0, 1, 2, 31, 32, 33, 64, 500]
+    rows = [np.sort(rng.choice(dim, size=int(n), replace=False)) for n in lens]
+    vals = [rng.normal(size=len(r)).astype(np.float32) for r in rows]
+    if odd:
+        rows[9][-1] = dim + 3          # past the dimension: drawn, never read from the table
+        rows[10][:] = dim + np.arange(len(rows[10]))
+        vals[11][:] = 0
+        vals[12][0] = np.nan
+        vals[13][0] = np.inf
+        vals[14] *= np.float32(1e-42)
+        vals[15] *= np.float32(1e35)
+        rows[16], vals[16] = rows[16][:1], vals[16][:1]
+        rows[17] = rows[7].copy()      # the same row twice, one negated, and a row that nearly cancels
+        vals[17] = -vals[7]
+        vals[18] = np.where(np.arange(len(vals[18])) % 2, 1, -1).astype(np.float32)
+    off = np.zeros(n_rows + 1, np.int64)
+    np.cumsum([len(r) for r in rows], out=off[1:])
+    return off, np.concatenate(rows).astype(np.uint32), np.concatenate(vals).astype(np.float32)
+
+
+def bits_of(ctx, vecs, n_rows, n_bits, layout, flags):
+    out = torch.full((n_rows * (n_bits // 32),), -1, dtype=torch.int32, device="cuda").view(torch.uint32)
+    P.bayeslsh_srp_sigs(ctx, vecs, None, n_bits, 0x1234_5678_9ABC, layout, out, flags=flags)
+    P.bayeslsh_sync(ctx)
+    w = down(out)
+    return w.reshape(n_rows, -1) if layout == P.OBJECT_MAJOR else np.ascontiguousarray(w.reshape(-1, n_rows).T)
+
+
+@pytest.mark.parametrize("n_bits", [32, 96, 256, 288, 544, 2048])
+@pytest.mark.parametrize("flags", [0, P.SRP_PLANES_Q16])
+def test_every_route_gives_the_same_bits(n_bits, flags):
+    print("sparse SRP routes: %d bits flags %d" % (n_bits, flags), flush=True)
+    rng = np.random.default_rng(n_bits + flags)
+    n_rows, dim = 2100, 1500
+    off, idx, val = corpus(rng, n_rows, dim, True)
+    assert off[-1] > 2 * dim
+    vecs = P.csr_vectors(up(off), up(idx), up(val), dim)
+    got = {}
+    mask_row = n_bits // 32 * 4
+    # no workspace; masks of 1000 rows and no room for the table; everything
+    for name, room in (("sums", 0), ("pieces", 1000 * mask_row), ("table", None)):
+        ctx = P.bayeslsh_create(0)
+        try:
+            if room is not None:
+                P.bayeslsh_reserve_workspace(ctx, room, fixed=True)
+            for layout in (P.OBJECT_MAJOR, P.WORD_MAJOR):
+                got[name, layout] = bits_of(ctx, vecs, n_rows, n_bits, layout, flags)
+            if room is None:
+                assert P.bayeslsh_workspace_bytes(ctx) >= dim * n_bits * 2
+        finally:
+            ctx.close()
+    want = got["sums", P.OBJECT_MAJOR]
+    for key, w in got.items():
+        np.testing.assert_array_equal(w, want, err_msg=str(key))
+    # an empty row and a row of zeros: every sum is 0, every bit 1
+    assert (want[0] == 0xFFFFFFFF).all() and (want[11] == 0xFFFFFFFF).all()
+    # a NaN in the row: no bit
+    assert (want[12] == 0).all()
+
+
+@pytest.mark.parametrize("n_rows", [1, 3, 4, 5, 33])
+def test_few_rows(n_rows):
+    """Blocks that are not full, against the sums alone."""
+    rng = np.random.default_rng(n_rows)
+    off, idx, val = corpus(rng, n_rows, 1 << 20, False)
+    vecs = P.csr_vectors(up(off), up(idx), up(val), 1 << 20)
+    a, b = P.bayeslsh_create(0), P.bayeslsh_create(0)
+    try:
+        P.bayeslsh_reserve_workspace(b, 0, fixed=True)
+        for n_bits in (128, 160, 2048):
+            np.testing.assert_array_equal(bits_of(a, vecs, n_rows, n_bits, P.OBJECT_MAJOR, 0),
+                                          bits_of(b, vecs, n_rows, n_bits, P.OBJECT_MAJOR, 0))
+    finally:
+        a.close()
+        b.close()

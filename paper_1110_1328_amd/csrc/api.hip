@@ -22,6 +22,7 @@ int launch_srp_dense(blsh_ctx *ctx, const float *X, int64_t n_rows, int64_t dim,
 
 int launch_exact(blsh_ctx *ctx, const VerifyArgs &a, int64_t max_items, hipStream_t s);
 int launch_exact_pairs(blsh_ctx *ctx, const VerifyArgs &a, double *out, hipStream_t s);
+int launch_verify_few(blsh_ctx *ctx, const VerifyArgs &a, int k, bool word_major, int words, hipStream_t s);
 int launch_verify_tail(blsh_ctx *ctx, const VerifyArgs &a, int k, bool word_major, int words, hipStream_t s);
 int launch_zero_slices(blsh_ctx *ctx, int64_t *cnt, hipStream_t s);
 int launch_tiles_exact(blsh_ctx *ctx, const VerifyArgs &a, int64_t grid_waves, hipStream_t s);
@@ -270,6 +271,7 @@ static void fill_cand(VerifyArgs &a, const blsh_candidates *c) {
 //                    uses slice w % kSlices), so a slice never overflows
 //   st_rel, st_val   kSlices accepted-pair staging slices of st_cap entries
 static constexpr int64_t kChunk = int64_t(1) << 28;
+static constexpr int64_t kFewCand = int64_t(1) << 16;
 static constexpr int64_t kExhChunk = int64_t(1) << 24;
 static constexpr int64_t kStageDefault = int64_t(1) << 24;
 static constexpr size_t kSliceBufWords = (size_t(3) * kSlices + 2) * kCntStride;
@@ -554,6 +556,13 @@ static int run_verify(blsh_ctx *ctx, const blsh_candidates *cand, const blsh_sig
   // wait on one survivor's sparse gathers); otherwise it computes them itself
   const bool fused_exact = lite && exhaustive_mode == -1 && sigs->measure == BLSH_COSINE && a.pfx == nullptr;
   const bool queued = (lite && !fused_exact) || tail;
+  // Algorithm 1 of few candidates: one launch that appends to the caller's list,
+  // instead of two or three.  Its waves add to one counter, a few ns apart; a
+  // call over word-major signatures with a prefix array takes (us, one launch /
+  // queue and flush) 14.5 / 24.3 at 1000 candidates, 15.6 / 25.0 at 32000,
+  // 17.6 / 24.5 at 65000, 21.7 / 24.3 at 130000; minhash 10.6 / 12.8 up to
+  // 65000 and 13.5 / 12.7 at 130000.
+  const bool few = !exh && !lite && n_cand <= kFewCand;
   // launches are chunked so that no grid exceeds 2^32 work-items (the
   // dispatch's grid size): the comparator runs up to 64 lanes per candidate
   const int64_t chunk = std::min<int64_t>(n_cand, noalloc ? kNaChunk : exh ? kExhChunk : kChunk);
@@ -582,6 +591,19 @@ static int run_verify(blsh_ctx *ctx, const blsh_candidates *cand, const blsh_sig
   }
   int na_set = 0;
   int &set = noalloc ? na_set : ctx->slice_set;
+  if (few) {
+    a.direct = 1;
+    a.c_begin = 0;
+    a.c_end = n_cand;
+    a.acc_total = w.cnt + (size_t(3) * kSlices + set) * kCntStride;
+    if (!noalloc) ctx->slices_dirty = true;
+    rc = sigs->measure == BLSH_COSINE
+             ? launch_verify_few(ctx, a, k, sigs->layout == BLSH_WORD_MAJOR, (n_levels * k + 1 + 31) / 32, s)
+             : launch_verify(ctx, a, k, false, false, s);
+    if (rc) return rc == BLSH_EDEVICE ? fail(rc, "kernel launch failed: %s", hipGetErrorString(hipGetLastError())) : rc;
+    if (!noalloc) ctx->slices_dirty = false;
+    return BLSH_OK;
+  }
   auto set_cnt = [&](int st) { return w.cnt + size_t(st) * kSlices * kCntStride; };
   auto set_total = [&](int st) { return w.cnt + (size_t(3) * kSlices + st) * kCntStride; };
   for (int64_t c0 = 0; c0 < n_cand; c0 += chunk) {

@@ -89,6 +89,7 @@ struct VerifyArgs {
   // 32 bits through a 24-bit multiply (n_obj <= 2^24, size < 2^32): the rows
   // are then read as a buffer with 32-bit offsets; else 0
   uint32_t sig_buf_bytes;
+  int32_t direct;   // one launch of few candidates: no staging, no flush (finish_direct)
 };
 
 __device__ inline int lane_id() { return __lane_id(); }

@@ -32,6 +32,7 @@
 #include <map>
 #include <mutex>
 #include <type_traits>
+#include <utility>
 
 #include "device_common.h"
 
@@ -386,28 +387,65 @@ __global__ __launch_bounds__(kBlock, 8) void k_verify_bits(VerifyArgs a) {
   }
 }
 
+// A call of few candidates in one launch (a.direct): accepted pairs go straight
+// to the caller's list, and the last block to finish stores their number and
+// leaves the counters zero for the next call.  Called by every thread of every block.
+__device__ inline void finish_direct(const VerifyArgs &a) {
+  __syncthreads();   // this block's emissions are counted
+  if (threadIdx.x != 0) return;
+  unsigned long long *total = (unsigned long long *)a.acc_total, *ticket = total + 1;
+  __threadfence();
+  if (atomicAdd(ticket, 1ull) + 1 == gridDim.x) {
+    *a.n_acc = int64_t(atomicExch(total, 0ull));
+    atomicExch(ticket, 0ull);
+  }
+}
+
 // ---------------------------------------------------------------------------
 // Minhash: a group of K/4 lanes per candidate
 // ---------------------------------------------------------------------------
-template <int G, int S>
-struct MinhashStep {
-  template <int K>
-  __device__ static inline void run(const VerifyArgs &a, uint32_t xi, uint32_t yi, uint32_t alive, int j, int r,
-                                    uint32_t &own) {
-    const uint32_t xs = group_bcast<G, S>(xi);
-    const uint32_t ys = group_bcast<G, S>(yi);
-    const uint32_t al = group_bcast<G, S>(alive);
-    uint32_t c = 0;
-    if (al) {
-      const uint4 hx = *reinterpret_cast<const uint4 *>(a.sig + size_t(xs) * a.row_words + j * K + 4 * r);
-      const uint4 hy = *reinterpret_cast<const uint4 *>(a.sig + size_t(ys) * a.row_words + j * K + 4 * r);
-      c = uint32_t(hx.x == hy.x) + uint32_t(hx.y == hy.y) + uint32_t(hx.z == hy.z) + uint32_t(hx.w == hy.w);
-    }
-    c = group_sum<G>(c);
-    if (r == S) own = c;
-    if constexpr (S + 1 < G) MinhashStep<G, S + 1>::template run<K>(a, xi, yi, alive, j, r, own);
+// Agreements of level j for the wave's 64 candidates: the group of G lanes
+// holding a candidate compares the K hashes of each of its G members in turn
+// (lane r hashes 4 r .. 4 r + 3), the rows of up to 8 members requested before any is
+// compared.  SAME_X: one x for the whole wave, read once.  A decided candidate's
+// y is its x (no line of its own).  Returns the count of this lane's candidate.
+// Bound by the round trips of a wave's gathers: with each member's rows read in
+// turn a level was G trips long, now one or two.  10^6 candidates of one x, 256
+// hashes, k = 32: 17.9 -> 13.9 us; all pairs of 2000 sets: 41.6 -> 37.2 us.
+template <int G, int S0, int... S>
+__device__ inline void bcast_rows(uint32_t v, uint32_t *out, std::integer_sequence<int, S...>) {
+  ((out[S] = group_bcast<G, S0 + S>(v)), ...);
+}
+
+template <int K, bool SAME_X, int S0 = 0>
+__device__ inline uint32_t minhash_level(const VerifyArgs &a, uint32_t xi, uint32_t yi, int j, int r) {
+  constexpr int G = K / 4, CH = G < 8 ? G : 8;
+  uint32_t xs[CH], ys[CH];
+  bcast_rows<G, S0>(yi, ys, std::make_integer_sequence<int, CH>{});
+  const uint32_t col = uint32_t(j * K + 4 * r);
+  uint4 hx[SAME_X ? 1 : CH], hy[CH];
+  if constexpr (SAME_X) {
+    hx[0] = *reinterpret_cast<const uint4 *>(a.sig + size_t(xi) * a.row_words + col);
+  } else {
+    bcast_rows<G, S0>(xi, xs, std::make_integer_sequence<int, CH>{});
+#pragma unroll
+    for (int s = 0; s < CH; ++s) hx[s] = *reinterpret_cast<const uint4 *>(a.sig + size_t(xs[s]) * a.row_words + col);
   }
-};
+#pragma unroll
+  for (int s = 0; s < CH; ++s) hy[s] = *reinterpret_cast<const uint4 *>(a.sig + size_t(ys[s]) * a.row_words + col);
+  uint32_t own = 0;
+#pragma unroll
+  for (int s = 0; s < CH; ++s) {
+    const uint4 x = hx[SAME_X ? 0 : s], y = hy[s];
+    const uint32_t c = group_sum<G>(uint32_t(x.x == y.x) + uint32_t(x.y == y.y) + uint32_t(x.z == y.z) + uint32_t(x.w == y.w));
+    if (r == S0 + s) own = c;
+  }
+  if constexpr (S0 + CH < G) {
+    const uint32_t rest = minhash_level<K, SAME_X, S0 + CH>(a, xi, yi, j, r);
+    if (r >= S0 + CH) own = rest;
+  }
+  return own;
+}
 
 template <int K, int KIND, bool LITE>
 __global__ __launch_bounds__(kBlock) void k_verify_minhash(VerifyArgs a) {
@@ -422,7 +460,6 @@ __global__ __launch_bounds__(kBlock) void k_verify_minhash(VerifyArgs a) {
   const int64_t c = a.c_begin + tile * kBlock + threadIdx.x;
   const int lane = lane_id();
   const int r = lane & (G - 1);
-  if (__ballot(c < a.c_end) == 0) return;  // whole wave past the end
 
   uint32_t xi = 0, yi = 0, alive = 0;
   bool bad = false;
@@ -432,10 +469,13 @@ __global__ __launch_bounds__(kBlock) void k_verify_minhash(VerifyArgs a) {
   uint32_t m = 0;
   uint8_t code = bad ? 0xFF : 0;
   bool emit = false;
+  // (lanes without a candidate take the first lane's x: their rows are its own)
+  const uint32_t x0 = uint32_t(__builtin_amdgcn_readfirstlane(int(xi)));
+  const bool same_x = __ballot(alive != 0 && xi != x0) == 0;
   for (int j = 0; j < L; ++j) {
     if (__ballot(alive != 0) == 0) break;
-    uint32_t own = 0;
-    MinhashStep<G, 0>::template run<K>(a, xi, yi, alive, j, r, own);
+    const uint32_t own = same_x ? minhash_level<K, true>(a, x0, alive ? yi : x0, j, r)
+                                : minhash_level<K, false>(a, xi, alive ? yi : xi, j, r);
     if (alive) {
       m += own;
       if (int(m) < s_min[j]) {
@@ -462,7 +502,9 @@ __global__ __launch_bounds__(kBlock) void k_verify_minhash(VerifyArgs a) {
   } else {
     const double alpha = tab_f64(a.table, 4), beta = tab_f64(a.table, 6);
     const float v = emit ? map_estimate(a.measure, int(m), ((code & 63) + 1) * K, alpha, beta) : 0.f;
-    emit_accepted(a, emit, uint64_t(c), v);
+    if (a.direct) emit_direct(a, emit, uint64_t(c), v);
+    else emit_accepted(a, emit, uint64_t(c), v);
+    if (a.direct) finish_direct(a);
   }
 }
 
@@ -516,6 +558,76 @@ __device__ inline uint32_t agree_at(const uint32_t (&d)[8], int q) {
 }
 
 constexpr int kTailWM = 0, kTailRow16 = 1, kTailRow4 = 2;
+
+// Levels j .. L - 1 of the pair (x, y) with m agreements so far, SW words of each
+// side per step: its code, and whether it is emitted.
+template <int K, int LM, int SW>
+__device__ inline void finish_pair(const VerifyArgs &a, uint32_t x, uint32_t y, int j, uint32_t &m, uint8_t &code,
+                                   bool &emit, const int *s_min, const uint32_t *s_acc, int words) {
+  constexpr bool WM = LM == kTailWM;
+  constexpr int kStepLevels = SW * 32 / K, kLevelWords = K == 64 ? 2 : 1;
+  const int L = a.n_levels;
+  bool done = false;
+  while (!done) {
+    // words [w0, w0 + SW) of both sides (w0: first word of level j; a 16-byte
+    // chunk boundary for rows)
+    int w0 = j * K / 32;
+    if constexpr (!WM) w0 &= ~3;
+    const int base = w0 * 32 / K;   // level of the first loaded hashes
+    const int avail = min(SW, a.row_words - w0);
+    uint32_t d[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    if constexpr (WM) {
+      uint32_t hx[SW], hy[SW];
+#pragma unroll
+      for (int u = 0; u < SW; ++u) {
+        const bool in = SW <= kLevelWords || u < avail;   // (a single level's words are there)
+        hx[u] = in ? a.sig[size_t(w0 + u) * a.n_obj + x] : 0u;
+        hy[u] = in ? a.sig[size_t(w0 + u) * a.n_obj + y] : 0u;
+      }
+#pragma unroll
+      for (int u = 0; u < SW; ++u) d[u] = hx[u] ^ hy[u];
+    } else if constexpr (LM == kTailRow4) {
+      const uint32_t *rx = a.sig + size_t(x) * a.row_words + w0, *ry = a.sig + size_t(y) * a.row_words + w0;
+      uint32_t hx[8], hy[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        hx[u] = u < avail ? rx[u] : 0u;
+        hy[u] = u < avail ? ry[u] : 0u;
+      }
+#pragma unroll
+      for (int u = 0; u < 8; ++u) d[u] = hx[u] ^ hy[u];
+    } else {
+      const u32x4 hx0 = *reinterpret_cast<const u32x4 *>(a.sig + size_t(x) * a.row_words + w0);
+      const u32x4 hy0 = *reinterpret_cast<const u32x4 *>(a.sig + size_t(y) * a.row_words + w0);
+      u32x4 hx1 = hx0, hy1 = hy0;
+      if (avail > 4) {
+        hx1 = *reinterpret_cast<const u32x4 *>(a.sig + size_t(x) * a.row_words + w0 + 4);
+        hy1 = *reinterpret_cast<const u32x4 *>(a.sig + size_t(y) * a.row_words + w0 + 4);
+      }
+      d[0] = hx0.x ^ hy0.x; d[1] = hx0.y ^ hy0.y; d[2] = hx0.z ^ hy0.z; d[3] = hx0.w ^ hy0.w;
+      d[4] = hx1.x ^ hy1.x; d[5] = hx1.y ^ hy1.y; d[6] = hx1.z ^ hy1.z; d[7] = hx1.w ^ hy1.w;
+    }
+    const int q0 = j - base, qn = min(L - base, avail * 32 / K);
+#pragma unroll
+    for (int q = 0; q < kStepLevels; ++q) {
+      if (q >= q0 && q < qn && !done) {
+        m += agree_at<K>(d, q);
+        const int jj = base + q;
+        if (int(m) < s_min[jj]) {
+          code = uint8_t((BLSH_PRUNED << 6) | jj);
+          done = true;
+        } else if ((s_acc[jj * words + (m >> 5)] >> (m & 31)) & 1u) {
+          code = uint8_t((BLSH_ACCEPT_CONC << 6) | jj);
+          emit = done = true;
+        } else if (jj == L - 1) {
+          code = uint8_t((BLSH_ACCEPT_NMAX << 6) | jj);
+          emit = done = true;
+        }
+      }
+    }
+    j = base + qn;
+  }
+}
 
 template <int K, int LM>
 __global__ __launch_bounds__(kBlock) void k_verify_tail(VerifyArgs a) {
@@ -624,6 +736,72 @@ __global__ __launch_bounds__(kBlock) void k_verify_tail(VerifyArgs a) {
     const float v = emit ? map_estimate(a.measure, int(m), ((code & 63) + 1) * K, alpha, beta) : 0.f;
     emit_accepted(a, emit, uint64_t(c), v);
   }
+}
+
+// SRP Algorithm 1 of a call of few candidates, one lane per candidate from its
+// first level to its last: the prefix (when a.pfx) in one round trip, then 8
+// words of each side per step.  Bound by latency: the launch itself (about 6 us
+// between back-to-back calls) and a chain of dependent reads -- ids, prefix,
+// rows -- which more lanes per candidate would not shorten; a second and third
+// launch (queue, tail, flush) cost more than lanes left idle by decided
+// candidates.  1000 candidates of one x, 1024 bits, k = 32: word-major with a
+// prefix 24.5 -> 14.4 us, word-major alone 53.8 -> 14.9, rows 21.8 -> 11.5.
+template <int K, int LM>
+__global__ __launch_bounds__(kBlock) void k_verify_few(VerifyArgs a) {
+  extern __shared__ uint32_t s_acc[];   // n_levels * words accept-bit words
+  __shared__ int s_min[kMaxLevels];
+  constexpr int PL = 128 / K;
+  const int L = a.n_levels;
+  const int words = int(a.table[2]);
+  const int64_t c = a.c_begin + int64_t(blockIdx.x) * kBlock + threadIdx.x;
+  const bool in = c < a.c_end;
+  uint32_t x = 0, y = 0;
+  const bool ok = in && fetch_candidate(a, c, x, y);
+  uint32_t d[4] = {0, 0, 0, 0};
+  if (ok && a.pfx) {
+    const char *pb = reinterpret_cast<const char *>(a.pfx);
+    const uint32_t sb = uint32_t(a.pfx_stride) * 4u;
+    const u32x4 hx = *reinterpret_cast<const u32x4 *>(pb + uint64_t(x) * sb);
+    const u32x4 hy = *reinterpret_cast<const u32x4 *>(pb + uint64_t(y) * sb);
+    d[0] = hx.x ^ hy.x; d[1] = hx.y ^ hy.y; d[2] = hx.z ^ hy.z; d[3] = hx.w ^ hy.w;
+  }
+  if (threadIdx.x < kMaxLevels)
+    s_min[threadIdx.x] = threadIdx.x < L ? int(a.table[kTabMinOff + threadIdx.x]) : 0x7fffffff;
+  for (int i = threadIdx.x; i < L * words; i += kBlock) s_acc[i] = a.table[kTabAccOff + i];
+  __syncthreads();
+  const double alpha = tab_f64(a.table, 4), beta = tab_f64(a.table, 6);
+  uint32_t m = 0;
+  uint8_t code = 0xFF;
+  bool emit = false, open = ok;
+  if (a.pfx) {
+#pragma unroll
+    for (int j = 0; j < PL; ++j) {
+      if (j < L && open) {
+        m += agree_from_xor<K>(d, j);
+        if (int(m) < s_min[j]) {
+          code = uint8_t((BLSH_PRUNED << 6) | j);
+          open = false;
+        } else if ((s_acc[j * words + (m >> 5)] >> (m & 31)) & 1u) {
+          code = uint8_t((BLSH_ACCEPT_CONC << 6) | j);
+          emit = true;
+          open = false;
+        } else if (j == L - 1) {
+          code = uint8_t((BLSH_ACCEPT_NMAX << 6) | j);
+          emit = true;
+          open = false;
+        }
+      }
+    }
+  }
+  if (open) finish_pair<K, LM, 8>(a, x, y, a.pfx ? PL : 0, m, code, emit, s_min, s_acc, words);
+  if (in) {
+    if (!ok) raise_status(a.status, BLSH_EBADID);
+    a.code[c] = code;
+    if (a.m_dbg) a.m_dbg[c] = uint16_t(m);
+  }
+  const float v = emit ? map_estimate(a.measure, int(m), ((code & 63) + 1) * K, alpha, beta) : 0.f;
+  emit_direct(a, emit, uint64_t(c), v);
+  finish_direct(a);
 }
 
 // Sum over aligned groups of G lanes (G = 16 or 64), in every lane of the group.
@@ -1525,7 +1703,10 @@ __global__ void k_zero_i64(int64_t *p) {
 // needed after a call that stopped before its last flush.
 __global__ void k_zero_slices(int64_t *cnt) {
   for (int i = 0; i < 3; ++i) cnt[(size_t(i) * kSlices + threadIdx.x) * kCntStride] = 0;
-  if (threadIdx.x < 2) cnt[(size_t(3) * kSlices + threadIdx.x) * kCntStride] = 0;
+  if (threadIdx.x < 2) {   // the running counts, and the block tickets beside them
+    cnt[(size_t(3) * kSlices + threadIdx.x) * kCntStride] = 0;
+    cnt[(size_t(3) * kSlices + threadIdx.x) * kCntStride + 1] = 0;
+  }
 }
 
 // After each launch (chunk), one block per staging slice, no atomics: every
@@ -1687,6 +1868,24 @@ int launch_exact(blsh_ctx *ctx, const VerifyArgs &a, int64_t max_items, hipStrea
   LaunchScope ls(ctx, s, "exact");
   hipLaunchKernelGGL(k_exact, dim3(nb), dim3(kBlock), 0, s, a);
   return hipGetLastError() == hipSuccess ? BLSH_OK : BLSH_EDEVICE;
+}
+
+// A call of few candidates (a.direct): one launch.
+int launch_verify_few(blsh_ctx *ctx, const VerifyArgs &a, int k, bool word_major, int words, hipStream_t s) {
+  const dim3 nb(unsigned(blocks_for(a.c_end - a.c_begin, kBlock)));
+  const size_t lds = size_t(a.n_levels) * words * 4;
+  const bool row16 = a.row_words % 4 == 0 && (uintptr_t(a.sig) & 15) == 0;
+  LaunchScope ls(ctx, s, "verify_few");
+#define BLSH_F(KK)                                                                                 \
+  if (k == KK) {                                                                                   \
+    if (word_major) hipLaunchKernelGGL((k_verify_few<KK, kTailWM>), nb, dim3(kBlock), lds, s, a);    \
+    else if (row16) hipLaunchKernelGGL((k_verify_few<KK, kTailRow16>), nb, dim3(kBlock), lds, s, a); \
+    else hipLaunchKernelGGL((k_verify_few<KK, kTailRow4>), nb, dim3(kBlock), lds, s, a);            \
+    return hipGetLastError() == hipSuccess ? BLSH_OK : BLSH_EDEVICE;                               \
+  }
+  BLSH_F(16) BLSH_F(32) BLSH_F(64)
+#undef BLSH_F
+  return fail(BLSH_EINVAL, "unsupported k=%d", k);
 }
 
 // words: accept-bit words per level of the launch's table (LDS of the tail).

@@ -14,16 +14,16 @@
 //   rows: at least the 128 hashes one 16-byte load brings) is spilled to the
 //   wave's own region of the measure's survivor queue (ballot compaction, no
 //   atomics); when the region is full it simply continues in registers.
-// Phase 2 (k_batch_phase2): persistent blocks drain the survivor queues with
-//   every lane busy: one lane per SRP survivor (the words of the next levels
-//   loaded ahead), one group of k/4 lanes per minhash survivor, running the
-//   remaining levels; a block takes the regions it drains as one list.
+// Phase 2 (k_batch_offsets, k_batch_phase2): the survivor queues are cut into
+//   equal shares for the waves of a second grid: one lane per SRP survivor, one
+//   group of k/4 lanes per minhash survivor, running the remaining levels, up to
+//   four levels' words loaded ahead.
 //
 // Accepted pairs are staged in slices (as in the single-call paths) and
 // appended to the caller's list by k_batch_flush at the end of the batch.
 //
 // The kernels read all their arguments from one device-resident BatchBlock,
-// so the graph that holds [reset, phase 1 x 2, phase 2, flush] is captured
+// so the graph that holds [phase 1 x 2, offsets, phase 2, flush] is captured
 // once per (k pair, tile shapes, grid) and replayed for any batch: each call
 // only refreshes the block and the tile prefix sums.
 #include <algorithm>
@@ -89,14 +89,19 @@ struct BatchBlock {
   // accepted-pair staging (as in the single-call paths): kSlices slices of
   // st_cap entries, counts at acc_cnt[s * kCntStride], appended to the list by
   // k_batch_flush; entries past a slice's capacity go to the list directly at
-  // positions from the running count *acc_total
-  int64_t *acc_cnt;
+  // positions from the running count *acc_total.  Batches alternate between two
+  // sets of these counts: the flush of one leaves those of the next (acc_next,
+  // laid out as acc_cnt with the running count behind) zero.
+  int64_t *acc_cnt, *acc_next;
   uint64_t *st_idx;
   float *st_val;
   int64_t st_cap;
   int64_t *acc_total;
   uint4 *spill[2];               // survivor queue per measure: spill_region entries per phase-1 wave
   uint32_t *spill_count[2];     // entries each phase-1 wave stored in its region
+  // the regions that hold entries, in order (k_batch_offsets): x = entries of all
+  // before, y = wave; at [spill_waves] the total and the number of such regions
+  uint2 *spill_used[2];
   int64_t spill_region;
   int32_t spill_waves;          // waves of the phase-1 grid
   int32_t inreg_levels;
@@ -482,30 +487,99 @@ __global__ __launch_bounds__(kBBlock) void k_batch_phase1(const BatchBlock *__re
 // ---------------------------------------------------------------------------
 // phase 2: spilled survivors
 // ---------------------------------------------------------------------------
-// Block b drains the regions of phase-1 waves b, b + grid, ... taken together
-// as one list: a region holds few survivors, and each survivor is a chain of
-// dependent level loads, so passes over the concatenation overlap the chains
-// of all its regions.  Item i of that list: its wave and its entry there.
-__device__ inline bool region_item(const uint32_t *count, int64_t n_waves, int64_t i, int64_t &w_out,
-                                   int64_t &k_out) {
-  int64_t acc = 0;
-  for (int64_t w = blockIdx.x; w < n_waves; w += gridDim.x) {
-    const int64_t n = count[w];
-    if (i < acc + n) {
-      w_out = w;
-      k_out = i - acc;
-      return true;
+// The regions that hold entries, with the entries before each (one block per
+// measure).  Empty ones are left out, so any 64 consecutive items of the queue
+// lie in at most 64 consecutive regions of the list.
+constexpr int kOffsetsBlock = 1024;
+static_assert(kBBlock / kWave == 4, "four waves a block: the counts are whole 16-byte groups");
+__global__ __launch_bounds__(kOffsetsBlock) void k_batch_offsets(const BatchBlock *__restrict__ Bp) {
+  const BatchBlock &B = *Bp;
+  __shared__ uint64_t s_sum[2][kOffsetsBlock / kWave];
+  const uint4 *cnt = reinterpret_cast<const uint4 *>(B.spill_count[blockIdx.x]);
+  uint2 *used = B.spill_used[blockIdx.x];
+  const int W4 = B.spill_waves / 4, t = threadIdx.x;
+  // regions in the high half, entries in the low
+  uint64_t carry = 0;
+  for (int w0 = 0, buf = 0; w0 < W4; w0 += kOffsetsBlock, buf ^= 1) {
+    uint4 c = make_uint4(0, 0, 0, 0);
+    if (w0 + t < W4) c = cnt[w0 + t];
+    const uint32_t n[4] = {c.x, c.y, c.z, c.w};
+    uint64_t own = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) own += (n[i] ? uint64_t(1) << 32 : 0) + n[i];
+    uint64_t v = own;
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {
+      const uint64_t u = __shfl_up(v, o);
+      if (lane_id() >= o) v += u;
     }
-    acc += n;
+    if (lane_id() == kWave - 1) s_sum[buf][t / kWave] = v;
+    __syncthreads();
+    uint64_t before = carry + v - own;
+#pragma unroll
+    for (int w = 0; w < kOffsetsBlock / kWave; ++w) {
+      const uint64_t u = s_sum[buf][w];
+      if (w < t / kWave) before += u;
+      carry += u;
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      if (n[i]) {
+        used[before >> 32] = make_uint2(uint32_t(before), uint32_t((w0 + t) * 4 + i));
+        before += (uint64_t(1) << 32) + n[i];
+      }
+    }
   }
-  return false;
+  if (t == 0) used[B.spill_waves] = make_uint2(uint32_t(carry), uint32_t(carry >> 32));
 }
 
-__device__ inline int64_t block_region_total(const uint32_t *count, int64_t n_waves) {
-  int64_t t = 0;
-  for (int64_t w = blockIdx.x; w < n_waves; w += gridDim.x) t += count[w];
-  return t;
+// Entries and regions of a measure's queue.
+__device__ inline uint2 queue_end(const BatchBlock &B, int meas) {
+  const uint32_t *p = reinterpret_cast<const uint32_t *>(B.spill_used[meas] + B.spill_waves);
+  return make_uint2(ld_uniform(p), ld_uniform(p + 1));
 }
+
+// Entry i0 + k (k < 64, this lane's) of a measure's queue; `end` = (total, regions).
+// Called by all lanes of the wave; lanes past the total take the last entry.
+__device__ inline uint4 spilled_item(const BatchBlock &B, int meas, uint2 end, uint32_t i0, uint32_t k) {
+  const uint2 *used = B.spill_used[meas];
+  const uint32_t n = end.y, lane = lane_id();
+  // last region starting at or before i0, 64 probes at a time
+  uint32_t lo = 0, len = n;
+  while (len > kWave) {
+    const uint32_t step = (len + kWave - 1) / kWave, at = lo + lane * step;
+    const uint64_t mask = __ballot(at < lo + len && used[min(at, n - 1)].x <= i0);   // lane 0's always is
+    const uint32_t hit = uint32_t(__popcll(mask)) - 1;
+    len = min(step, len - hit * step);
+    lo += hit * step;
+  }
+  uint2 u = used[min(lo + lane, n - 1)];
+  const uint32_t skip = uint32_t(__popcll(__ballot(lane < len && u.x <= i0))) - 1;
+  if (skip != 0) {
+    lo += skip;
+    u = used[min(lo + lane, n - 1)];
+  }
+  // this lane's region among the 64 from there
+  const uint32_t i = min(i0 + k, end.x - 1);
+  int a = 0;
+#pragma unroll
+  for (int o = kWave / 2; o > 0; o >>= 1) {
+    const uint32_t f = uint32_t(__shfl(int(u.x), a + o));
+    if (lo + a + o < n && f <= i) a += o;
+  }
+  const uint32_t first = uint32_t(__shfl(int(u.x), a)), w = uint32_t(__shfl(int(u.y), a));
+  return B.spill[meas][int64_t(w) * B.spill_region + (i - first)];
+}
+
+// A survivor's decisions: the thresholds of a level, and the accept test (a
+// compare where the level's accept set is an interval, as its table says).
+struct LevelRule {
+  const uint32_t *tab;
+  int words;
+  bool interval;
+  __device__ explicit LevelRule(const uint32_t *t) : tab(t), words(int(t[2])), interval((t[kTabFlagOff] & 1u) != 0) {}
+  __device__ bool accepted(int j, int m, int alo) const { return interval ? m >= alo : accept_bit(tab, words, j, m); }
+};
 
 // SRP words of level j of q and y (k = 16: the word holding the level)
 template <int K>
@@ -535,53 +609,67 @@ __device__ inline uint32_t level_agree(const LevelWords<K> &w, int j) {
   else return 16u - __popc(((w.q[0] ^ w.y[0]) >> ((j & 1) * 16)) & 0xFFFFu);
 }
 
-// SRP levels whose words are loaded before the first of them is decided: four
-// shorten the chain of a deep survivor (dense serving 50 -> 41 ms); at k = 64
-// a level is already two words per side and the loads past the decision cost
-// more than they save.
+// Levels of a survivor loaded together.  A survivor of the first levels is as
+// often as not decided at its next one, so the first step of k = 64 (two words
+// per side and level) and of minhash (a line per side) loads that alone; what is
+// left by then tends to go deep, and four levels at a time shorten its chain of
+// dependent reads.
 template <int K>
-constexpr int phase2_ahead() { return K == 64 ? 1 : 4; }
+constexpr int phase2_first() { return K == 64 ? 1 : 4; }
+constexpr int kPhase2Ahead = 4;
 
+// Every wave takes an equal share of each queue, by items of all phase-1 waves:
+// related candidates have neighbouring ids, so single waves of phase 1 hold
+// thousands of survivors where most hold none.  Bound by the chain of a survivor's
+// dependent reads (entry, list, table, rows by steps).  512 lists of 56 M
+// candidates, 0.6 M survivors (k = 16 / 64): 316 us with each block draining the
+// regions of its own phase-1 waves one level at a time, 66 + 5 (the offsets) now;
+// 64 lists of 6.9 M: the whole batch 187 -> 118 us.
 template <int KJ, int KC>
 __global__ __launch_bounds__(kBBlock) void k_batch_phase2(const BatchBlock *__restrict__ Bp) {
   constexpr int G = KJ / 4;
-  constexpr int AHEAD = phase2_ahead<KC>();
   const BatchBlock &B = *Bp;
-  const int64_t R = B.spill_region;
+  const int lane = lane_id();
+  const uint32_t wave = blockIdx.x * (kBBlock / kWave) + uint32_t(__builtin_amdgcn_readfirstlane(int(threadIdx.x) / kWave));
+  const uint32_t waves = gridDim.x * (kBBlock / kWave);
   // SRP survivors: one lane each
   {
     const SigView &S = B.sig[BLSH_COSINE];
-    const uint32_t *cnt = B.spill_count[BLSH_COSINE];
-    const int64_t total = block_region_total(cnt, B.spill_waves);
-    for (int64_t i0 = 0; i0 < total; i0 += kBBlock) {
-      int64_t w = 0, k = 0;
-      const bool act = region_item(cnt, B.spill_waves, i0 + threadIdx.x, w, k);
+    const uint2 end = queue_end(B, BLSH_COSINE);
+    const uint32_t total = end.x;
+    for (uint64_t i0 = uint64_t(wave) * kWave; i0 < total; i0 += uint64_t(waves) * kWave) {
+      const bool act = i0 + lane < total;
       int64_t pos = 0;
       uint32_t m = 0;
       uint8_t code = 0;
       bool emit = false;
+      const uint4 e = spilled_item(B, BLSH_COSINE, end, uint32_t(i0), lane);
       if (act) {
-        const uint4 e = B.spill[BLSH_COSINE][w * R + k];
         pos = int64_t(uint64_t(e.x) | (uint64_t(e.y) << 32));
         const BatchList Ls = B.lists[e.z];
-        const uint32_t *tab = B.tables[Ls.table];
+        const LevelRule T(B.tables[Ls.table]);
         const int L = B.n_levels[Ls.table];
-        const int words = int(tab[2]);
         m = e.w & 0xFFFFu;
         const uint32_t q = Ls.query, yv = B.cand[pos];
         bool done = false;
-        for (int j0 = int(e.w >> 16); j0 < L && !done; j0 += AHEAD) {
-          LevelWords<KC> lw[AHEAD];
+        for (int j0 = int(e.w >> 16), n = phase2_first<KC>(); !done; j0 += n, n = kPhase2Ahead) {
+          const int j1 = min(L, j0 + n);
+          LevelWords<KC> lw[kPhase2Ahead];
+          int lo[kPhase2Ahead], alo[kPhase2Ahead];
 #pragma unroll
-          for (int d = 0; d < AHEAD; ++d)
-            if (j0 + d < L) load_level<KC>(S, q, yv, j0 + d, lw[d]);
+          for (int d = 0; d < kPhase2Ahead; ++d)
+            if (j0 + d < j1) {
+              load_level<KC>(S, q, yv, j0 + d, lw[d]);
+              lo[d] = int(T.tab[kTabMinOff + j0 + d]);
+              alo[d] = int(T.tab[kTabAloOff + j0 + d]);
+            }
 #pragma unroll
-          for (int d = 0; d < AHEAD; ++d) {
+          for (int d = 0; d < kPhase2Ahead; ++d) {
             const int j = j0 + d;
-            if (done || j >= L) break;
+            if (done || j >= j1) break;
             m += level_agree<KC>(lw[d], j);
-            if (int(m) < int(tab[kTabMinOff + j])) { code = uint8_t((BLSH_PRUNED << 6) | j); done = true; }
-            else if (accept_bit(tab, words, j, int(m))) { code = uint8_t((BLSH_ACCEPT_CONC << 6) | j); emit = true; done = true; }
+            if (int(m) < lo[d]) { code = uint8_t((BLSH_PRUNED << 6) | j); done = true; }
+            else if (T.accepted(j, int(m), alo[d])) { code = uint8_t((BLSH_ACCEPT_CONC << 6) | j); emit = true; done = true; }
             else if (j == L - 1) { code = uint8_t((BLSH_ACCEPT_NMAX << 6) | j); emit = true; done = true; }
           }
         }
@@ -595,55 +683,57 @@ __global__ __launch_bounds__(kBBlock) void k_batch_phase2(const BatchBlock *__re
   // minhash survivors: one group of G lanes each
   {
     const SigView &S = B.sig[BLSH_JACCARD];
-    const uint32_t *cnt = B.spill_count[BLSH_JACCARD];
-    const int64_t total = block_region_total(cnt, B.spill_waves);
-    constexpr int PER_BLOCK = kBBlock / G;
-    const int g = threadIdx.x / G, r = threadIdx.x % G;
-    for (int64_t i0 = 0; i0 < total; i0 += PER_BLOCK) {
-      int64_t w = 0, k = 0;
-      const bool act = region_item(cnt, B.spill_waves, i0 + g, w, k);
+    const uint2 end = queue_end(B, BLSH_JACCARD);
+    const uint32_t total = end.x;
+    constexpr int PER_WAVE = kWave / G;
+    const int g = lane / G, r = lane % G;
+    for (uint64_t i0 = uint64_t(wave) * PER_WAVE; i0 < total; i0 += uint64_t(waves) * PER_WAVE) {
+      const bool act = i0 + g < total;
       int64_t pos = 0;
-      uint32_t m = 0, q = 0, yv = 0;
-      int j = 0, L = 0, words = 0;
-      const uint32_t *tab = nullptr;
-      if (act) {
-        const uint4 e = B.spill[BLSH_JACCARD][w * R + k];
-        pos = int64_t(uint64_t(e.x) | (uint64_t(e.y) << 32));
-        const BatchList Ls = B.lists[e.z];
-        tab = B.tables[Ls.table];
-        L = B.n_levels[Ls.table];
-        words = int(tab[2]);
-        m = e.w & 0xFFFFu;
-        j = int(e.w >> 16);
-        q = Ls.query;
-        yv = B.cand[pos];
-      }
-      bool alive = act && j < L;
+      uint32_t m = 0;
       uint8_t code = 0;
       bool emit = false;
-      while (__ballot(alive) != 0) {
-        uint32_t c = 0;
-        if (alive) {
-          const uint4 hq = *reinterpret_cast<const uint4 *>(S.data + size_t(q) * S.row_words + j * KJ + 4 * r);
-          const uint4 hy = *reinterpret_cast<const uint4 *>(S.data + size_t(yv) * S.row_words + j * KJ + 4 * r);
-          c = uint32_t(hq.x == hy.x) + uint32_t(hq.y == hy.y) + uint32_t(hq.z == hy.z) + uint32_t(hq.w == hy.w);
+      const uint4 e = spilled_item(B, BLSH_JACCARD, end, uint32_t(i0), g);
+      if (act) {   // (a group's lanes agree on everything below)
+        pos = int64_t(uint64_t(e.x) | (uint64_t(e.y) << 32));
+        const BatchList Ls = B.lists[e.z];
+        const LevelRule T(B.tables[Ls.table]);
+        const int L = B.n_levels[Ls.table];
+        m = e.w & 0xFFFFu;
+        const uint32_t *rq = S.data + size_t(Ls.query) * S.row_words + 4 * r;
+        const uint32_t *ry = S.data + size_t(B.cand[pos]) * S.row_words + 4 * r;
+        bool done = false;
+        for (int j0 = int(e.w >> 16), n = 1; !done; j0 += n, n = kPhase2Ahead) {
+          const int j1 = min(L, j0 + n);
+          uint4 hq[kPhase2Ahead], hy[kPhase2Ahead];
+          int lo[kPhase2Ahead], alo[kPhase2Ahead];
+#pragma unroll
+          for (int d = 0; d < kPhase2Ahead; ++d)
+            if (j0 + d < j1) {
+              hq[d] = *reinterpret_cast<const uint4 *>(rq + (j0 + d) * KJ);
+              hy[d] = *reinterpret_cast<const uint4 *>(ry + (j0 + d) * KJ);
+              lo[d] = int(T.tab[kTabMinOff + j0 + d]);
+              alo[d] = int(T.tab[kTabAloOff + j0 + d]);
+            }
+#pragma unroll
+          for (int d = 0; d < kPhase2Ahead; ++d) {
+            const int j = j0 + d;
+            if (done || j >= j1) break;
+            m += group_sum<G>(uint32_t(hq[d].x == hy[d].x) + uint32_t(hq[d].y == hy[d].y) +
+                              uint32_t(hq[d].z == hy[d].z) + uint32_t(hq[d].w == hy[d].w));
+            if (int(m) < lo[d]) { code = uint8_t((BLSH_PRUNED << 6) | j); done = true; }
+            else if (T.accepted(j, int(m), alo[d])) { code = uint8_t((BLSH_ACCEPT_CONC << 6) | j); emit = true; done = true; }
+            else if (j == L - 1) { code = uint8_t((BLSH_ACCEPT_NMAX << 6) | j); emit = true; done = true; }
+          }
         }
-        c = group_sum<G>(c);
-        if (alive) {
-          m += c;
-          if (int(m) < int(tab[kTabMinOff + j])) { code = uint8_t((BLSH_PRUNED << 6) | j); alive = false; }
-          else if (accept_bit(tab, words, j, int(m))) { code = uint8_t((BLSH_ACCEPT_CONC << 6) | j); emit = true; alive = false; }
-          else if (j == L - 1) { code = uint8_t((BLSH_ACCEPT_NMAX << 6) | j); emit = true; alive = false; }
-          ++j;
+        if (r == 0) {
+          B.code[pos] = code;
+          if (B.m_dbg) B.m_dbg[pos] = uint16_t(m);
         }
       }
-      if (act && r == 0) {
-        B.code[pos] = code;
-        if (B.m_dbg) B.m_dbg[pos] = uint16_t(m);
-      }
-      const bool e = emit && r == 0;
-      const float v = e ? map_estimate(BLSH_JACCARD, int(m), ((code & 63) + 1) * KJ, B.alpha, B.beta) : 0.f;
-      emit_block(B, e, pos, v);
+      emit = emit && r == 0;
+      const float v = emit ? map_estimate(BLSH_JACCARD, int(m), ((code & 63) + 1) * KJ, B.alpha, B.beta) : 0.f;
+      emit_block(B, emit, pos, v);
     }
   }
 }
@@ -829,18 +919,21 @@ __global__ __launch_bounds__(kBBlock) void k_batch_exhaustive(const BatchBlock *
   }
 }
 
-// Clears the running count and the staging counts: one block of kSlices
-// threads.
-__global__ void k_batch_reset(const BatchBlock *__restrict__ Bp) {
-  const BatchBlock &B = *Bp;
-  B.acc_cnt[threadIdx.x * kCntStride] = 0;
-  if (threadIdx.x == 0) *B.acc_total = 0;
+// Clears both sets of staging counts and running counts (one block of kSlices
+// threads): before the first batch, and after one that was not launched whole.
+__global__ void k_batch_reset(int64_t *cnt) {
+  for (int set = 0; set < 2; ++set) {
+    int64_t *c = cnt + set * (size_t(kSlices) + 1) * kCntStride;
+    c[threadIdx.x * kCntStride] = 0;
+    if (threadIdx.x == 0) c[size_t(kSlices) * kCntStride] = 0;
+  }
 }
 
 // Appends the staging slices to the accepted list, one block per slice, no
 // atomics: every block scans the kSlices counts, block s copies slice s after
 // the slices before it and after the entries written directly; block 0
-// stores the final count to *n_acc (which no block reads).
+// stores the final count to *n_acc (which no block reads).  Leaves the next
+// batch's counts zero.
 __global__ __launch_bounds__(kBBlock) void k_batch_flush(const BatchBlock *__restrict__ Bp) {
   static_assert(kSlices == kBBlock, "one staging slice per thread of a block");
   const BatchBlock &B = *Bp;
@@ -878,7 +971,11 @@ __global__ __launch_bounds__(kBBlock) void k_batch_flush(const BatchBlock *__res
     }
   }
   if (trunc) raise_status(B.status, BLSH_ETRUNCATED);
-  if (sl == 0 && t == 0) *B.n_acc = s_base + s_total;
+  if (t == 0) B.acc_next[size_t(sl) * kCntStride] = 0;
+  if (sl == 0 && t == 0) {
+    B.acc_next[size_t(kSlices) * kCntStride] = 0;
+    *B.n_acc = s_base + s_total;
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -890,14 +987,17 @@ struct BatchState {
   BatchList *d_lists = nullptr, *h_lists = nullptr;
   int64_t *d_prefix = nullptr, *h_prefix = nullptr;
   int64_t lists_cap = 0;
-  // staging: kSlices counters (kCntStride apart), the running count, then
-  // kSlices x kBatchStage entries
+  // staging: two sets of kSlices counters (kCntStride apart) and the running
+  // count, then kSlices x kBatchStage entries
   int64_t *d_stage_cnt = nullptr;
+  int stage_set = 0;                    // set of the next batch; its counts are zero
+  bool stage_dirty = true;              // unless this is set
   uint64_t *d_st_idx = nullptr;
   float *d_st_val = nullptr;
   uint4 *d_spill[2] = {nullptr, nullptr};
   int64_t spill_cap = 0;
   uint32_t *d_spill_count = nullptr;    // [2][spill_waves_cap]
+  uint2 *d_spill_used = nullptr;        // [2][spill_waves_cap + 1]
   int64_t spill_waves_cap = 0;
   hipEvent_t staged{};
   bool staged_valid = false;
@@ -929,6 +1029,7 @@ static void batch_free(BatchState *b) {
   if (b->d_st_val) (void)hipFree(b->d_st_val);
   for (auto *p : b->d_spill) if (p) (void)hipFree(p);
   if (b->d_spill_count) (void)hipFree(b->d_spill_count);
+  if (b->d_spill_used) (void)hipFree(b->d_spill_used);
   if (b->staged_valid) (void)hipEventDestroy(b->staged);
   if (b->cap_stream) (void)hipStreamDestroy(b->cap_stream);
   delete b;
@@ -942,7 +1043,7 @@ static int batch_state(blsh_ctx *ctx, BatchState **out) {
     if (!b) return fail(BLSH_ENOMEM, "host allocation failed");
     if (hipMalloc(&b->d_block, sizeof(BatchBlock)) != hipSuccess ||
         hipHostMalloc(reinterpret_cast<void **>(&b->h_block), sizeof(BatchBlock), hipHostMallocDefault) != hipSuccess ||
-        hipMalloc(&b->d_stage_cnt, (size_t(kSlices) + 1) * kCntStride * sizeof(int64_t)) != hipSuccess ||
+        hipMalloc(&b->d_stage_cnt, 2 * (size_t(kSlices) + 1) * kCntStride * sizeof(int64_t)) != hipSuccess ||
         hipMalloc(&b->d_st_idx, size_t(kSlices) * kBatchStage * sizeof(uint64_t)) != hipSuccess ||
         hipMalloc(&b->d_st_val, size_t(kSlices) * kBatchStage * sizeof(float)) != hipSuccess ||
         hipStreamCreateWithFlags(&b->cap_stream, hipStreamNonBlocking) != hipSuccess ||
@@ -983,9 +1084,12 @@ static int grow_spill_counts(BatchState *b, int64_t waves) {
   if (b->spill_waves_cap >= waves) return BLSH_OK;
   BLSH_HIP(hipDeviceSynchronize());
   if (b->d_spill_count) (void)hipFree(b->d_spill_count);
+  if (b->d_spill_used) (void)hipFree(b->d_spill_used);
   b->d_spill_count = nullptr;
+  b->d_spill_used = nullptr;
   b->spill_waves_cap = 0;
-  if (hipMalloc(&b->d_spill_count, size_t(2 * waves) * sizeof(uint32_t)) != hipSuccess)
+  if (hipMalloc(&b->d_spill_count, size_t(2 * waves) * sizeof(uint32_t)) != hipSuccess ||
+      hipMalloc(&b->d_spill_used, size_t(2 * (waves + 1)) * sizeof(uint2)) != hipSuccess)
     return fail(BLSH_ENOMEM, "spill counts");
   b->spill_waves_cap = waves;
   return BLSH_OK;
@@ -1017,12 +1121,12 @@ static void launch_phase1_mh(const BatchBlock *blk, int tm, int grid1, hipStream
 
 template <int KJ, int KC>
 static void launch_batch_kernels(BatchState *b, const BatchState::GraphKey &gk, hipStream_t s) {
-  hipLaunchKernelGGL(k_batch_reset, dim3(1), dim3(kSlices), 0, s, b->d_block);
   if (gk.mode == 1) {
     hipLaunchKernelGGL((k_batch_exhaustive<KJ, KC>), dim3(gk.grid1), dim3(kBBlock), 0, s, b->d_block);
   } else {
     launch_phase1_srp<KC>(b->d_block, gk.ts, gk.grid1, s);
     launch_phase1_mh<KJ>(b->d_block, gk.tm, gk.grid1, s);
+    hipLaunchKernelGGL(k_batch_offsets, dim3(2), dim3(kOffsetsBlock), 0, s, b->d_block);
     hipLaunchKernelGGL((k_batch_phase2<KJ, KC>), dim3(gk.grid2), dim3(kBBlock), 0, s, b->d_block);
   }
   hipLaunchKernelGGL(k_batch_flush, dim3(kSlices), dim3(kBBlock), 0, s, b->d_block);
@@ -1171,8 +1275,10 @@ int verify_batched(blsh_ctx *ctx, const blsh_list_desc *lists, int64_t n_lists, 
     B.n_acc = res->n_accepted;
     B.m_dbg = res->m_debug;
     B.status = ctx->d_status;
-    B.acc_cnt = b->d_stage_cnt;
-    B.acc_total = b->d_stage_cnt + size_t(kSlices) * kCntStride;
+    const size_t set_words = (size_t(kSlices) + 1) * kCntStride;
+    B.acc_cnt = b->d_stage_cnt + size_t(b->stage_set) * set_words;
+    B.acc_next = b->d_stage_cnt + size_t(b->stage_set ^ 1) * set_words;
+    B.acc_total = B.acc_cnt + size_t(kSlices) * kCntStride;
     B.st_idx = b->d_st_idx;
     B.st_val = b->d_st_val;
     B.st_cap = ctx->tuning.acc_stage_cap > 0
@@ -1184,6 +1290,8 @@ int verify_batched(blsh_ctx *ctx, const blsh_list_desc *lists, int64_t n_lists, 
     B.spill_region = spill_cap / B.spill_waves;
     B.spill_count[0] = b->d_spill_count;
     B.spill_count[1] = b->d_spill_count + B.spill_waves;
+    B.spill_used[0] = b->d_spill_used;
+    B.spill_used[1] = b->d_spill_used + B.spill_waves + 1;
     B.inreg_levels = inreg;
     BLSH_HIP(hipMemcpyAsync(b->d_block, b->h_block, sizeof(BatchBlock), hipMemcpyHostToDevice, s));
     // the pinned staging may be rewritten by the next call once these copies ran
@@ -1198,11 +1306,18 @@ int verify_batched(blsh_ctx *ctx, const blsh_list_desc *lists, int64_t n_lists, 
     if (r2) return r2;
     const int ts = mode ? kExSrpTile : c.ts, tm = mode ? kExMhTile : c.tm;
     if ((r2 = prepare(c.kj, c.kc, ts, tm, c.inreg, grid1))) return r2;
-    const int grid2 = std::max(1, ctx->n_cu * 4);
+    const int grid2 = std::max(1, ctx->n_cu * 6);
     hipGraphExec_t ex;
     if ((r2 = get_graph(b, BatchState::GraphKey{mode, c.kj, c.kc, ts, tm, grid1, grid2}, &ex))) return r2;
+    if (b->stage_dirty) {
+      hipLaunchKernelGGL(k_batch_reset, dim3(1), dim3(kSlices), 0, s, b->d_stage_cnt);
+      BLSH_HIP(hipGetLastError());
+    }
+    b->stage_dirty = true;
     LaunchScope ls(ctx, s, mode ? "batched_exhaustive_graph" : "batched_graph");
     BLSH_HIP(hipGraphLaunch(ex, s));
+    b->stage_dirty = false;
+    b->stage_set ^= 1;
     return BLSH_OK;
   };
 

@@ -47,6 +47,10 @@ constexpr int kMhTileDefault = 64;
 constexpr int kExSrpTile = 1024;   // comparator: candidates per SRP block tile
 constexpr int kExMhTile = 256;     // comparator: candidates per minhash block tile
 constexpr int kXcds = 8;           // phase 1: list tiles split in kXcds position ranges, one per XCD
+// survivor queue of a small batch: 128 entries a wave of the largest grid the
+// autotuner takes.  A wave whose region is full runs its tile to the last level
+// alone, which takes a batch of 34 K candidates 22 us longer.
+constexpr int64_t kMinSpill = int64_t(1) << 20;
 constexpr int64_t kBatchStage = 4096;   // accepted-pair staging entries per slice
 
 struct BatchList {
@@ -212,16 +216,52 @@ __device__ inline uint32_t prefix_agree(const uint32_t *d, int j) {
   else return 16u - __popc((d[j >> 1] >> ((j & 1) * 16)) & 0xFFFFu);
 }
 
-// 64 P consecutive candidates of one SRP list: candidate base + 64 p + lane.
+// What a wave keeps of a list from tile to tile (uniform).
+struct ListState {
+  int64_t end;              // one past the list's last candidate
+  uint32_t query;
+  int32_t id;
+  const uint32_t *tab;
+  int L, words;
+  bool interval;            // the table's accept sets are intervals (thresholds at kTabAloOff)
+};
+
+__device__ inline ListState list_state(const BatchBlock &B, int64_t l, const BatchList &Ls) {
+  ListState st;
+  st.end = Ls.offset + Ls.length;
+  st.query = Ls.query;
+  st.id = int32_t(l);
+  st.tab = ld_uniform(B.tables + Ls.table);
+  st.L = ld_uniform(B.n_levels + Ls.table);
+  st.words = int(ld_uniform(st.tab + 2));
+  st.interval = (ld_uniform(st.tab + kTabFlagOff) & 1u) != 0;
+  return st;
+}
+
+// Accept test of level j; alo: its interval's start.
+__device__ inline bool accepted_at(const ListState &st, int j, int m, int alo) {
+  return st.interval ? m >= alo : accept_bit(st.tab, st.words, j, m);
+}
+
+// Candidates base + 64 p + lane below end.
+template <int P>
+__device__ inline void load_ids(const BatchBlock &B, int64_t base, int64_t end, uint32_t (&y)[P]) {
+#pragma unroll
+  for (int p = 0; p < P; ++p) {
+    const int64_t c = base + p * kWave + lane_id();
+    y[p] = c < end ? __builtin_nontemporal_load(B.cand + c) : 0u;
+  }
+}
+
+// 64 P consecutive candidates of one SRP list: candidate base + 64 p + lane,
+// its id in y[p].
 template <int K, int P>
-__device__ void srp_tile(const BatchBlock &B, const BatchList &Ls, int32_t list_id, int64_t base,
-                         const uint32_t *tab, int L, int64_t wave, uint32_t &n_spill) {
+__device__ inline void srp_tile(const BatchBlock &B, const SigView &S, const ListState &st, int64_t base,
+                                const uint32_t (&ids)[P], int64_t wave, uint32_t &n_spill) {
   constexpr int PL = 128 / K;          // levels held by a 128-bit prefix
-  const SigView S = B.sig[BLSH_COSINE];
-  const int words = int(ld_uniform(tab + 2));
+  const int L = st.L;
   const int lane = lane_id();
-  const int64_t end = Ls.offset + Ls.length;
-  const uint32_t q = Ls.query;
+  const uint32_t q = st.query;
   const bool q_ok = q < S.n_obj;
   // a prefix view (the caller's prefix array, or object-major rows that a
   // 16-byte load can start): one gather per side serves the first 128 hashes
@@ -229,11 +269,9 @@ __device__ void srp_tile(const BatchBlock &B, const BatchList &Ls, int32_t list_
   uint32_t y[P], alive = 0, bad = 0, in = 0;
 #pragma unroll
   for (int p = 0; p < P; ++p) {
-    const int64_t c = base + p * kWave + lane;
-    y[p] = 0;
-    if (c < end) {
+    y[p] = ids[p];
+    if (base + p * kWave + lane < st.end) {
       in |= 1u << p;
-      y[p] = __builtin_nontemporal_load(B.cand + c);
       if (q_ok && y[p] < S.n_obj) alive |= 1u << p; else { bad |= 1u << p; y[p] = 0; }
     }
   }
@@ -242,10 +280,10 @@ __device__ void srp_tile(const BatchBlock &B, const BatchList &Ls, int32_t list_
 #pragma unroll
   for (int p = 0; p < P; ++p) { m[p] = 0; code[p] = 0; }
   auto decide = [&](int p, int j) {
-    if (int(m[p]) < int(ld_uniform(tab + kTabMinOff + j))) {
+    if (int(m[p]) < int(ld_uniform(st.tab + kTabMinOff + j))) {
       code[p] = uint8_t((BLSH_PRUNED << 6) | j);
       alive &= ~(1u << p);
-    } else if (accept_bit(tab, words, j, int(m[p]))) {
+    } else if (accepted_at(st, j, int(m[p]), int(ld_uniform(st.tab + kTabAloOff + j)))) {
       code[p] = uint8_t((BLSH_ACCEPT_CONC << 6) | j);
       alive &= ~(1u << p);
       emit |= 1u << p;
@@ -300,7 +338,7 @@ __device__ void srp_tile(const BatchBlock &B, const BatchList &Ls, int32_t list_
   if (J < L) {
     uint4 e[P];
 #pragma unroll
-    for (int p = 0; p < P; ++p) e[p] = spill_entry(base + p * kWave + lane, uint32_t(list_id), m[p], uint32_t(J));
+    for (int p = 0; p < P; ++p) e[p] = spill_entry(base + p * kWave + lane, uint32_t(st.id), m[p], uint32_t(J));
     alive &= ~spill_tile<P>(B, BLSH_COSINE, wave, n_spill, alive, e);
   }
   word_levels(J, L);
@@ -326,27 +364,23 @@ __device__ void srp_tile(const BatchBlock &B, const BatchList &Ls, int32_t list_
 // the level), with the rows of a pass loaded for all P candidates before any
 // comparison.
 template <int K, int P>
-__device__ void minhash_tile(const BatchBlock &B, const BatchList &Ls, int32_t list_id, int64_t base,
-                             const uint32_t *tab, int L, int64_t wave, uint32_t &n_spill) {
+__device__ inline void minhash_tile(const BatchBlock &B, const SigView &S, const ListState &st, int64_t base,
+                                    const uint32_t (&ids)[P], int64_t wave, uint32_t &n_spill) {
   constexpr int G = K / 4;
   constexpr int CH = G < 8 ? G : 8;      // rows in flight per pass and candidate
-  const SigView S = B.sig[BLSH_JACCARD];
-  const int words = int(ld_uniform(tab + 2));
-  const int64_t end = Ls.offset + Ls.length;
+  const int L = st.L;
   const int lane = lane_id(), r = lane & (G - 1);
-  const uint32_t q = Ls.query;
+  const uint32_t q = st.query;
   const bool q_ok = q < S.n_obj;
   uint32_t y[P], m[P], alive = 0, bad = 0, in = 0, emit = 0;
   uint8_t code[P];
 #pragma unroll
   for (int p = 0; p < P; ++p) {
-    const int64_t c = base + p * kWave + lane;
-    y[p] = 0;
+    y[p] = ids[p];
     m[p] = 0;
     code[p] = 0;
-    if (c < end) {
+    if (base + p * kWave + lane < st.end) {
       in |= 1u << p;
-      y[p] = __builtin_nontemporal_load(B.cand + c);
       if (q_ok && y[p] < S.n_obj) alive |= 1u << p; else bad |= 1u << p;
     }
   }
@@ -384,10 +418,10 @@ __device__ void minhash_tile(const BatchBlock &B, const BatchList &Ls, int32_t l
       if (!((alive >> p) & 1u)) continue;
       m[p] += own[p];
       const int mp = int(m[p]);
-      if (mp < int(ld_uniform(tab + kTabMinOff + j))) {
+      if (mp < int(ld_uniform(st.tab + kTabMinOff + j))) {
         code[p] = uint8_t((BLSH_PRUNED << 6) | j);
         alive &= ~(1u << p);
-      } else if (accept_bit(tab, words, j, mp)) {
+      } else if (accepted_at(st, j, mp, int(ld_uniform(st.tab + kTabAloOff + j)))) {
         code[p] = uint8_t((BLSH_ACCEPT_CONC << 6) | j);
         alive &= ~(1u << p);
         emit |= 1u << p;
@@ -403,7 +437,7 @@ __device__ void minhash_tile(const BatchBlock &B, const BatchList &Ls, int32_t l
   if (J < L) {
     uint4 e[P];
 #pragma unroll
-    for (int p = 0; p < P; ++p) e[p] = spill_entry(base + p * kWave + lane, uint32_t(list_id), m[p], uint32_t(J));
+    for (int p = 0; p < P; ++p) e[p] = spill_entry(base + p * kWave + lane, uint32_t(st.id), m[p], uint32_t(J));
     alive &= ~spill_tile<P>(B, BLSH_JACCARD, wave, n_spill, alive, e);
   }
   for (int j = J; j < L && __ballot(alive != 0); ++j) level(j);
@@ -433,28 +467,49 @@ __device__ inline int64_t list_of_tile(const int64_t *prefix, int64_t n_lists, i
   return lo;
 }
 
+// The same by the whole wave, 64 lists a probe.
+__device__ inline int64_t wave_list_of_tile(const int64_t *prefix, int64_t n_lists, int64_t t) {
+  int64_t lo = 0, len = n_lists;
+  while (len > 1) {
+    const int64_t step = (len + kWave - 1) / kWave, at = lo + lane_id() * step;
+    const uint64_t mask = __ballot(lane_id() * step < len && prefix[min(at, n_lists - 1)] <= t);   // a run from lane 0
+    const int64_t hit = max(__popcll(mask), 1) - 1;
+    lo += hit * step;
+    len = min(step, len - hit * step);
+  }
+  return lo;
+}
+
 // The tiles [t0, t1) of slice x, run in order by one wave (lists of measure
-// MEAS, 64 P candidates per tile).
+// MEAS, 64 P candidates per tile); a list's tiles with its query, thresholds
+// and pointers kept, and the next tile's ids requested before a tile is run.
 template <int MEAS, int K, int P>
 __device__ inline void phase1_range(const BatchBlock &B, int x, const int64_t *prefix, int64_t t0, int64_t t1,
                                     int64_t wave, uint32_t &n_spill) {
   constexpr int64_t tsz = int64_t(P) * kWave;
-  int64_t l = list_of_tile(prefix, B.n_lists, t0);
+  const SigView S = B.sig[MEAS];
+  int64_t l = wave_list_of_tile(prefix, B.n_lists, t0);
   int64_t first = ld_uniform(prefix + l), next = ld_uniform(prefix + l + 1);
-  for (int64_t t = t0; t < t1; ++t) {
+  for (int64_t t = t0; t < t1;) {
     while (t >= next) {   // lists with no tiles in this slice
       ++l;
       first = next;
       next = ld_uniform(prefix + l + 1);
     }
     const BatchList Ls = ld_list(B.lists + l);
-    const uint32_t *tab = ld_uniform(B.tables + Ls.table);
-    const int L = ld_uniform(B.n_levels + Ls.table);
     const int64_t tile = (int64_t(x) * ((Ls.length + tsz - 1) / tsz)) / kXcds + (t - first);
-    if constexpr (MEAS == BLSH_COSINE)
-      srp_tile<K, P>(B, Ls, int32_t(l), Ls.offset + tile * tsz, tab, L, wave, n_spill);
-    else
-      minhash_tile<K, P>(B, Ls, int32_t(l), Ls.offset + tile * tsz, tab, L, wave, n_spill);
+    int64_t base = Ls.offset + tile * tsz;
+    uint32_t y[P], yn[P];
+    load_ids<P>(B, base, Ls.offset + Ls.length, y);
+    const ListState st = list_state(B, l, Ls);
+    const int64_t te = min(t1, next);
+    for (; t < te; ++t, base += tsz) {
+      load_ids<P>(B, base + tsz, t + 1 < te ? st.end : 0, yn);
+      if constexpr (MEAS == BLSH_COSINE) srp_tile<K, P>(B, S, st, base, y, wave, n_spill);
+      else minhash_tile<K, P>(B, S, st, base, y, wave, n_spill);
+#pragma unroll
+      for (int p = 0; p < P; ++p) y[p] = yn[p];
+    }
   }
 }
 
@@ -464,7 +519,10 @@ __device__ inline void phase1_range(const BatchBlock &B, int x, const int64_t *p
 // XCD touches about an eighth of the signature rows and its L2 holds them.
 // Within an XCD every wave runs a contiguous range of that XCD's tiles.  One
 // launch runs the lists of one measure (MEAS), so the streaming minhash rows
-// do not evict the SRP rows from L2.
+// do not evict the SRP rows from L2.  Bound by a tile's chain -- ids from HBM, rows
+// from L2, thresholds -- and for minhash by the lines that miss L2.  512 lists,
+// 32 M SRP candidates (k = 64, a prefix array): 199 us reading each list's state
+// and ids tile by tile, 159 with both ahead.
 template <int MEAS, int K, int P>
 __global__ __launch_bounds__(kBBlock) void k_batch_phase1(const BatchBlock *__restrict__ Bp) {
   const BatchBlock &B = *Bp;
@@ -1224,7 +1282,7 @@ int verify_batched(blsh_ctx *ctx, const blsh_list_desc *lists, int64_t n_lists, 
   int64_t prefix_shape[2] = {-1, -1};   // tile shapes of the prefix sums last uploaded in this call
   const int64_t spill_cap = ctx->tuning.batch_spill_cap > 0
                                 ? int64_t(ctx->tuning.batch_spill_cap)
-                                : std::max<int64_t>(1024, std::min<int64_t>(n_cand, int64_t(1) << 24));
+                                : std::max<int64_t>(kMinSpill, std::min<int64_t>(n_cand, int64_t(1) << 24));
   if ((rc = grow_spill(b, spill_cap))) return rc;
 
   auto prepare = [&](int kkj, int kkc, int64_t srp_tile, int64_t mh_tile, int inreg, int grid1) -> int {

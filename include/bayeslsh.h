@@ -258,7 +258,7 @@ typedef struct {
   int32_t last_batch_k_jaccard;
   int32_t last_batch_inreg;
   int32_t last_batch_blocks_per_cu;
-  int32_t batch_spill_cap;   /* batched: survivor-queue entries per measure (0 = min(n_cand, 2^24)) */
+  int32_t batch_spill_cap;   /* batched: survivor-queue entries per measure (0 = n_cand, from 2^20 to 2^24) */
   int32_t last_batch_k_cosine;
   int32_t acc_stage_cap;     /* accepted-pair staging entries (0 = 2^24 single-call, 2^20 batched) */
   int32_t batch_srp_tile;    /* 0, 128, 256 or 512 */

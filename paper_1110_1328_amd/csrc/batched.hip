@@ -480,14 +480,18 @@ __device__ inline int64_t wave_list_of_tile(const int64_t *prefix, int64_t n_lis
   return lo;
 }
 
-// The tiles [t0, t1) of slice x, run in order by one wave (lists of measure
-// MEAS, 64 P candidates per tile); a list's tiles with its query, thresholds
-// and pointers kept, and the next tile's ids requested before a tile is run.
+// The tiles [w c, (w + 1) c) of slice x's order, list after list, belong to wave w
+// (lists of measure MEAS, 64 P candidates per tile).  Where a list spans several
+// whole waves these share its tiles by turns, not by ranges, so that the waves
+// of all long lists pass through their sorted ids together and read the same
+// rows at about the same time.  A list's query, thresholds and pointers are kept
+// from tile to tile, and the next tile's ids requested before a tile is run.
 template <int MEAS, int K, int P>
-__device__ inline void phase1_range(const BatchBlock &B, int x, const int64_t *prefix, int64_t t0, int64_t t1,
+__device__ inline void phase1_range(const BatchBlock &B, int x, const int64_t *prefix, int64_t T, int64_t w, int64_t c,
                                     int64_t wave, uint32_t &n_spill) {
   constexpr int64_t tsz = int64_t(P) * kWave;
   const SigView S = B.sig[MEAS];
+  const int64_t t0 = w * c, t1 = min(T, t0 + c);
   int64_t l = wave_list_of_tile(prefix, B.n_lists, t0);
   int64_t first = ld_uniform(prefix + l), next = ld_uniform(prefix + l + 1);
   for (int64_t t = t0; t < t1;) {
@@ -497,14 +501,21 @@ __device__ inline void phase1_range(const BatchBlock &B, int x, const int64_t *p
       next = ld_uniform(prefix + l + 1);
     }
     const BatchList Ls = ld_list(B.lists + l);
-    const int64_t tile = (int64_t(x) * ((Ls.length + tsz - 1) / tsz)) / kXcds + (t - first);
+    int64_t n = min(t1, next) - t;   // tiles of this list here, `stride` apart
+    int64_t stride = 1, at = t - first;
+    if (n == c) {   // the whole wave: one of the waves [wa, wb) within the list
+      const int64_t wa = (uint32_t(first) + uint32_t(c) - 1) / uint32_t(c), wb = uint32_t(next) / uint32_t(c);
+      stride = wb - wa;
+      at = wa * c - first + (w - wa);
+    }
+    t += n;
+    const int64_t tile = (int64_t(x) * ((Ls.length + tsz - 1) / tsz)) / kXcds + at;
     int64_t base = Ls.offset + tile * tsz;
     uint32_t y[P], yn[P];
     load_ids<P>(B, base, Ls.offset + Ls.length, y);
     const ListState st = list_state(B, l, Ls);
-    const int64_t te = min(t1, next);
-    for (; t < te; ++t, base += tsz) {
-      load_ids<P>(B, base + tsz, t + 1 < te ? st.end : 0, yn);
+    for (; n > 0; --n, base += stride * tsz) {
+      load_ids<P>(B, base + stride * tsz, n > 1 ? st.end : 0, yn);
       if constexpr (MEAS == BLSH_COSINE) srp_tile<K, P>(B, S, st, base, y, wave, n_spill);
       else minhash_tile<K, P>(B, S, st, base, y, wave, n_spill);
 #pragma unroll
@@ -533,11 +544,11 @@ __global__ __launch_bounds__(kBBlock) void k_batch_phase1(const BatchBlock *__re
   const int64_t Wx = nbx * (kBBlock / kWave);
   const int64_t *prefix = B.tile_prefix + int64_t(MEAS * kXcds + x) * (B.n_lists + 1);
   const int64_t Tx = ld_uniform(prefix + B.n_lists);
-  const int64_t t0 = wx * Tx / Wx, t1 = (wx + 1) * Tx / Wx;
+  const int64_t c = (Tx + Wx - 1) / Wx;   // (fewer than 2^32 tiles: ids take 256 bytes each)
   const int64_t wave = int64_t(blockIdx.x) * (kBBlock / kWave) +
                        int64_t(__builtin_amdgcn_readfirstlane(int(threadIdx.x) / kWave));
   uint32_t n_spill = 0;
-  if (t0 < t1) phase1_range<MEAS, K, P>(B, x, prefix, t0, t1, wave, n_spill);
+  if (wx * c < Tx) phase1_range<MEAS, K, P>(B, x, prefix, Tx, wx, c, wave, n_spill);
   if (lane_id() == 0)   // every wave of the grid reports its fill, 0 included
     B.spill_count[MEAS][wave] = n_spill;
 }

@@ -33,16 +33,12 @@ def signatures(measure, n_hashes, seed):
     return G.pack_bits(G.calibration_bits(len(s), n_hashes, s, seed))
 
 
-@pytest.mark.parametrize("kj,kc,layout", [(16, 64, P.WORD_MAJOR), (32, 32, P.OBJECT_MAJOR), (64, 16, P.WORD_MAJOR)])
-@pytest.mark.parametrize("tuning", [{}, {"batch_spill_cap": 4096}, {"batch_inreg": 1}, {"batch_inreg": 64},
-                                    {"batch_inreg": 1, "batch_blocks_per_cu": 1, "acc_stage_cap": 512}])
-def test_bunched_survivors(ctx, kj, kc, layout, tuning):
-    print("bunched survivors k %d/%d layout %d %s" % (kj, kc, layout, tuning), flush=True)
+def check(ctx, lists, kj, kc, layout, tuning):
     rng = np.random.default_rng(kj + kc)
     jac, cos = signatures(P.JACCARD, 256, 5), signatures(P.COSINE, 512, 6)
     meas, ts, query, ids = [], [], [], []
-    for i, (n, run) in enumerate(LISTS * 2):
-        me = (P.JACCARD, P.COSINE)[i >= len(LISTS)]
+    for i, (n, run) in enumerate(lists * 2):
+        me = (P.JACCARD, P.COSINE)[i >= len(lists)]
         q = int(rng.integers(0, N_OBJ))
         own = rng.integers(0, N_OBJ, n)
         at = int(rng.integers(0, n - run + 1))
@@ -70,3 +66,20 @@ def test_bunched_survivors(ctx, kj, kc, layout, tuning):
             assert_same_as_oracle(decode_result(res, n), want)
     finally:
         P.bayeslsh_set_tuning(ctx)
+
+
+@pytest.mark.parametrize("kj,kc,layout", [(16, 64, P.WORD_MAJOR), (32, 32, P.OBJECT_MAJOR), (64, 16, P.WORD_MAJOR)])
+@pytest.mark.parametrize("tuning", [{}, {"batch_spill_cap": 4096}, {"batch_inreg": 1}, {"batch_inreg": 64},
+                                    {"batch_inreg": 1, "batch_blocks_per_cu": 1, "acc_stage_cap": 512}])
+def test_bunched_survivors(ctx, kj, kc, layout, tuning):
+    print("bunched survivors k %d/%d layout %d %s" % (kj, kc, layout, tuning), flush=True)
+    check(ctx, LISTS, kj, kc, layout, tuning)
+
+
+@pytest.mark.parametrize("lengths", [[250_007], [100, 90_017, 0, 33, 120_000, 1], [70_001, 64, 70_016, 512, 70_000]])
+def test_lists_over_several_waves(ctx, lengths):
+    """Lists long enough that waves of a small grid run several tiles each and
+    share a list by turns, between lists that begin and end inside a wave."""
+    print("lists over several waves %s" % lengths, flush=True)
+    check(ctx, [(n, n // 50) for n in lengths], 16, 64, P.WORD_MAJOR,
+          {"batch_blocks_per_cu": 1, "batch_srp_tile": 128, "batch_mh_tile": 64})

@@ -44,6 +44,10 @@ constexpr int kBBlock = 256;
 // or 128 (1 or 2 per lane)
 constexpr int kSrpTileDefault = 256;
 constexpr int kMhTileDefault = 64;
+// phase-1 blocks per CU: all resident at once (the SRP kernel's registers allow 7),
+// so that the waves of a list keep pace.  512 lists of 56 M candidates (k = 16 / 64):
+// 474 us with 4, 449 with 5, 437 with 6, 484 with 7, 499 with 8; 34 K candidates: 56 to 57.
+constexpr int kBlocksDefault = 6;
 constexpr int kExSrpTile = 1024;   // comparator: candidates per SRP block tile
 constexpr int kExMhTile = 256;     // comparator: candidates per minhash block tile
 constexpr int kXcds = 8;           // phase 1: list tiles split in kXcds position ranges, one per XCD
@@ -1391,7 +1395,7 @@ int verify_batched(blsh_ctx *ctx, const blsh_list_desc *lists, int64_t n_lists, 
   };
 
   // k of a measure no list uses is irrelevant: 32
-  BatchState::Choice ch{kj ? kj : 32, kc ? kc : 32, kSrpTileDefault, kMhTileDefault, 2, 8};
+  BatchState::Choice ch{kj ? kj : 32, kc ? kc : 32, kSrpTileDefault, kMhTileDefault, 2, kBlocksDefault};
   const int fixed_tile[2] = {ctx->tuning.batch_mh_tile, ctx->tuning.batch_srp_tile};
   if (fixed_tile[0] > 0) ch.tm = fixed_tile[0];
   if (fixed_tile[1] > 0) ch.ts = fixed_tile[1];
@@ -1458,7 +1462,7 @@ int verify_batched(blsh_ctx *ctx, const blsh_list_desc *lists, int64_t n_lists, 
       float best = 1e30f;
       BatchState::Choice pick = ch;
       for (int inreg : {1, 2, 4, kMaxLevels})   // kMaxLevels: every level in registers, no queue
-        for (int bpc : {2, 4, 8}) {
+        for (int bpc : {2, 4, kBlocksDefault}) {
           BatchState::Choice c = ch;
           c.inreg = inreg;
           c.bpc = bpc;

@@ -23,7 +23,8 @@ int launch_srp_dense(blsh_ctx *ctx, const float *X, int64_t n_rows, int64_t dim,
 int launch_exact(blsh_ctx *ctx, const VerifyArgs &a, int64_t max_items, hipStream_t s);
 int launch_exact_pairs(blsh_ctx *ctx, const VerifyArgs &a, double *out, hipStream_t s);
 int launch_verify_few(blsh_ctx *ctx, const VerifyArgs &a, int k, bool word_major, int words, hipStream_t s);
-int launch_verify_tail(blsh_ctx *ctx, const VerifyArgs &a, int k, bool word_major, int words, hipStream_t s);
+int launch_verify_tail(blsh_ctx *ctx, const VerifyArgs &a, int k, bool word_major, bool intervals, int words,
+                       hipStream_t s);
 int launch_zero_slices(blsh_ctx *ctx, int64_t *cnt, hipStream_t s);
 int launch_tiles_exact(blsh_ctx *ctx, const VerifyArgs &a, int64_t grid_waves, hipStream_t s);
 int launch_verify_tiles(blsh_ctx *ctx, const VerifyArgs &a, int k, int n_max, int words, bool intervals, bool lite,
@@ -541,11 +542,11 @@ static int run_verify(blsh_ctx *ctx, const blsh_candidates *cand, const blsh_sig
   a.t = t;
   if (n_cand == 0 || (cand->kind == BLSH_TILES && cand->n_tiles == 0))
     return launch_zero(ctx, res->n_accepted, s) ? fail(BLSH_EDEVICE, "launch failed") : BLSH_OK;
+  const bool intervals = (na_host->image[kTabFlagOff] & 1u) != 0;
   if (cand->kind == BLSH_TILES) {
-    const bool intervals = (na_host->image[kTabFlagOff] & 1u) != 0 && !ctx->tuning.tiles_accept_bitmask;
     if (lite) fill_exact(a, exact);
     // the rows are staged up to the last level: n_max, or h for Lite
-    return run_tiles(ctx, cand, a, k, lite ? h : n_max, n_levels, intervals || lite, lite, s);
+    return run_tiles(ctx, cand, a, k, lite ? h : n_max, n_levels, (intervals && !ctx->tuning.tiles_accept_bitmask) || lite, lite, s);
   }
   // SRP Algorithm 1 with a prefix view: candidates undecided after the first
   // 128 hashes are queued and finished by a second kernel with every lane busy
@@ -615,7 +616,7 @@ static int run_verify(blsh_ctx *ctx, const blsh_candidates *cand, const blsh_sig
     const bool wm = sigs->measure == BLSH_COSINE && sigs->layout == BLSH_WORD_MAJOR;
     if (!noalloc) ctx->slices_dirty = true;
     rc = exh ? launch_exhaustive(ctx, a, k, s) : launch_verify(ctx, a, k, lite, wm, s);
-    if (!rc && tail) rc = launch_verify_tail(ctx, a, k, wm, (n_levels * k + 1 + 31) / 32, s);
+    if (!rc && tail) rc = launch_verify_tail(ctx, a, k, wm, intervals, (n_levels * k + 1 + 31) / 32, s);
     if (!rc && queued && !tail) rc = launch_exact(ctx, a, a.c_end - a.c_begin, s);
     if (!rc) rc = launch_acc_flush(ctx, a, set_cnt(nxt), set_total(nxt), a.c_end == n_cand, s);
     if (rc) return rc == BLSH_EDEVICE ? fail(rc, "kernel launch failed: %s", hipGetErrorString(hipGetLastError())) : rc;

@@ -738,6 +738,127 @@ __global__ __launch_bounds__(kBlock) void k_verify_tail(VerifyArgs a) {
   }
 }
 
+// The tail over rows that 16-byte loads can read, for tables whose accept sets
+// are intervals: G lanes per pair, lane r with words 4 r .. 4 r + 3 of both
+// sides, so a pair's levels (G * 128 hashes of them) come in one round trip and a
+// row's line is read by neighbouring lanes at once.  Each lane counts its own
+// levels, a scan over the group gives the matches up to them, and the least
+// deciding level of the group is the pair's.  Bound by the rows' lines (256 bytes
+// a pair at 1024 hashes, random in an array larger than the L2) and, next, by
+// vector issue; with one lane per pair, 32 bytes of each side a step, it was
+// bound by the chain of steps.  16 M undecided of 215 M pairs, 1024 bits, k = 32:
+// 1063 -> 770 us (two pairs at a time 832; registers for 5 or 7 waves a SIMD
+// instead of 6: 857, 927).
+template <int K, int G>
+__global__ __launch_bounds__(kBlock, K == 16 ? 4 : 6) void k_verify_tail_rows(VerifyArgs a) {
+  constexpr int LPL = 128 / K;      // levels of a lane
+  constexpr int CH = 4;             // pairs of a group whose rows are in flight together
+  __shared__ int2 s_th[kMaxLevels];   // pruned below x, accepted from y (the last level: all that are not pruned)
+  const int L = a.n_levels;
+  if (threadIdx.x < kMaxLevels) {
+    const int j = threadIdx.x;
+    const int lo = j < L ? int(a.table[kTabMinOff + j]) : -1;
+    s_th[j] = make_int2(lo, j < L - 1 ? int(a.table[kTabAloOff + j]) : j == L - 1 ? lo : 0x7fffffff);
+  }
+  __syncthreads();
+  const double alpha = tab_f64(a.table, 4), beta = tab_f64(a.table, 6);
+  const int alo_last = int(a.table[kTabAloOff + L - 1]);
+  const int r = lane_id() & (G - 1);
+  // block b serves queue slice b % kSlices, as in k_verify_tail
+  const int sl = int(blockIdx.x % kSlices);
+  const int64_t n = min(a.q_cnt[sl * kCntStride], a.q_cap);
+  const uint32_t *rel = a.q_rel + size_t(sl) * a.q_cap;
+  const uint32_t *qm = a.q_m + size_t(sl) * a.q_cap;
+  const int64_t stride = int64_t(gridDim.x / kSlices) * kBlock;
+  for (int64_t i0 = int64_t(blockIdx.x / kSlices) * kBlock; i0 < n; i0 += stride) {
+    const int64_t i = i0 + threadIdx.x;
+    const bool in = i < n;
+    uint32_t x = 0, y = 0, at = 0, e = kDecidedBit;
+    if (in) {
+      at = rel[i];
+      e = qm[i];
+      const int64_t c = a.c_begin + at;
+      if (!(e & kDecidedBit)) {
+        if (a.kind == BLSH_PAIRS) {
+          x = a.x[c];
+          y = a.y[c];
+        } else {
+          fetch_candidate(a, c, x, y);
+        }
+      }
+    }
+    uint32_t found = e & ~kDecidedBit;   // m | level << 16 where this lane's pair is decided
+    if (__ballot(!(e & kDecidedBit)) != 0) {
+      auto some = [&](auto s0_) {        // pairs s0 .. s0 + CH - 1 of each group
+        constexpr int S0 = decltype(s0_)::value;
+        uint32_t xs[CH], ys[CH], run[CH];
+        bcast_rows<G, S0>(x, xs, std::make_integer_sequence<int, CH>{});
+        bcast_rows<G, S0>(y, ys, std::make_integer_sequence<int, CH>{});
+        bcast_rows<G, S0>(e, run, std::make_integer_sequence<int, CH>{});
+        uint32_t open = 0;
+#pragma unroll
+        for (int s = 0; s < CH; ++s) {
+          if (!(run[s] & kDecidedBit)) open |= 1u << s;
+          run[s] &= 0xFFFFu;
+        }
+        for (int chunk = r; __ballot(open != 0) != 0; chunk += G) {
+          u32x4 hx[CH], hy[CH];
+#pragma unroll
+          for (int s = 0; s < CH; ++s) {
+            hx[s] = hy[s] = u32x4{0, 0, 0, 0};
+            if (((open >> s) & 1u) && 4 * chunk < a.row_words) {
+              hx[s] = *reinterpret_cast<const u32x4 *>(a.sig + size_t(xs[s]) * a.row_words + 4 * chunk);
+              hy[s] = *reinterpret_cast<const u32x4 *>(a.sig + size_t(ys[s]) * a.row_words + 4 * chunk);
+            }
+          }
+          const int j0 = chunk * LPL;
+          int2 th[LPL];
+#pragma unroll
+          for (int q = 0; q < LPL; ++q) th[q] = s_th[min(j0 + q, kMaxLevels - 1)];
+#pragma unroll
+          for (int s = 0; s < CH; ++s) {
+            const uint32_t d[4] = {hx[s].x ^ hy[s].x, hx[s].y ^ hy[s].y, hx[s].z ^ hy[s].z, hx[s].w ^ hy[s].w};
+            uint32_t cnt[LPL], own = 0;
+#pragma unroll
+            for (int q = 0; q < LPL; ++q) {
+              cnt[q] = chunk == 0 ? 0u : agree_from_xor<K>(d, q);   // (the first 128 are in the queue's m)
+              own += cnt[q];
+            }
+            uint32_t m = run[s] + group_excl_scan<G>(own);
+            uint32_t first = 0xFFFFFFFFu;
+#pragma unroll
+            for (int q = 0; q < LPL; ++q) {
+              m += cnt[q];
+              const bool dec = chunk != 0 && (int(m) < th[q].x || int(m) >= th[q].y);
+              if (dec) first = min(first, (uint32_t(j0 + q) << 16) | m);
+            }
+            first = group_min<G>(first);
+            run[s] += group_sum<G>(own);
+            if (((open >> s) & 1u) && first != 0xFFFFFFFFu) {
+              open &= ~(1u << s);
+              if (r == S0 + s) found = first;
+            }
+          }
+        }
+      };
+      some(std::integral_constant<int, 0>{});
+      if constexpr (G > CH) some(std::integral_constant<int, CH>{});
+    }
+    const int64_t c = a.c_begin + at;
+    const uint32_t m = found & 0xFFFFu;
+    const int j = int(found >> 16);
+    const bool pruned = !(e & kDecidedBit) && int(m) < s_th[j].x, nmax = !(e & kDecidedBit) && j == L - 1 && int(m) < alo_last;
+    const uint8_t code = uint8_t(((pruned ? BLSH_PRUNED : nmax ? BLSH_ACCEPT_NMAX : BLSH_ACCEPT_CONC) << 6) | j);
+    const bool emit = in && !pruned;
+    if (in) {
+      a.code[c] = code;
+      if (a.m_dbg) a.m_dbg[c] = uint16_t(m);
+    }
+    const float v = emit ? map_estimate(a.measure, int(m), (j + 1) * K, alpha, beta) : 0.f;
+    emit_accepted(a, emit, uint64_t(c), v);
+  }
+}
+
 // SRP Algorithm 1 of a call of few candidates, one lane per candidate from its
 // first level to its last: the prefix (when a.pfx) in one round trip, then 8
 // words of each side per step.  Bound by latency: the launch itself (about 6 us
@@ -1891,14 +2012,21 @@ int launch_verify_few(blsh_ctx *ctx, const VerifyArgs &a, int k, bool word_major
 // words: accept-bit words per level of the launch's table (LDS of the tail).
 // Object-major rows take 16-byte chunk loads only when every row starts on a
 // 16-byte boundary and holds a whole number of chunks.
-int launch_verify_tail(blsh_ctx *ctx, const VerifyArgs &a, int k, bool word_major, int words, hipStream_t s) {
+int launch_verify_tail(blsh_ctx *ctx, const VerifyArgs &a, int k, bool word_major, bool intervals, int words,
+                       hipStream_t s) {
   const int64_t nb = round_up(int64_t(ctx->n_cu) * 16, kSlices);
   const size_t lds = size_t(a.n_levels) * words * 4;
   const bool row16 = a.row_words % 4 == 0 && (uintptr_t(a.sig) & 15) == 0;
+  // a group's first pass covers the rows of up to 1024 hashes; of up to 512 with
+  // half the lanes a pair, so that none is without words
   LaunchScope ls(ctx, s, "verify_tail");
 #define BLSH_T(KK)                                                                                          \
   if (k == KK) {                                                                                            \
     if (word_major) hipLaunchKernelGGL((k_verify_tail<KK, kTailWM>), dim3(nb), dim3(kBlock), lds, s, a);     \
+    else if (row16 && intervals && a.n_levels * KK > 512)                                                   \
+      hipLaunchKernelGGL((k_verify_tail_rows<KK, 8>), dim3(nb), dim3(kBlock), 0, s, a);                     \
+    else if (row16 && intervals)                                                                            \
+      hipLaunchKernelGGL((k_verify_tail_rows<KK, 4>), dim3(nb), dim3(kBlock), 0, s, a);                     \
     else if (row16) hipLaunchKernelGGL((k_verify_tail<KK, kTailRow16>), dim3(nb), dim3(kBlock), lds, s, a);  \
     else hipLaunchKernelGGL((k_verify_tail<KK, kTailRow4>), dim3(nb), dim3(kBlock), lds, s, a);             \
     return hipGetLastError() == hipSuccess ? BLSH_OK : BLSH_EDEVICE;                                        \

@@ -2017,15 +2017,18 @@ int launch_verify_tail(blsh_ctx *ctx, const VerifyArgs &a, int k, bool word_majo
   const int64_t nb = round_up(int64_t(ctx->n_cu) * 16, kSlices);
   const size_t lds = size_t(a.n_levels) * words * 4;
   const bool row16 = a.row_words % 4 == 0 && (uintptr_t(a.sig) & 15) == 0;
-  // a group's first pass covers the rows of up to 1024 hashes; of up to 512 with
-  // half the lanes a pair, so that none is without words
+  // groups of lanes over rows of more than 256 hashes (one lane's single step of 16
+  // bytes a side is as good up to there): 300 K objects of 256 bits, 215 M pairs, 1293
+  // us with a lane a pair and 1325 with groups, 150 K of 512 bits, 54 M pairs, 348 and
+  // 329.  Half the lanes a pair up to 512 hashes, so that none is without words.
+  const bool grouped = row16 && intervals && a.n_levels * k > 256;
   LaunchScope ls(ctx, s, "verify_tail");
 #define BLSH_T(KK)                                                                                          \
   if (k == KK) {                                                                                            \
     if (word_major) hipLaunchKernelGGL((k_verify_tail<KK, kTailWM>), dim3(nb), dim3(kBlock), lds, s, a);     \
-    else if (row16 && intervals && a.n_levels * KK > 512)                                                   \
+    else if (grouped && a.n_levels * KK > 512)                                                              \
       hipLaunchKernelGGL((k_verify_tail_rows<KK, 8>), dim3(nb), dim3(kBlock), 0, s, a);                     \
-    else if (row16 && intervals)                                                                            \
+    else if (grouped)                                                                                       \
       hipLaunchKernelGGL((k_verify_tail_rows<KK, 4>), dim3(nb), dim3(kBlock), 0, s, a);                     \
     else if (row16) hipLaunchKernelGGL((k_verify_tail<KK, kTailRow16>), dim3(nb), dim3(kBlock), lds, s, a);  \
     else hipLaunchKernelGGL((k_verify_tail<KK, kTailRow4>), dim3(nb), dim3(kBlock), lds, s, a);             \

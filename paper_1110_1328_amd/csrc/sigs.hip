@@ -308,9 +308,12 @@ __global__ __launch_bounds__(256) void k_srp_sparse(const int64_t *offsets, cons
   for (int o = 32; o > 0; o >>= 1) mass += __shfl_xor(mass, o);
   // roundings: one per nonzero of a block's sum (a drawn entry's product with
   // the unit: one more of its own term), one per block, each 2^-24 of at most
-  // 2^15 units of the mass; and those of the mass itself
+  // 2^15 units of the mass; and those of the mass itself.  Near the bottom of the
+  // float range a rounding is 2^-150 instead, at most 10 of them a nonzero: under
+  // 2^-8 of the mass (two of the four roundings to spare) for any row of 2^32
+  // nonzeros and a mass of 2^-100 or more.  A smaller mass decides nothing.
   const float n = float(e - s);
-  const float T = mass * (err + (kSumBlock + n / kSumBlock + 4.f) * 0x1p-9f) * (1.f + n * 0x1p-23f) * 1.001f;
+  const float T = mass < 0x1p-100f ? INFINITY : mass * (err + (kSumBlock + n / kSumBlock + 4.f) * 0x1p-9f) * (1.f + n * 0x1p-23f) * 1.001f;
   uint32_t nib = 0, unsure = 0;
 #pragma unroll
   for (int c = 0; c < 4 * QPL; ++c) {

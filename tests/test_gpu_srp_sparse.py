@@ -90,3 +90,30 @@ def test_few_rows(n_rows):
     finally:
         a.close()
         b.close()
+
+
+@pytest.mark.parametrize("flags", [0, P.SRP_PLANES_Q16])
+@pytest.mark.parametrize("dim", [1 << 20, 512])     # entries drawn as they occur, the table
+@pytest.mark.parametrize("nnz", [5, 10, 32])
+def test_values_at_the_bottom_of_the_float_range(nnz, dim, flags):
+    """Rows of +-2^e from the least denormal up: there a rounding is no longer a
+    share of what is rounded, and the fp32 sums may decide only what is far
+    above it."""
+    n_rows, n_bits = 4096, 2048
+    print("sparse SRP denormals: %d nonzeros dim %d flags %d" % (nnz, dim, flags), flush=True)
+    rng = np.random.default_rng(nnz + flags)
+    e = np.full(n_rows, -149)
+    e[n_rows // 2:] = rng.integers(-149, -90, n_rows - n_rows // 2)
+    val = (np.ldexp(1.0, e)[:, None] * rng.choice([-1.0, 1.0], (n_rows, nnz))).astype(np.float32)
+    assert (val != 0).all()
+    idx = np.argsort(rng.random((n_rows, 512)), axis=1)[:, :nnz] * (dim // 512)
+    off = np.arange(n_rows + 1, dtype=np.int64) * nnz
+    vecs = P.csr_vectors(up(off), up(np.sort(idx, axis=1).astype(np.uint32).reshape(-1)), up(val.reshape(-1)), dim)
+    a, b = P.bayeslsh_create(0), P.bayeslsh_create(0)
+    try:
+        P.bayeslsh_reserve_workspace(b, 0, fixed=True)   # the sums alone
+        got, want = (bits_of(c, vecs, n_rows, n_bits, P.OBJECT_MAJOR, flags) for c in (a, b))
+        assert np.unpackbits((got ^ want).view(np.uint8)).sum() == 0
+    finally:
+        a.close()
+        b.close()

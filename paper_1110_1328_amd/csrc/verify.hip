@@ -945,8 +945,8 @@ __device__ inline double group_sum_f64(double v) {
 }
 
 // Exact similarity of every candidate in [c_begin, c_end), written to out[c] in
-// FP64 (bad ids: NaN and BLSH_EBADID).  Sparse rows and sets: a wave takes 64
-// consecutive candidates, x by x (lists, bucket-major pairs and all pairs hold
+// FP64 (bad ids: NaN and BLSH_EBADID).  Sparse rows and sets: a wave takes
+// `share` (at most 64) consecutive candidates, x by x (lists, bucket-major pairs and all pairs hold
 // runs of one x): x's row goes into a hash table in LDS, and each of its
 // candidates' rows is looked up there by 16 lanes, four candidates at a time (a
 // single one by all 64).  An x row that the table does not hold goes pair by
@@ -1040,18 +1040,18 @@ __device__ __forceinline__ RowSums probe_row(const VerifyArgs &a, int64_t at, in
 }
 
 template <bool CSR>
-__global__ __launch_bounds__(kBlock) void k_exact_pairs(VerifyArgs a, double *out) {
+__global__ __launch_bounds__(kBlock) void k_exact_pairs(VerifyArgs a, int share, double *out) {
   __shared__ uint32_t s_keys[kBlock / kWave][kHashSlots];
   __shared__ float s_vals[kBlock / kWave][kHashSlots];
   const int lane = lane_id(), w = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6), grp = lane >> 4;
   uint32_t *keys = s_keys[w];
   float *vals = s_vals[w];
   const int64_t waves = int64_t(gridDim.x) * (kBlock / kWave);
-  for (int64_t c0 = a.c_begin + (int64_t(blockIdx.x) * (kBlock / kWave) + w) * kWave; c0 < a.c_end; c0 += waves * kWave) {
+  for (int64_t c0 = a.c_begin + (int64_t(blockIdx.x) * (kBlock / kWave) + w) * share; c0 < a.c_end; c0 += waves * share) {
     const int64_t c = c0 + lane;
     uint32_t xi = 0, yi = 0;
     bool ok = false;
-    if (c < a.c_end) {
+    if (lane < share && c < a.c_end) {
       ok = fetch_candidate(a, c, xi, yi);
       if (!ok) {
         out[c] = __builtin_nan("");
@@ -2129,9 +2129,12 @@ int launch_exact_pairs(blsh_ctx *ctx, const VerifyArgs &a, double *out, hipStrea
     else
       hipLaunchKernelGGL(k_exact_dense_pairs<1>, nb, dim3(kBlock), 0, s, a, out);
   } else {
-    const dim3 nb(unsigned(std::min<int64_t>(blocks_for(n, kBlock), int64_t(ctx->n_cu) * 64)));
-    if (a.ex_kind == BLSH_CSR) hipLaunchKernelGGL(k_exact_pairs<true>, nb, dim3(kBlock), 0, s, a, out);
-    else hipLaunchKernelGGL(k_exact_pairs<false>, nb, dim3(kBlock), 0, s, a, out);
+    // 64 candidates to a wave where that fills the chip, fewer where it does not:
+    // a wave's distinct x are worked through one after another
+    const int share = int(std::min<int64_t>(kWave, blocks_for(n, int64_t(ctx->n_cu) * 32)));
+    const dim3 nb(unsigned(std::min<int64_t>(blocks_for(n, int64_t(share) * (kBlock / kWave)), int64_t(ctx->n_cu) * 64)));
+    if (a.ex_kind == BLSH_CSR) hipLaunchKernelGGL(k_exact_pairs<true>, nb, dim3(kBlock), 0, s, a, share, out);
+    else hipLaunchKernelGGL(k_exact_pairs<false>, nb, dim3(kBlock), 0, s, a, share, out);
   }
   return hipGetLastError() == hipSuccess ? BLSH_OK : BLSH_EDEVICE;
 }

@@ -104,3 +104,61 @@ def test_dense_similarity_dims(ctx, dim):
         norm = np.sqrt((a * a).sum(1)) * np.sqrt((b * b).sum(1))
         want = np.where(norm > 0, (a * b).sum(1) / np.where(norm > 0, norm, 1), 0)
         np.testing.assert_allclose(got[ok], want, rtol=0, atol=1e-12)
+
+
+def csr_rows(rng, n, nnz, dim):
+    """n rows of nnz sorted unique terms."""
+    step = dim // nnz
+    idx = np.arange(nnz) * step + rng.integers(0, step, (n, nnz))
+    return np.arange(n + 1, dtype=np.int64) * nnz, idx.astype(np.uint32)
+
+
+def passes_us(f, n=20):
+    """Microseconds a call among others, the least of five runs."""
+    for _ in range(3):
+        f()
+    a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    got = []
+    for _ in range(5):
+        torch.cuda.synchronize()
+        a.record()
+        for _ in range(n):
+            f()
+        b.record()
+        torch.cuda.synchronize()
+        got.append(a.elapsed_time(b) / n * 1e3)
+    return min(got)
+
+
+@pytest.mark.parametrize("kind", ["csr", "sets"])
+def test_a_small_sample_is_spread_over_the_chip(ctx, kind):
+    """The sample of a prior, a thousand pairs of distinct x: as many waves as the
+    chip holds side by side, so about the time of one pair (4 times would be
+    four pairs one after another in a wave; a wave of 64 takes 16 times)."""
+    rng = np.random.default_rng(3)
+    off, idx = csr_rows(rng, 5000, 100, 1 << 20)
+    vecs = (P.csr_vectors(up(off), up(idx.reshape(-1)), up(rng.normal(size=idx.size).astype(np.float32)), 1 << 20)
+            if kind == "csr" else P.set_vectors(up(off), up(idx.reshape(-1)), 1 << 20))
+    us = {}
+    for m in (1, 1000):
+        x, y = (up(rng.integers(0, 5000, m).astype(np.uint32)) for _ in range(2))
+        out, c = torch.empty(m, dtype=torch.float64, device="cuda"), P.pairs(x, y)
+        us[m] = passes_us(lambda: P.bayeslsh_exact_similarity(ctx, c, vecs, out))
+    print("similarity sample %s: %s us" % (kind, us), flush=True)
+    assert us[1000] < 4 * us[1]
+
+
+@pytest.mark.parametrize("n", [8192, 8193, 8192 * 63 + 5, 8192 * 64 + 1])
+def test_candidates_a_wave(ctx, n):
+    """One, two and up to 64 candidates to a wave (256 CUs: 8192 waves), the last wave's share cut short."""
+    rng = np.random.default_rng(n)
+    off, idx = csr_rows(rng, 300, 7, 140)
+    x, y = rng.integers(0, 300, n), rng.integers(0, 300, n)
+    x[: n // 2] = np.sort(x[: n // 2])
+    member = np.zeros((300, 140), np.int32)
+    np.put_along_axis(member, idx.astype(np.int64), 1, axis=1)
+    common = (member @ member.T)[x, y]
+    got = down(P.bayeslsh_exact_similarity(ctx, P.pairs(up(x.astype(np.uint32)), up(y.astype(np.uint32))),
+                                           P.set_vectors(up(off), up(idx.reshape(-1)), 140)))[:n]
+    P.bayeslsh_sync(ctx)
+    np.testing.assert_array_equal(got, common / (14 - common))

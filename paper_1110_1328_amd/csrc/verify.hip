@@ -19,7 +19,7 @@
 //                     per side, then sums the agreements with DPP; lane l owns
 //                     candidate l of the wave's tile of 64.
 //   k_exact           exact similarity on Lite survivors (one wave per pair).
-//   k_exact_pairs, k_exact_dense_pairs  exact similarity of every candidate.
+//   k_exact_runs, k_exact_pairs, k_exact_dense_pairs  exact similarity of every candidate.
 //   k_exhaustive_*    the comparator: all n_max hashes of both object-major rows,
 //                     per-level counts, prefix sums, then the decision sequence
 //                     of Algorithm 1/2 replayed (or the classical m/n estimate).
@@ -946,21 +946,27 @@ __device__ inline double group_sum_f64(double v) {
 
 // Exact similarity of every candidate in [c_begin, c_end), written to out[c] in
 // FP64 (bad ids: NaN and BLSH_EBADID).  Sparse rows and sets: a wave takes
-// `share` (at most 64) consecutive candidates, x by x (lists, bucket-major pairs and all pairs hold
-// runs of one x): x's row goes into a hash table in LDS, and each of its
+// `share` (at most 64) consecutive candidates, x by x (lists, bucket-major pairs
+// and all pairs hold runs of one x): x's row goes into a hash table in LDS, and each of its
 // candidates' rows is looked up there by 16 lanes, four candidates at a time (a
-// single one by all 64).  An x row that the table does not hold goes pair by
-// pair through exact_wave.
+// single one by all 64).  Lone pairs (runs shorter than 4/3 on average), an x row
+// that fills the table too far and a row much longer than that are left to
+// k_exact_pairs, a wave to a pair, where nothing is gained by a table.
 // Bound by VALU issue (120 instructions a pair) and the chain from ids over
 // offsets and rows to the table: 4M pairs of rows of 100 terms (16 x 16 tiled
-// order) in 1.22 ms; 3.79 ms with a wave, a staged row, a binary search of 7 steps
-// per entry and 18 shuffles to a pair.
-constexpr int kHashSlots = kExactLds;           // 4-byte keys and values, one table per wave
-constexpr int kHashRow = kHashSlots * 3 / 4;    // longest row in the table
+// order) in 1.10 ms (1.20 with 512 slots); 3.79 ms with a wave, a staged row, a binary search of 7 steps
+// per entry and 18 shuffles to a pair.  Both kernels against a wave a pair alone
+// (us): 400,000 pairs in runs of 16, rows of 200 terms 218 / 668, of 384 551 / 976; lone
+// pairs 710 / 695; 100,000 lone pairs 115 / 112.
+constexpr int kHashSlots = 1024;                // 4-byte keys and values, one table per wave
+// longest row in the table (sets: what there is to save, a row's binary searches, is less)
+template <bool CSR>
+constexpr int kHashRow = CSR ? 384 : 256;
+constexpr int kLongRow = 1536;                  // longest row looked up in it
 constexpr uint32_t kHashEmpty = 0xFFFFFFFFu;    // (a term of this number is kept beside the table)
 
-__device__ inline uint32_t hash_slot(uint32_t key) { return (key * 0x9E3779B1u) >> 23; }
-static_assert(kHashSlots == 1 << (32 - 23), "slot bits of the hash");
+__device__ inline uint32_t hash_slot(uint32_t key) { return (key * 0x9E3779B1u) >> 22; }
+static_assert(kHashSlots == 1 << (32 - 22), "slot bits of the hash");
 
 // Entries [at, at + n) of a row summed over the group of G lanes: products with
 // the table's values and squares (CSR), or the number of entries found.
@@ -1039,10 +1045,14 @@ __device__ __forceinline__ RowSums probe_row(const VerifyArgs &a, int64_t at, in
   return RowSums{dot, sq, found};
 }
 
+// What k_exact_runs leaves to k_exact_pairs (a NaN that no similarity is; one
+// with these bits would only be worked out again).
+constexpr uint64_t kLeft = 0x7FF8B1A5B1A5B1A5ull;
+
 template <bool CSR>
-__global__ __launch_bounds__(kBlock) void k_exact_pairs(VerifyArgs a, int share, double *out) {
+__global__ __launch_bounds__(kBlock) void k_exact_runs(VerifyArgs a, int share, double *out) {
   __shared__ uint32_t s_keys[kBlock / kWave][kHashSlots];
-  __shared__ float s_vals[kBlock / kWave][kHashSlots];
+  __shared__ float s_vals[kBlock / kWave][CSR ? kHashSlots : 1];
   const int lane = lane_id(), w = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6), grp = lane >> 4;
   uint32_t *keys = s_keys[w];
   float *vals = s_vals[w];
@@ -1058,24 +1068,30 @@ __global__ __launch_bounds__(kBlock) void k_exact_pairs(VerifyArgs a, int share,
         raise_status(a.status, BLSH_EBADID);
       }
     }
+    uint64_t left = __ballot(ok);
+    // mostly lone pairs: all of them to the other kernel
+    const uint32_t before = uint32_t(__shfl_up(int(xi), 1));
+    const int starts = __popcll(__ballot(ok && (lane == 0 || xi != before)));
+    if (4 * starts > 3 * __popcll(left)) {
+      if (ok) out[c] = __builtin_bit_cast(double, kLeft);
+      continue;
+    }
     int64_t ys = 0, yn = 0;
     if (ok) {
       ys = a.ex_offsets[yi];
       yn = a.ex_offsets[yi + 1] - ys;
     }
-    uint64_t left = __ballot(ok);
+    const bool far = yn > kLongRow;
+    if (far) out[c] = __builtin_bit_cast(double, kLeft);
+    left &= ~__ballot(far);
     while (left) {
       // the candidates of the first x left
       const uint32_t x = uint32_t(__builtin_amdgcn_readlane(int(xi), __ffsll((unsigned long long)left) - 1));
       uint64_t run = left & __ballot(xi == x);
       left &= ~run;
       const int64_t xs = a.ex_offsets[x], xn = a.ex_offsets[x + 1] - xs;
-      if (xn > kHashRow) {
-        for (; run; run &= run - 1) {
-          const int l = __ffsll((unsigned long long)run) - 1;
-          const double sim = exact_wave(a, x, uint32_t(__builtin_amdgcn_readlane(int(yi), l)), keys, vals);
-          if (lane == 0) out[c0 + l] = sim;
-        }
+      if (xn > kHashRow<CSR>) {
+        if ((run >> lane) & 1u) out[c] = __builtin_bit_cast(double, kLeft);
         continue;
       }
       wave_lds_sync();   // the table before was read
@@ -1095,7 +1111,7 @@ __global__ __launch_bounds__(kBlock) void k_exact_pairs(VerifyArgs a, int share,
           top = v;
         } else {
           uint32_t slot = hash_slot(key);
-          for (;;) {   // (at most kHashRow of the slots are taken: one is free)
+          for (;;) {   // (at most 3 in 8 of the slots are taken: one is free)
             const uint32_t old = atomicCAS(&keys[slot], kHashEmpty, key);
             if (old == kHashEmpty) break;
             slot = (slot + 1) & (kHashSlots - 1);
@@ -1131,6 +1147,40 @@ __global__ __launch_bounds__(kBlock) void k_exact_pairs(VerifyArgs a, int share,
         if (mine >= 0 && (lane & (one ? 63 : 15)) == 0) out[c0 + mine] = sim;
       }
     }
+  }
+}
+
+// A wave per pair: every candidate of the call, or (LEFT) those that
+// k_exact_runs left, `window` (at most 64) candidates to a block.
+template <bool LEFT>
+__global__ __launch_bounds__(kBlock) void k_exact_pairs(VerifyArgs a, int window, double *out) {
+  __shared__ uint32_t s_idx[kBlock / kWave][kExactLds];
+  __shared__ float s_val[kBlock / kWave][kExactLds];
+  const int w = threadIdx.x >> 6;
+  auto pair = [&](int64_t c) {
+    uint32_t xi, yi;
+    if (!fetch_candidate(a, c, xi, yi)) {
+      if (lane_id() == 0) {
+        out[c] = __builtin_nan("");
+        raise_status(a.status, BLSH_EBADID);
+      }
+      return;
+    }
+    const double sim = exact_wave(a, xi, yi, s_idx[w], s_val[w]);
+    if (lane_id() == 0) out[c] = sim;
+  };
+  if constexpr (LEFT) {
+    for (int64_t c0 = a.c_begin + int64_t(blockIdx.x) * window; c0 < a.c_end; c0 += int64_t(gridDim.x) * window) {
+      const int64_t c = c0 + lane_id();
+      const uint64_t todo = __ballot(lane_id() < window && c < a.c_end && __builtin_bit_cast(uint64_t, out[c]) == kLeft);
+      __syncthreads();   // (every wave has read the marks before one is replaced)
+      int i = 0;
+      for (uint64_t m = todo; m; m &= m - 1, ++i)
+        if (i % (kBlock / kWave) == w) pair(c0 + __ffsll((unsigned long long)m) - 1);
+    }
+  } else {
+    const int64_t waves = int64_t(gridDim.x) * (kBlock / kWave);
+    for (int64_t c = a.c_begin + int64_t(blockIdx.x) * (kBlock / kWave) + w; c < a.c_end; c += waves) pair(c);
   }
 }
 
@@ -2129,12 +2179,20 @@ int launch_exact_pairs(blsh_ctx *ctx, const VerifyArgs &a, double *out, hipStrea
     else
       hipLaunchKernelGGL(k_exact_dense_pairs<1>, nb, dim3(kBlock), 0, s, a, out);
   } else {
-    // 64 candidates to a wave where that fills the chip, fewer where it does not:
-    // a wave's distinct x are worked through one after another
-    const int share = int(std::min<int64_t>(kWave, blocks_for(n, int64_t(ctx->n_cu) * 32)));
-    const dim3 nb(unsigned(std::min<int64_t>(blocks_for(n, int64_t(share) * (kBlock / kWave)), int64_t(ctx->n_cu) * 64)));
-    if (a.ex_kind == BLSH_CSR) hipLaunchKernelGGL(k_exact_pairs<true>, nb, dim3(kBlock), 0, s, a, share, out);
-    else hipLaunchKernelGGL(k_exact_pairs<false>, nb, dim3(kBlock), 0, s, a, share, out);
+    // (a second launch and the marks cost about 4 us: calls of up to 65,536 pairs, 50 to
+    // 120 us with a wave a pair, go without)
+    if (n <= int64_t(ctx->n_cu) * 256) {
+      const dim3 nb(unsigned(std::min<int64_t>(blocks_for(n, kBlock / kWave), int64_t(ctx->n_cu) * 16)));
+      hipLaunchKernelGGL(k_exact_pairs<false>, nb, dim3(kBlock), 0, s, a, 0, out);
+    } else {
+      const int share = int(std::min<int64_t>(kWave, blocks_for(n, int64_t(ctx->n_cu) * 32)));
+      const dim3 nb(unsigned(std::min<int64_t>(blocks_for(n, int64_t(share) * (kBlock / kWave)), int64_t(ctx->n_cu) * 64)));
+      if (a.ex_kind == BLSH_CSR) hipLaunchKernelGGL(k_exact_runs<true>, nb, dim3(kBlock), 0, s, a, share, out);
+      else hipLaunchKernelGGL(k_exact_runs<false>, nb, dim3(kBlock), 0, s, a, share, out);
+      const int window = 4 * int(std::min<int64_t>(kWave / 4, blocks_for(n, int64_t(ctx->n_cu) * 128)));
+      const dim3 np(unsigned(std::min<int64_t>(blocks_for(n, window), int64_t(ctx->n_cu) * 64)));
+      hipLaunchKernelGGL(k_exact_pairs<true>, np, dim3(kBlock), 0, s, a, window, out);
+    }
   }
   return hipGetLastError() == hipSuccess ? BLSH_OK : BLSH_EDEVICE;
 }

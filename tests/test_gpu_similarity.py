@@ -148,9 +148,10 @@ def test_a_small_sample_is_spread_over_the_chip(ctx, kind):
     assert us[1000] < 4 * us[1]
 
 
-@pytest.mark.parametrize("n", [8192, 8193, 8192 * 63 + 5, 8192 * 64 + 1])
+@pytest.mark.parametrize("n", [8193, 65536, 65537, 8192 * 9, 8192 * 63 + 5, 8192 * 64 + 1])
 def test_candidates_a_wave(ctx, n):
-    """One, two and up to 64 candidates to a wave (256 CUs: 8192 waves), the last wave's share cut short."""
+    """A wave a pair (256 CUs: up to 65,536 pairs), then 9 and up to 64 candidates to
+    a wave, half of them in runs and half lone, the last wave's share cut short."""
     rng = np.random.default_rng(n)
     off, idx = csr_rows(rng, 300, 7, 140)
     x, y = rng.integers(0, 300, n), rng.integers(0, 300, n)
@@ -162,3 +163,81 @@ def test_candidates_a_wave(ctx, n):
                                            P.set_vectors(up(off), up(idx.reshape(-1)), 140)))[:n]
     P.bayeslsh_sync(ctx)
     np.testing.assert_array_equal(got, common / (14 - common))
+
+
+@pytest.mark.parametrize("kind", ["csr", "sets"])
+@pytest.mark.parametrize("spread", [900, 100_000])
+def test_runs_of_one_x_over_odd_rows(ctx, kind, spread):
+    """More pairs than go a wave each: the shapes above in runs of 64, 5 and 2 and one
+    run across waves, bad ids among them."""
+    rng = np.random.default_rng(spread + 1)
+    rs = rows(rng, spread)
+    n = len(rs)
+    vs = [rng.normal(size=len(r)).astype(np.float32) for r in rs] if kind == "csr" else None
+    off = np.zeros(n + 1, np.int64)
+    np.cumsum([len(r) for r in rs], out=off[1:])
+    idx = np.concatenate(rs).astype(np.uint32)
+    vecs = (P.csr_vectors(up(off), up(idx), up(np.concatenate(vs)), 1 << 32) if kind == "csr"
+            else P.set_vectors(up(off), up(idx), 1 << 32))
+    ax, ay = (v.reshape(-1) for v in np.indices((n, n)))
+    table = reference(rs, vs, ax, ay).reshape(n, n)
+    m = 70_000
+    x = np.concatenate([np.repeat(rng.integers(0, n, m // r + 1), r)[: m // 4] for r in (64, 5, 2, m)])
+    y = rng.integers(0, n, len(x))
+    bad = rng.choice(len(x), 50, replace=False)
+    y[bad[:25]], x[bad[25:]] = n, n + 3
+    got = down(P.bayeslsh_exact_similarity(ctx, P.pairs(up(x.astype(np.uint32)), up(y.astype(np.uint32))), vecs))[:len(x)]
+    with pytest.raises(P.BayesLSHError):
+        P.bayeslsh_sync(ctx)
+    ok = np.ones(len(x), bool)
+    ok[bad] = False
+    assert np.isnan(got[bad]).all()
+    np.testing.assert_allclose(got[ok], table[x[ok], y[ok]], rtol=0, atol=1e-12)
+
+
+@pytest.mark.parametrize("kind", ["csr", "sets"])
+def test_rows_longer_than_the_table(ctx, kind):
+    """Rows of one piece, of several and of parts of one against short rows, rows
+    of their own kind, rows that end before a piece does and rows far longer."""
+    rng = np.random.default_rng(17)
+    sizes = [0, 1, 30, 64, 65, 300, 383, 384, 385, 386, 500, 767, 768, 769, 1024, 1025, 1200, 1536, 2000, 5000, 17_000, 40_000]
+    rs = [np.sort(rng.choice(60_000, size=n, replace=False)).astype(np.int64) for n in sizes]
+    rs += [np.arange(400), np.arange(50_000, 51_000), np.arange(0, 60_000, 90), np.arange(59_000, 60_000)]
+    for i in range(5, len(rs), 3):
+        rs[i][-1] = TOP
+    n = len(rs)
+    vs = [rng.normal(size=len(r)).astype(np.float32) for r in rs] if kind == "csr" else None
+    off = np.zeros(n + 1, np.int64)
+    np.cumsum([len(r) for r in rs], out=off[1:])
+    idx = np.concatenate(rs).astype(np.uint32)
+    vecs = (P.csr_vectors(up(off), up(idx), up(np.concatenate(vs)), 1 << 32) if kind == "csr"
+            else P.set_vectors(up(off), up(idx), 1 << 32))
+    x, y = (v.reshape(-1) for v in np.indices((n, n)))
+    want = reference(rs, vs, x, y)
+    many = np.tile(np.arange(n * n), 65536 // (n * n) + 2)
+    for order in (np.arange(n * n), many, rng.permutation(many)):   # a wave a pair, runs of one x, lone pairs
+        got = down(P.bayeslsh_exact_similarity(ctx, P.pairs(up(x[order].astype(np.uint32)), up(y[order].astype(np.uint32))),
+                                               vecs))[:len(order)]
+        P.bayeslsh_sync(ctx)
+        np.testing.assert_allclose(got, want[order], rtol=0, atol=1e-12)
+
+
+@pytest.mark.parametrize("kind,long", [("csr", 500), ("sets", 100_000)])
+def test_long_rows_take_no_longer_than_their_entries(ctx, kind, long):
+    """Pairs of a row of 100 terms and a long one, 64 of them, against 64 pairs of
+    rows of 100: a set of 100,000 is searched, not read; rows past the table's
+    size are not one pair after another in a wave."""
+    rng = np.random.default_rng(4)
+    short, sidx = csr_rows(rng, 64, 100, 1 << 20)
+    _, lidx = csr_rows(rng, 64, long, 1 << 20)
+    off = np.concatenate([short, short[-1] + long * np.arange(1, 65, dtype=np.int64)])
+    idx = np.concatenate([sidx.reshape(-1), lidx.reshape(-1)])
+    vecs = (P.csr_vectors(up(off), up(idx), up(rng.normal(size=idx.size).astype(np.float32)), 1 << 20)
+            if kind == "csr" else P.set_vectors(up(off), up(idx), 1 << 20))
+    i, out = np.arange(64, dtype=np.uint32), torch.empty(64, dtype=torch.float64, device="cuda")
+    us = []
+    for x, y in ((i, i[::-1]), (i, i + 64), (i + 64, i)):
+        c = P.pairs(up(np.ascontiguousarray(x)), up(np.ascontiguousarray(y)))
+        us.append(passes_us(lambda: P.bayeslsh_exact_similarity(ctx, c, vecs, out)))
+    print("similarity of long rows %s %d: %s us" % (kind, long, us), flush=True)
+    assert max(us[1:]) < 6 * us[0]

@@ -161,8 +161,9 @@ __global__ __launch_bounds__(256) void k_fill_u8(uint8_t *p, int64_t n) {
 // With S = sum v g' in fp32, the sum has S's sign wherever |S| exceeds
 //   sum |v| (kFastErr + half a unit [table] + 2^-13 [2-byte entries])
 //   + the fp32 additions' rounding;
-// every other bit (about 1 in 1000 with the table and rows of 100 terms, 1 in
-// 30,000 without) is marked open and worked out from g in FP64.  So the bits are those of
+// every other bit (about 1 in 1000 with the table and rows of 100 equal weights, 1 in
+// 6,400 without) is marked open and settled: by the approximate entries themselves
+// summed in FP64 where that is enough, else (1 in 30,000) by g.  So the bits are those of
 // the FP64 sums, every one.
 // ---------------------------------------------------------------------------
 // |g' - g| over every Philox word: the radius is off by at most 5.8e-7 and the sine
@@ -170,7 +171,8 @@ __global__ __launch_bounds__(256) void k_fill_u8(uint8_t *p, int64_t n) {
 // and the entry's own rounding to fp32 add at most 8.2e-7.
 constexpr float kFastErr = 0x1p-18f;
 constexpr float kUnit = 4800.f;          // |g| < 6.77: codes within 16 bits
-constexpr int kSumBlock = 32;            // nonzeros summed before they are added to the row's sum
+constexpr int kSumBlock = 32;            // nonzeros summed before they are added to the sum of a stretch
+constexpr int kSumStretch = 1024;        // nonzeros of a stretch; a longer row's stretches are added in FP64
 
 __device__ inline float srp_fast_radius(uint32_t w) {
   // sqrt(-2 ln u), u = (w + 0.5) 2^-32; near 1 from t = 1 - u, which fp32 holds to its last bit
@@ -178,6 +180,13 @@ __device__ inline float srp_fast_radius(uint32_t w) {
   const float near_one = t * (1.f + t * (0.5f + t * (1.f / 3.f + t * (0.25f + t * (0.2f + t * (1.f / 6.f))))));
   const float l = t < 0.0625f ? near_one : -0.69314718f * __builtin_amdgcn_logf(u);
   return __builtin_amdgcn_sqrtf(2.f * l);
+}
+
+// About the entry of hash h at coordinate `term`.
+__device__ inline float srp_fast1(uint32_t term, uint32_t h, uint32_t k0, uint32_t k1) {
+  const uint4 w = philox4x32_10(make_uint4(term, h >> 2, 0u, 0u), k0, k1);
+  const float a = __builtin_fmaf(float(h & 2 ? w.w : w.y), 0x1p-32f, 0x1p-33f);
+  return srp_fast_radius(h & 2 ? w.z : w.x) * (h & 1 ? __builtin_amdgcn_sinf(a) : __builtin_amdgcn_cosf(a));
 }
 
 // About the entries of hashes 4 q .. 4 q + 3 at coordinate `term`.
@@ -238,6 +247,7 @@ __global__ __launch_bounds__(256) void k_srp_sparse(const int64_t *offsets, cons
                                                     int32_t word_major, uint32_t *out, uint32_t *open,
                                                     const int16_t *table, int64_t dim, float err) {
   constexpr int U = TABLE ? 8 : 1;
+  __shared__ double s_total[4 * QPL][256];   // sums of a long row's stretches (each thread its own)
   typedef uint32_t codes __attribute__((ext_vector_type(2 * QPL), aligned(8)));
   const int lane = lane_id();
   const int64_t row_blocks = int64_t(gridDim.x) / n_slices;
@@ -300,6 +310,14 @@ __global__ __launch_bounds__(256) void k_srp_sparse(const int64_t *offsets, cons
     }
 #pragma unroll
     for (int c = 0; c < 4 * QPL; ++c) { sum[c] += acc[c]; acc[c] = 0.f; }
+    if ((t1 - s) % kSumStretch == 0 && t1 < e) {   // wave-uniform
+      const bool first = t1 - s == kSumStretch;
+#pragma unroll
+      for (int c = 0; c < 4 * QPL; ++c) {
+        s_total[c][threadIdx.x] = (first ? 0.0 : s_total[c][threadIdx.x]) + double(sum[c]);
+        sum[c] = 0.f;
+      }
+    }
   }
   // the mass sum |v|
   float mass = 0.f;
@@ -307,18 +325,20 @@ __global__ __launch_bounds__(256) void k_srp_sparse(const int64_t *offsets, cons
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) mass += __shfl_xor(mass, o);
   // roundings: one per nonzero of a block's sum (a drawn entry's product with
-  // the unit: one more of its own term), one per block, each 2^-24 of at most
+  // the unit: one more of its own term), one per block of a stretch, each 2^-24 of at most
   // 2^15 units of the mass; and those of the mass itself.  Near the bottom of the
   // float range a rounding is 2^-150 instead, at most 10 of them a nonzero: under
   // 2^-8 of the mass (two of the four roundings to spare) for any row of 2^32
   // nonzeros and a mass of 2^-100 or more.  A smaller mass decides nothing.
   const float n = float(e - s);
-  const float T = mass < 0x1p-100f ? INFINITY : mass * (err + (kSumBlock + n / kSumBlock + 4.f) * 0x1p-9f) * (1.f + n * 0x1p-23f) * 1.001f;
+  const float T = mass < 0x1p-100f ? INFINITY : mass * (err + (kSumBlock + fminf(n, kSumStretch) / kSumBlock + 4.f) * 0x1p-9f) * (1.f + n * 0x1p-23f) * 1.001f;
   uint32_t nib = 0, unsure = 0;
 #pragma unroll
   for (int c = 0; c < 4 * QPL; ++c) {
-    nib |= uint32_t(sum[c] >= 0.f) << c;
-    unsure |= uint32_t(!(fabsf(sum[c]) > T && fabsf(sum[c]) < INFINITY)) << c;   // (an overflow decides nothing)
+    // (the cast rounds by 2^-24 of the sum itself, which T has room for)
+    const float S = e - s > kSumStretch ? float(s_total[c][threadIdx.x] + double(sum[c])) : sum[c];
+    nib |= uint32_t(S >= 0.f) << c;
+    unsure |= uint32_t(!(fabsf(S) > T && fabsf(S) < INFINITY)) << c;   // (an overflow decides nothing)
   }
   constexpr int G = 8 / QPL;   // lanes per word
   const int sh = 4 * QPL * (lane & (G - 1)), w = q >> 3;
@@ -332,23 +352,36 @@ __global__ __launch_bounds__(256) void k_srp_sparse(const int64_t *offsets, cons
 
 // The open bits of rows [rows0, rows1) (open = null: every bit), worked out:
 // the FP64 sum of v g over the row's nonzeros in order, g rounded to fp32 (Q16:
-// the value of its 2-byte code).  A block lists the open bits of its 32 rows in
-// LDS, 256 words at a time while they fit; then 8 lanes take a bit: each draws
-// every eighth nonzero's entry, and all 8 sum the products in order.
+// the value of its 2-byte code).  A block lists the open bits of its `per` rows
+// (at most kSettleRows) in LDS, 256 words at a time while they fit.  8 lanes take
+// a bit, each every eighth nonzero, and sum the approximate entries themselves in
+// FP64: that leaves only the entries' error, |v| kFastErr (and half a code's cell),
+// so that 1 bit in 30 of those the table left open remains.  What remains is
+// drawn in FP64, a wave to a bit and 64 nonzeros at a time, the products (exact
+// in FP64) added in order.  Rows of 100,000 equal weights leave 3% of their bits open:
+// 64 of them take 45 ms in all (63 with FP64 entries for every bit; 6800 with every
+// open bit drawn in FP64 by 8 lanes, the stretches added in fp32 and 14 to 34% of the bits open).
 constexpr int kSettleList = 8192, kSettleRows = 32;
 static_assert(kSettleList >= 256 * 32, "one round of words fits the list");
+constexpr uint32_t kSettled = 0xFFFFFFFFu;
 
 template <bool Q16>
 __global__ __launch_bounds__(256) void k_srp_settle(const int64_t *offsets, const uint32_t *indices,
                                                     const float *values, int64_t n_rows, int64_t rows0, int64_t rows1,
-                                                    int32_t n_bits, uint32_t k0, uint32_t k1, int32_t word_major,
-                                                    uint32_t *out, const uint32_t *open) {
-  __shared__ uint32_t s_bit[kSettleList];   // (row - row0) n_bits + hash (at most 32 x 2048)
+                                                    int32_t per, int32_t n_bits, uint32_t k0, uint32_t k1,
+                                                    int32_t word_major, uint32_t *out, const uint32_t *open) {
+  __shared__ uint32_t s_bit[kSettleList];   // (row - row0) n_bits + hash (at most 32 x 2048), or kSettled
   __shared__ uint32_t s_wave[4];
   const int W = n_bits / 32, lane = lane_id(), wv = threadIdx.x >> 6, r = lane & 7;
-  const int64_t row0 = rows0 + int64_t(blockIdx.x) * kSettleRows;
-  const int words = int(min<int64_t>(kSettleRows, rows1 - row0)) * W;
+  const int64_t row0 = rows0 + int64_t(blockIdx.x) * per;
+  const int words = int(min<int64_t>(per, rows1 - row0)) * W;
   uint32_t count = 0;   // entries of the list (block-uniform)
+  auto put = [&](int64_t row, uint32_t h, bool one) {
+    uint32_t *word = word_major ? out + size_t(h >> 5) * n_rows + row : out + size_t(row) * W + (h >> 5);
+    const uint32_t bit = 1u << (h & 31);
+    if (one) atomicOr(word, bit);
+    else atomicAnd(word, ~bit);
+  };
   auto settle = [&]() {
     __syncthreads();
     for (uint32_t i0 = 0; i0 < count; i0 += 32) {   // block-uniform
@@ -358,25 +391,47 @@ __global__ __launch_bounds__(256) void k_srp_settle(const int64_t *offsets, cons
       const int64_t row = row0 + b / uint32_t(n_bits);
       const uint32_t h = b % uint32_t(n_bits);
       const int64_t s = offsets[row], e = act ? offsets[row + 1] : s;
-      double acc = 0.0;
-      for (int64_t t = s; __ballot(t < e) != 0; t += 8) {
-        double v = 0.0, g = 0.0;
-        if (t + r < e) {
-          v = values[t + r];
-          g = srp_gauss1(indices[t + r], h, k0, k1);
-          if constexpr (Q16) g = q16_value(q16_code(g));
-        }
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          const double vj = __shfl(v, j, 8), gj = __shfl(g, j, 8);
-          if (t + j < e) acc = __builtin_fma(vj, gj, acc);
-        }
+      double sum = 0.0, mass = 0.0;
+      for (int64_t t = s + r; t < e; t += 8) {
+        const double v = values[t];
+        sum = __builtin_fma(v, double(srp_fast1(indices[t], h, k0, k1)), sum);
+        mass += fabs(v);
       }
-      if (act && r == 0) {
-        uint32_t *word = word_major ? out + size_t(h >> 5) * n_rows + row : out + size_t(row) * W + (h >> 5);
-        const uint32_t bit = 1u << (h & 31);
-        if (acc >= 0.0) atomicOr(word, bit);
-        else atomicAnd(word, ~bit);
+#pragma unroll
+      for (int o = 1; o < 8; o <<= 1) {
+        sum += __shfl_xor(sum, o);
+        mass += __shfl_xor(mass, o);
+      }
+      // (the last term: the roundings of either FP64 sum, each 2^-53 of at most 7 times the mass)
+      const double T = mass * (kFastErr + (Q16 ? 0x1p-13 : 0.0) + double(e - s) * 0x1p-49) * 1.0001;
+      if (act && r == 0 && fabs(sum) > T && fabs(sum) < INFINITY) {
+        put(row, h, sum > 0.0);
+        s_bit[i] = kSettled;
+      }
+    }
+    __syncthreads();
+    for (uint32_t i0 = wv * kWave; i0 < count; i0 += 4 * kWave) {   // wave-uniform
+      const uint32_t mine = i0 + lane < count ? s_bit[i0 + lane] : kSettled;
+      for (uint64_t left = __ballot(mine != kSettled); left; left &= left - 1) {
+        const uint32_t b = uint32_t(__builtin_amdgcn_readlane(int(mine), __ffsll((unsigned long long)left) - 1));
+        const int64_t row = row0 + b / uint32_t(n_bits);
+        const uint32_t h = b % uint32_t(n_bits);
+        const int64_t s = offsets[row], e = offsets[row + 1];
+        double acc = 0.0;
+        for (int64_t t = s; t < e; t += kWave) {
+          double p = 0.0;
+          if (t + lane < e) {
+            double g = srp_gauss1(indices[t + lane], h, k0, k1);
+            if constexpr (Q16) g = q16_value(q16_code(g));
+            p = double(values[t + lane]) * g;
+          }
+          const int n = int(min<int64_t>(kWave, e - t));
+          const uint64_t u = __builtin_bit_cast(uint64_t, p);
+          for (int j = 0; j < n; ++j)
+            acc += __builtin_bit_cast(double, uint64_t(uint32_t(__builtin_amdgcn_readlane(int(u), j))) |
+                                                  uint64_t(uint32_t(__builtin_amdgcn_readlane(int(u >> 32), j))) << 32);
+        }
+        if (lane == 0) put(row, h, acc >= 0.0);
       }
     }
     __syncthreads();
@@ -907,9 +962,11 @@ int launch_srp_sparse(blsh_ctx *ctx, const int64_t *offsets, const uint32_t *ind
       hipLaunchKernelGGL((!use_table ? k_srp_sparse<false, 1> : qpl == 2 ? k_srp_sparse<true, 2> : k_srp_sparse<true, 1>),
                          dim3(unsigned((r1 - r0 + 3) / 4 * n_slices)), dim3(256), 0, s, offsets, indices, values, n_rows,
                          r0, r1, n_bits, n_slices, k0, k1, int(word_major), out, open, table, dim, err);
-    hipLaunchKernelGGL(q16 ? k_srp_settle<true> : k_srp_settle<false>,
-                       dim3(unsigned((r1 - r0 + kSettleRows - 1) / kSettleRows)), dim3(256), 0, s, offsets, indices,
-                       values, n_rows, r0, r1, n_bits, k0, k1, int(word_major), out, filter ? open : nullptr);
+    // (fewer rows to a block where 32 would leave CUs without one)
+    const int per = int(std::max<int64_t>(1, std::min<int64_t>(kSettleRows, (r1 - r0) / (int64_t(ctx->n_cu) * 4))));
+    hipLaunchKernelGGL(q16 ? k_srp_settle<true> : k_srp_settle<false>, dim3(unsigned((r1 - r0 + per - 1) / per)),
+                       dim3(256), 0, s, offsets, indices, values, n_rows, r0, r1, per, n_bits, k0, k1, int(word_major),
+                       out, filter ? open : nullptr);
   }
   return hipGetLastError() == hipSuccess ? BLSH_OK : BLSH_EDEVICE;
 }

@@ -117,3 +117,61 @@ def test_values_at_the_bottom_of_the_float_range(nnz, dim, flags):
     finally:
         a.close()
         b.close()
+
+
+def long_rows(rng, sizes, dim):
+    """Rows of `sizes` sorted terms, weights of one size and of many."""
+    rows = [np.sort(rng.permutation(dim)[:n]) for n in sizes]
+    vals = [np.where(rng.random(n) < 0.5, 1, rng.normal(size=n)).astype(np.float32) for n in sizes]
+    off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    return off, np.concatenate(rows).astype(np.uint32), np.concatenate(vals)
+
+
+@pytest.mark.parametrize("n_bits", [160, 1024])
+@pytest.mark.parametrize("flags", [0, P.SRP_PLANES_Q16])
+def test_rows_longer_than_a_stretch(n_bits, flags):
+    """Rows about a multiple of 1024 nonzeros long and far longer: the same bits
+    from the table, from drawn entries and from the sums alone."""
+    rng = np.random.default_rng(n_bits + flags)
+    sizes = [1023, 1024, 1025, 1055, 1056, 1057, 2047, 2048, 2049, 3072, 5000, 9999, 30_000, 7, 1024]
+    off, idx, val = long_rows(rng, sizes, 30_000)
+    got = {}
+    for name, room, dim in (("sums", 0, 30_000), ("drawn", None, 1 << 20), ("table", None, 30_000)):
+        ctx = P.bayeslsh_create(0)
+        try:
+            if room is not None:
+                P.bayeslsh_reserve_workspace(ctx, room, fixed=True)
+            got[name] = bits_of(ctx, P.csr_vectors(up(off), up(idx), up(val), dim), len(sizes), n_bits, P.OBJECT_MAJOR, flags)
+        finally:
+            ctx.close()
+    for name, w in got.items():
+        np.testing.assert_array_equal(w, got["sums"], err_msg=name)
+
+
+def test_long_rows_keep_their_pace():
+    """The same nonzeros in 200 rows of 30,000 as in 60,000 of 100: 800 waves, a
+    quarter of what the chip holds, and a few times the open bits, so within 16
+    times (with every open bit's entries drawn in FP64 it was over 100)."""
+    rng = np.random.default_rng(8)
+    ctx, dim = P.bayeslsh_create(0), 1 << 20
+    us = {}
+    try:
+        for n_rows, n in ((60_000, 100), (200, 30_000)):
+            step = dim // n
+            idx = (np.arange(n) * step + rng.integers(0, step, (n_rows, n))).astype(np.uint32)
+            off = np.arange(n_rows + 1, dtype=np.int64) * n
+            vecs = P.csr_vectors(up(off), up(idx.reshape(-1)), up(rng.normal(size=idx.size).astype(np.float32)), dim)
+            out = torch.empty(n_rows * 64, dtype=torch.int32, device="cuda").view(torch.uint32)
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            runs = []
+            for _ in range(3):
+                a.record()
+                P.bayeslsh_srp_sigs(ctx, vecs, None, 2048, 5, P.OBJECT_MAJOR, out)
+                b.record()
+                torch.cuda.synchronize()
+                runs.append(a.elapsed_time(b) * 1e3)
+            us[n] = min(runs)
+        print("sparse SRP, 6M nonzeros: %s us" % us, flush=True)
+        assert us[30_000] < 16 * us[100]
+    finally:
+        ctx.close()

@@ -334,14 +334,15 @@ enum {
  *     u_i = (w_i + 0.5)/2^32, (z0,z1) = BoxMuller(u0,u1), (z2,z3) = BoxMuller(u2,u3),
  *     entry = z_{h mod 4}; a bit is the sign of the projection accumulated in
  *     FP64.  Most signs are decided from approximate entries with an error
- *     bound, the others (and every one without room for 32 rows' masks) from
+ *     bound, the others (and every one without room for 256 rows' masks) from
  *     the entries themselves: the same bits.  The call reads the nonzero count
  *     (offsets[n_obj]) back, waiting for `stream`; when it exceeds 2 * dim and
  *     dim * n_bits * 2 bytes fit in 16 GiB, the approximate entries of every
  *     term < dim are drawn once into a table in the context workspace (an index
  *     >= dim, outside the CSR contract, is drawn as it occurs rather than read
  *     past the table).  The workspace also holds n_obj * n_bits / 8 bytes of
- *     masks (of fewer rows at a time when it is fixed smaller).
+ *     masks, of fewer rows at a time when it is fixed smaller or device memory
+ *     is short; a table that cannot be allocated is done without.
  * flags: 0 or BLSH_SRP_PLANES_Q16 (CSR only; with DENSE vectors it is
  * BLSH_EINVAL).  n_bits must be a multiple of 32 (DENSE: of 64). */
 int bayeslsh_srp_sigs(blsh_ctx *ctx, const blsh_vectors *vecs, const float *planes, int32_t n_bits,

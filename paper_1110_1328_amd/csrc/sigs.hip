@@ -104,6 +104,20 @@ __device__ inline uint4 philox4x32_10(uint4 c, uint32_t k0, uint32_t k1) {
   return c;
 }
 
+// The plane entries of hashes 4 q .. 4 q + 3 at coordinate `term`.
+__device__ inline void srp_gauss4(uint32_t term, uint32_t q, uint32_t k0, uint32_t k1, double g[4]) {
+  const uint4 w = philox4x32_10(make_uint4(term, q, 0u, 0u), k0, k1);
+  const double two32 = 4294967296.0, two_pi = 6.283185307179586476925286766559;
+  const double r0 = sqrt(-2.0 * log((double(w.x) + 0.5) / two32)), r1 = sqrt(-2.0 * log((double(w.z) + 0.5) / two32));
+  double s1, c1, s3, c3;   // one argument reduction for each sine-cosine pair
+  sincos(two_pi * ((double(w.y) + 0.5) / two32), &s1, &c1);
+  sincos(two_pi * ((double(w.w) + 0.5) / two32), &s3, &c3);
+  g[0] = double(float(r0 * c1));
+  g[1] = double(float(r0 * s1));
+  g[2] = double(float(r1 * c3));
+  g[3] = double(float(r1 * s3));
+}
+
 // The plane entry of hash h at coordinate `term`.
 __device__ inline double srp_gauss1(uint32_t term, uint32_t h, uint32_t k0, uint32_t k1) {
   const uint4 w = philox4x32_10(make_uint4(term, h >> 2, 0u, 0u), k0, k1);
@@ -352,8 +366,10 @@ __global__ __launch_bounds__(256) void k_srp_sparse(const int64_t *offsets, cons
 
 // The open bits of rows [rows0, rows1) (open = null: every bit), worked out:
 // the FP64 sum of v g over the row's nonzeros in order, g rounded to fp32 (Q16:
-// the value of its 2-byte code).  A block lists the open bits of its `per` rows
-// (at most kSettleRows) in LDS, 256 words at a time while they fit.  8 lanes take
+// the value of its 2-byte code).  Rows with more than half their bits open (weights
+// outside the fp32 sums' range, or no workspace for masks) go four hashes to a
+// thread, the entries of a quad drawn together.  Of the others a block lists the
+// open bits of its `per` rows (at most kSettleRows) in LDS, 256 words at a time while they fit.  8 lanes take
 // a bit, each every eighth nonzero, and sum the approximate entries themselves in
 // FP64: that leaves only the entries' error, |v| kFastErr (and half a code's cell),
 // so that 1 bit in 30 of those the table left open remains.  What remains is
@@ -372,9 +388,47 @@ __global__ __launch_bounds__(256) void k_srp_settle(const int64_t *offsets, cons
                                                     int32_t word_major, uint32_t *out, const uint32_t *open) {
   __shared__ uint32_t s_bit[kSettleList];   // (row - row0) n_bits + hash (at most 32 x 2048), or kSettled
   __shared__ uint32_t s_wave[4];
-  const int W = n_bits / 32, lane = lane_id(), wv = threadIdx.x >> 6, r = lane & 7;
+  __shared__ uint32_t s_row[kSettleRows];   // open bits of a row, then whether it goes whole
+  __shared__ int32_t s_whole[kSettleRows];
+  const int W = n_bits / 32, Q = n_bits / 4, lane = lane_id(), wv = threadIdx.x >> 6, r = lane & 7;
   const int64_t row0 = rows0 + int64_t(blockIdx.x) * per;
-  const int words = int(min<int64_t>(per, rows1 - row0)) * W;
+  const int n_own = int(min<int64_t>(per, rows1 - row0)), words = n_own * W;
+  if (threadIdx.x < kSettleRows) s_row[threadIdx.x] = 0;
+  __syncthreads();
+  if (open)
+    for (int w = threadIdx.x; w < words; w += 256) {
+      const uint32_t mask = open[size_t(row0 - rows0) * W + w];
+      if (mask) atomicAdd(&s_row[w / W], uint32_t(__popc(mask)));
+    }
+  __syncthreads();
+  const bool all = lane < n_own && (!open || 2 * s_row[lane % kSettleRows] > uint32_t(n_bits));
+  const uint64_t whole = __ballot(all);   // (the same in every wave)
+  __syncthreads();
+  if (wv == 0 && lane < n_own) {
+    s_row[lane] = all;
+    if (all) s_whole[lanes_below(whole)] = lane;
+  }
+  __syncthreads();
+  // (Q is a multiple of 8, so the lanes of a word are in the loop together)
+  for (int it = threadIdx.x; it < __popcll(whole) * Q; it += 256) {
+    const int64_t row = row0 + s_whole[it / Q];
+    const int q = it % Q;
+    const int64_t s = offsets[row], e = offsets[row + 1];
+    double acc[4] = {0.0, 0.0, 0.0, 0.0};
+    for (int64_t t = s; t < e; ++t) {
+      const double v = values[t];
+      double g[4];
+      srp_gauss4(indices[t], uint32_t(q), k0, k1, g);
+#pragma unroll
+      for (int c = 0; c < 4; ++c) acc[c] = __builtin_fma(v, Q16 ? q16_value(q16_code(g[c])) : g[c], acc[c]);
+    }
+    uint32_t nib = 0;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) nib |= uint32_t(acc[c] >= 0.0) << c;
+    const uint32_t word = group_or<8>(nib << (4 * r));
+    if (r == 0) out[word_major ? size_t(q >> 3) * n_rows + row : size_t(row) * W + (q >> 3)] = word;
+  }
+  if (!open) return;
   uint32_t count = 0;   // entries of the list (block-uniform)
   auto put = [&](int64_t row, uint32_t h, bool one) {
     uint32_t *word = word_major ? out + size_t(h >> 5) * n_rows + row : out + size_t(row) * W + (h >> 5);
@@ -439,7 +493,7 @@ __global__ __launch_bounds__(256) void k_srp_settle(const int64_t *offsets, cons
   };
   for (int w0 = 0; w0 < words; w0 += 256) {
     const int w = w0 + threadIdx.x;
-    uint32_t mask = w >= words ? 0u : open ? open[size_t(row0 - rows0) * W + w] : 0xFFFFFFFFu;
+    uint32_t mask = w >= words || s_row[w / W] ? 0u : open[size_t(row0 - rows0) * W + w];
     const uint32_t mine = uint32_t(__popc(mask));
     uint32_t before = mine;
 #pragma unroll
@@ -907,6 +961,9 @@ int launch_minhash(blsh_ctx *ctx, const int64_t *offsets, const uint32_t *elems,
 
 constexpr size_t kSrpTableMaxBytes = size_t(16) << 30;
 constexpr int64_t kSrpRows = int64_t(1) << 22;   // rows per launch (8 slices of 64 lanes each: 2^31 work-items)
+// Fewest rows per launch: 20,000 rows of 100 terms, entries drawn, 256 at a time 5.3
+// ms, 32 at a time 34 ms, and 11.5 with every bit worked out.
+constexpr int64_t kSrpFewest = 256;
 
 int launch_srp_sparse(blsh_ctx *ctx, const int64_t *offsets, const uint32_t *indices, const float *values,
                       int64_t n_rows, int64_t dim, int n_bits, uint64_t seed, bool word_major, bool q16,
@@ -920,25 +977,40 @@ int launch_srp_sparse(blsh_ctx *ctx, const int64_t *offsets, const uint32_t *ind
   BLSH_HIP(hipMemcpyAsync(&nnz, offsets + n_rows, sizeof(int64_t), hipMemcpyDeviceToHost, s));
   BLSH_HIP(hipStreamSynchronize(s));
   // workspace: the table, a byte per term, and the masks of as many rows' open
-  // bits as one launch takes.  A context whose workspace is fixed too small for the table
-  // draws the entries per nonzero instead, masks that do not all fit go in
-  // several launches, and without room for 32 rows' masks every bit is
-  // worked out (the same bits each time).
+  // bits as one launch takes.  What does not fit (a workspace fixed smaller, or
+  // not enough device memory): first fewer rows at a time, then no table (entries
+  // drawn per nonzero), then no masks (every bit worked out): the same bits each time.
   auto align = [](size_t b) { return (b + 255) & ~size_t(255); };
   const size_t mask_row = size_t(n_bits / 32) * 4;
   const size_t table_bytes = align(size_t(std::max<int64_t>(dim, 0)) * size_t(n_bits) * sizeof(int16_t));
   const size_t used_bytes = align(size_t(std::max<int64_t>(dim, 0)));
-  const size_t fewest = mask_row * size_t(std::min<int64_t>(n_rows, kSettleRows));
-  const int64_t most = std::min<int64_t>(n_rows, kSrpRows);
-  bool use_table = dim > 0 && nnz > 2 * dim && table_bytes <= kSrpTableMaxBytes &&
-                   (!ctx->ws_fixed || table_bytes + used_bytes + fewest <= ctx->ws_bytes);
+  const int64_t most = std::min<int64_t>(n_rows, kSrpRows), fewest = std::min<int64_t>(n_rows, kSrpFewest);
+  bool use_table = dim > 0 && nnz > 2 * dim && table_bytes <= kSrpTableMaxBytes;
   size_t table_room = use_table ? table_bytes + used_bytes : 0;
-  if (!ctx->ws_fixed && ensure_workspace(ctx, table_room + mask_row * size_t(most)) != BLSH_OK) {
-    (void)hipGetLastError();   // no memory for it: what there is, without the table
-    use_table = false;
-    table_room = 0;
+  int64_t chunk = most;   // rows per launch; 0: no masks
+  if (ctx->ws_fixed) {
+    if (table_room + mask_row * size_t(fewest) > ctx->ws_bytes) {
+      use_table = false;
+      table_room = 0;
+    }
+    chunk = std::min<int64_t>(most, int64_t((ctx->ws_bytes - table_room) / mask_row));
+    if (chunk < fewest) chunk = 0;
+  } else {
+    int rc;
+    while ((rc = ensure_workspace(ctx, table_room + mask_row * size_t(chunk))) == BLSH_ENOMEM) {
+      (void)hipGetLastError();
+      if (chunk > fewest) {
+        chunk = std::max(fewest, chunk / 8);
+      } else if (use_table) {
+        use_table = false;
+        table_room = 0;
+        chunk = most;
+      } else {
+        chunk = 0;
+      }
+    }
+    if (rc) return rc;
   }
-  const int64_t chunk = std::min<int64_t>(most, int64_t((ctx->ws_bytes - table_room) / mask_row));
   int16_t *table = static_cast<int16_t *>(ctx->ws);
   uint8_t *used = static_cast<uint8_t *>(ctx->ws) + table_bytes;
   uint32_t *open = reinterpret_cast<uint32_t *>(static_cast<char *>(ctx->ws) + table_room);
@@ -955,7 +1027,7 @@ int launch_srp_sparse(blsh_ctx *ctx, const int64_t *offsets, const uint32_t *ind
   const int qpl = use_table && n_bits > 256 ? 2 : 1;
   const int n_slices = (n_bits / 4 + kWave * qpl - 1) / (kWave * qpl);
   const float err = kUnit * kFastErr + (use_table ? 0.5f : 0.f) + (q16 ? kUnit / 8192.f : 0.f);
-  const bool filter = chunk >= std::min<int64_t>(n_rows, kSettleRows);
+  const bool filter = chunk > 0;
   for (int64_t r0 = 0, r1; r0 < n_rows; r0 = r1) {
     r1 = std::min(n_rows, r0 + (filter ? chunk : kSrpRows));
     if (filter)
@@ -963,7 +1035,7 @@ int launch_srp_sparse(blsh_ctx *ctx, const int64_t *offsets, const uint32_t *ind
                          dim3(unsigned((r1 - r0 + 3) / 4 * n_slices)), dim3(256), 0, s, offsets, indices, values, n_rows,
                          r0, r1, n_bits, n_slices, k0, k1, int(word_major), out, open, table, dim, err);
     // (fewer rows to a block where 32 would leave CUs without one)
-    const int per = int(std::max<int64_t>(1, std::min<int64_t>(kSettleRows, (r1 - r0) / (int64_t(ctx->n_cu) * 4))));
+    const int per = int(std::max<int64_t>(1, std::min<int64_t>(kSettleRows, (r1 - r0) / (int64_t(ctx->n_cu) * (filter ? 4 : 32)))));
     hipLaunchKernelGGL(q16 ? k_srp_settle<true> : k_srp_settle<false>, dim3(unsigned((r1 - r0 + per - 1) / per)),
                        dim3(256), 0, s, offsets, indices, values, n_rows, r0, r1, per, n_bits, k0, k1, int(word_major),
                        out, filter ? open : nullptr);

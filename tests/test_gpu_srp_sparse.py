@@ -175,3 +175,64 @@ def test_long_rows_keep_their_pace():
         assert us[30_000] < 16 * us[100]
     finally:
         ctx.close()
+
+
+def srp_us(ctx, vecs, n_rows, n_bits):
+    out = torch.empty(n_rows * (n_bits // 32), dtype=torch.int32, device="cuda").view(torch.uint32)
+    a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    runs = []
+    for _ in range(4):
+        a.record()
+        P.bayeslsh_srp_sigs(ctx, vecs, None, n_bits, 5, P.OBJECT_MAJOR, out)
+        b.record()
+        torch.cuda.synchronize()
+        runs.append(a.elapsed_time(b) * 1e3)
+    return min(runs), down(out)
+
+
+@pytest.mark.parametrize("n_rows,nnz,n_bits", [(500, 100, 2048), (4000, 30, 128)])
+def test_no_workspace_costs_the_entries_only(n_rows, nnz, n_bits):
+    """Without room for masks every entry is drawn in FP64, four hashes together:
+    about 4 times the filtered call (one hash at a time: over 100 times)."""
+    rng = np.random.default_rng(n_rows)
+    dim = 1 << 20
+    idx = (np.arange(nnz) * (dim // nnz) + rng.integers(0, dim // nnz, (n_rows, nnz))).astype(np.uint32)
+    vecs = P.csr_vectors(up(np.arange(n_rows + 1, dtype=np.int64) * nnz), up(idx.reshape(-1)),
+                         up(rng.normal(size=idx.size).astype(np.float32)), dim)
+    a, b = P.bayeslsh_create(0), P.bayeslsh_create(0)
+    try:
+        P.bayeslsh_reserve_workspace(b, 0, fixed=True)
+        (t, x), (u, y) = srp_us(a, vecs, n_rows, n_bits), srp_us(b, vecs, n_rows, n_bits)
+        print("sparse SRP %d rows: with a workspace %.0f us, without %.0f us" % (n_rows, t, u), flush=True)
+        np.testing.assert_array_equal(x, y)
+        assert u < 16 * t
+    finally:
+        a.close()
+        b.close()
+
+
+def test_a_table_that_cannot_be_allocated():
+    """With 5 GiB of device memory free, a table of 8 GiB is not to be had, the
+    masks are: entries are drawn as they occur, as in a workspace of the masks' size."""
+    n_rows, nnz, dim, n_bits = 45_000, 100, 1 << 21, 2048
+    rng = np.random.default_rng(2)
+    idx = (np.arange(nnz) * (dim // nnz) + rng.integers(0, dim // nnz, (n_rows, nnz))).astype(np.uint32)
+    vecs = P.csr_vectors(up(np.arange(n_rows + 1, dtype=np.int64) * nnz), up(idx.reshape(-1)),
+                         up(rng.normal(size=idx.size).astype(np.float32)), dim)
+    assert n_rows * nnz > 2 * dim
+    a, b = P.bayeslsh_create(0), P.bayeslsh_create(0)
+    torch.cuda.empty_cache()
+    free = torch.cuda.mem_get_info()[0]
+    taken = torch.empty(free - (5 << 30), dtype=torch.uint8, device="cuda")
+    try:
+        P.bayeslsh_reserve_workspace(b, n_rows * n_bits // 8, fixed=True)
+        (t, x), (u, y) = srp_us(a, vecs, n_rows, n_bits), srp_us(b, vecs, n_rows, n_bits)
+        print("sparse SRP, no table to be had: %.0f us, drawn %.0f us" % (t, u), flush=True)
+        assert n_rows * n_bits // 8 <= P.bayeslsh_workspace_bytes(a) < dim * n_bits * 2
+        np.testing.assert_array_equal(x, y)
+        assert t < 3 * u
+    finally:
+        del taken
+        torch.cuda.empty_cache()
+        a.close()
+        b.close()

@@ -407,8 +407,10 @@ __device__ inline void finish_direct(const VerifyArgs &a) {
 // Agreements of level j for the wave's 64 candidates: the group of G lanes
 // holding a candidate compares the K hashes of each of its G members in turn
 // (lane r hashes 4 r .. 4 r + 3), the rows of up to 8 members requested before any is
-// compared.  SAME_X: one x for the whole wave, read once.  A decided candidate's
-// y is its x (no line of its own).  Returns the count of this lane's candidate.
+// compared.  SAME_X: one x for the whole wave, read once.  A decided candidate has
+// the x of one that is not for both its rows (no line of its own: 8M pairs of many x,
+// one in ten similar, 256 hashes, k = 16 528 us; its own x read on 1555).  Returns the
+// count of this lane's candidate.
 // Bound by the round trips of a wave's gathers: with each member's rows read in
 // turn a level was G trips long, now one or two.  10^6 candidates of one x, 256
 // hashes, k = 32: 17.9 -> 13.9 us; all pairs of 2000 sets: 41.6 -> 37.2 us.
@@ -473,9 +475,12 @@ __global__ __launch_bounds__(kBlock) void k_verify_minhash(VerifyArgs a) {
   const uint32_t x0 = uint32_t(__builtin_amdgcn_readfirstlane(int(xi)));
   const bool same_x = __ballot(alive != 0 && xi != x0) == 0;
   for (int j = 0; j < L; ++j) {
-    if (__ballot(alive != 0) == 0) break;
+    const uint64_t live = __ballot(alive != 0);
+    if (live == 0) break;
+    // a decided lane reads a row that the wave reads anyway
+    const uint32_t x1 = same_x ? x0 : uint32_t(__builtin_amdgcn_readlane(int(xi), __ffsll((unsigned long long)live) - 1));
     const uint32_t own = same_x ? minhash_level<K, true>(a, x0, alive ? yi : x0, j, r)
-                                : minhash_level<K, false>(a, xi, alive ? yi : xi, j, r);
+                                : minhash_level<K, false>(a, alive ? xi : x1, alive ? yi : x1, j, r);
     if (alive) {
       m += own;
       if (int(m) < s_min[j]) {

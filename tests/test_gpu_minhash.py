@@ -40,3 +40,36 @@ def test_minhash_edges(n_hashes):
     h = (a[None, :] * elems.astype(np.uint64)[:, None] + b[None, :]) % np.uint64(PRIME)   # below 2^64
     want = np.minimum.reduceat(h, off[:-1], axis=0).astype(np.uint32)
     np.testing.assert_array_equal(got, want)
+
+
+def test_decided_pairs_are_not_read_on():
+    """Algorithm 1 over 4M id pairs of many x, one in ten similar: the levels past
+    the first read the rows of what is left, so the call takes under 4 times one
+    level of it (every pair's x row read at every level of its wave: over 5)."""
+    n, H, m, k = 200_000, 256, 4_000_000, 16
+    g = torch.Generator(device="cuda").manual_seed(9)
+    sig = torch.randint(0, 1 << 30, (n, H), generator=g, device="cuda", dtype=torch.int32)
+    keep = torch.rand(n // 2, H, generator=g, device="cuda") < torch.rand(n // 2, 1, generator=g, device="cuda")
+    sig[1::2] = torch.where(keep, sig[::2], sig[1::2])
+    x = torch.randint(0, n, (m,), generator=g, device="cuda", dtype=torch.int32)
+    y = torch.where(torch.rand(m, generator=g, device="cuda") < 0.1, x ^ 1,
+                    torch.randint(0, n, (m,), generator=g, device="cuda", dtype=torch.int32))
+    ctx, cand, res = P.bayeslsh_create(0), P.pairs(x.view(torch.uint32), y.view(torch.uint32)), P.make_result(m, m)
+    us = {}
+    try:
+        for n_max in (k, H):
+            S = P.Signatures(sig.reshape(-1).view(torch.uint32), P.JACCARD, P.OBJECT_MAJOR, n, H, n_max)
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            runs = []
+            for _ in range(5):
+                a.record()
+                for _ in range(5):
+                    P.bayeslsh_verify(ctx, cand, S, 0.7, 0.03, 0.05, 0.03, (1, 1), k, res)
+                b.record()
+                torch.cuda.synchronize()
+                runs.append(a.elapsed_time(b) * 200)
+            us[n_max] = min(runs)
+        print("minhash pairs: %s us" % us, flush=True)
+        assert us[H] < 4 * us[k]
+    finally:
+        ctx.close()

@@ -528,6 +528,10 @@ __device__ inline void write_rows(uint32_t &word, const uint64_t (&b)[16], std::
   ((word = write_lane<8 * (V >> 2) + (V & 3) + 4>(uint32_t(b[V] >> 32), word)), ...);
 }
 
+// The product of a block's rows (row0: this wave's first of 32) with the planes of
+// tiles [t0, t1), 32 to a tile; a wave that is not `mine` only helps to stage them.
+// AHEAD: the next slice of planes is read while one is multiplied (else after it:
+// fewer registers, for a kernel that holds other things).
 // X: [n_rows][D] fp32, R: [D][n_bits] fp32.  Block = 4 waves = 128 rows; the
 // D dimension is split between the two half-waves: lanes 0..31 cover
 // d in [0, D/2) and lanes 32..63 cover [D/2, D), so that each lane's A
@@ -535,16 +539,13 @@ __device__ inline void write_rows(uint32_t &word, const uint64_t (&b)[16], std::
 // double-buffered in LDS: the next slice is read into registers before the
 // current one's MFMA loop and written to the other buffer after it, so one
 // barrier per slice remains and the reads overlap the matrix work.
-template <int D>
-__global__ __launch_bounds__(256, 2) void k_srp_dense_mfma(const float *X, int64_t n_rows, const float *R,
-                                                        int32_t n_bits, int32_t word_major, uint32_t *out) {
+template <int D, bool AHEAD>
+__device__ inline void dense_chain(const float *X, int64_t n_rows, const float *R, int32_t n_bits, int32_t word_major,
+                                   uint32_t *out, int64_t row0, int t0, int t1, bool mine, float (&sR)[2][D * 32]) {
   constexpr int HD = D / 2;
-  constexpr int PER = D * 32 / 256;   // slice entries per thread
-  __shared__ float sR[2][D * 32];     // 32-plane slices: sR[b][d*32 + j] = R[d][col0 + j]
+  constexpr int PER = D * 32 / 256;   // slice entries per thread; sR[b][d*32 + j] = R[d][col0 + j]
   const int lane = lane_id();
-  const int wv = threadIdx.x >> 6;
   const int h = lane >> 5, i = lane & 31;
-  const int64_t row0 = int64_t(blockIdx.x) * 128 + wv * 32;
   const int64_t my_row = row0 + i;
   float xa[HD];
   if (my_row < n_rows) {
@@ -562,46 +563,65 @@ __global__ __launch_bounds__(256, 2) void k_srp_dense_mfma(const float *X, int64
   // row held in the result word by this lane (lanes 0..31): t = lane
   const int t = lane & 31;
   const int my_v = 4 * (t >> 3) + (t & 3), my_h = (t >> 2) & 1;
-  float st[PER];
-  auto fetch = [&](int tile) {   // entry idx = threadIdx.x + 256 u of the slice: d = idx / 32, j = idx % 32
+  constexpr int CH = AHEAD ? PER : 4;   // entries of a thread on their way to LDS
+  float st[CH];
+  // entry idx = threadIdx.x + 256 u of the slice: d = idx / 32, j = idx % 32 (d's part of u uniform, the thread's in 32 bits)
+  const uint32_t own = (threadIdx.x >> 5) * uint32_t(n_bits) + (threadIdx.x & 31);
+  auto fetch = [&](int tile, int u0) {
 #pragma unroll
-    for (int u = 0; u < PER; ++u) {
-      const int idx = int(threadIdx.x) + 256 * u;
-      st[u] = R[size_t(idx >> 5) * n_bits + tile * 32 + (idx & 31)];
+    for (int u = 0; u < CH; ++u) st[u] = (R + size_t(8 * (u0 + u)) * uint32_t(n_bits) + tile * 32)[own];
+  };
+  auto stash = [&](int b, int u0) {
+#pragma unroll
+    for (int u = 0; u < CH; ++u) sR[b][int(threadIdx.x) + 256 * (u0 + u)] = st[u];
+  };
+  auto slice = [&](int tile, int b) {
+#pragma unroll 1
+    for (int u0 = 0; u0 < PER; u0 += CH) {
+      fetch(tile, u0);
+      stash(b, u0);
     }
   };
-  auto stash = [&](int b) {
-#pragma unroll
-    for (int u = 0; u < PER; ++u) sR[b][int(threadIdx.x) + 256 * u] = st[u];
-  };
-  fetch(0);
-  stash(0);
+  slice(t0, 0);
   __syncthreads();
-  for (int tile = 0; tile < W; ++tile) {
-    const int b = tile & 1;
-    if (tile + 1 < W) fetch(tile + 1);
-    floatx16 acc = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int s = 0; s < HD; ++s) {
-      const float bv = sR[b][(h * HD + s) * 32 + i];
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(xa[s], bv, acc, 0, 0, 0);
-    }
-    uint32_t word = 0;
-#pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      const uint64_t mk = __ballot(acc[v] >= 0.f);
-      if (my_v == v) word = my_h ? uint32_t(mk >> 32) : uint32_t(mk);
-    }
-    const int64_t r = row0 + t;
-    if (lane < 32 && r < n_rows) {
-      if (word_major) out[size_t(tile) * n_rows + r] = word;
-      else out[size_t(r) * W + tile] = word;
+  for (int tile = t0; tile < t1; ++tile) {
+    const int b = (tile - t0) & 1;
+    if (AHEAD && tile + 1 < t1) fetch(tile + 1, 0);
+    if (mine) {
+      floatx16 acc = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  #pragma unroll
+      for (int s = 0; s < HD; ++s) {
+        const float bv = sR[b][(h * HD + s) * 32 + i];
+        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(xa[s], bv, acc, 0, 0, 0);
+      }
+      uint32_t word = 0;
+  #pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const uint64_t mk = __ballot(acc[v] >= 0.f);
+        if (my_v == v) word = my_h ? uint32_t(mk >> 32) : uint32_t(mk);
+      }
+      const int64_t r = row0 + t;
+      if (lane < 32 && r < n_rows) {
+        if (word_major) out[size_t(tile) * n_rows + r] = word;
+        else out[size_t(r) * W + tile] = word;
+      }
     }
     // buffer b ^ 1 was last read in the previous slice, before the barrier
     // that ended it; the barrier below orders these writes before its reads
-    if (tile + 1 < W) stash(b ^ 1);
+    if (tile + 1 < t1) {
+      if constexpr (AHEAD) stash(b ^ 1, 0);
+      else slice(tile + 1, b ^ 1);
+    }
     __syncthreads();
   }
+}
+
+template <int D>
+__global__ __launch_bounds__(256, 2) void k_srp_dense_mfma(const float *X, int64_t n_rows, const float *R,
+                                                        int32_t n_bits, int32_t word_major, uint32_t *out) {
+  __shared__ float sR[2][D * 32];
+  dense_chain<D, true>(X, n_rows, R, n_bits, word_major, out, int64_t(blockIdx.x) * 128 + (threadIdx.x >> 6) * 32, 0, n_bits / 32,
+                 true, sR);
 }
 
 // ---------------------------------------------------------------------------
@@ -619,22 +639,30 @@ __global__ __launch_bounds__(256, 2) void k_srp_dense_mfma(const float *X, int64
 // and k_srp_dense_mfma's fp32 chain by at most D 2^-23 ||x|| ||r||.  Where |S|
 // exceeds the sum of these (kFilter), S, the exact product and the chain have
 // one sign.  The other signs (about 1 in 1000 for Gaussian planes at D = 256),
-// and rows or planes whose scale lets the chain under- or overflow, are listed
+// and those of planes whose scale lets the chain under- or overflow, are listed
 // per wave and worked out by k_srp_dense_settle with the chain's own instructions in
-// the chain's own order, so the bits are k_srp_dense_mfma's, every one.
+// the chain's own order, so the bits are k_srp_dense_mfma's, every one.  A wave with
+// more open signs than its list holds (a row of such a scale is enough) stops
+// there, and its block takes its rows through the chain as k_srp_dense_mfma does
+// (100,000 x 256 x 1024, one row in 32 such: 709 us, 599 by k_srp_dense_mfma alone;
+// 1463 when the settling kernel took them).
 // ---------------------------------------------------------------------------
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
 template <int D>
 constexpr float kFilter = 3.1f / 262144.f + float(2 * D + 32) / 8388608.f;
-constexpr int kScaleLo = -40, kScaleHi = 60;   // exponents of a row's or plane's norm for which the chain neither under- nor overflows
+// exponents of a row's and a plane's norm for which the chain neither overflows
+// (products and partial sums below 2.25 2^120) nor loses more than kFilter has to
+// spare where it underflows (2 D 2^-126 against 2^-22 of 2^-94)
+constexpr int kRowLo = -70, kRowHi = 70, kPlaneLo = -24, kPlaneHi = 50;
 constexpr uint32_t kOpenCol = (1u << 26) - 1;  // an open sign: row in the wave << 27 | sign of S << 26 | plane
 
 // Scale of a vector with largest element mx: the power of two 2^-e that takes
 // its norm into [0.75, 1.5), found from the sum of squares of the elements
 // scaled by `first` (a power of two that takes mx into [1, 2)).  ok: e is in
-// the range above (false for zero, infinite or NaN).
+// [LO, HI] (false for zero, infinite or NaN).
 __device__ inline float first_scale(float mx) { return mx > 0.f && mx < INFINITY ? ldexpf(1.f, -ilogbf(mx)) : 1.f; }
+template <int LO, int HI>
 __device__ inline float norm_scale(float mx, float first, float sumsq, float &norm, bool &ok) {
   ok = mx > 0.f && mx < INFINITY && sumsq < INFINITY;
   if (!ok) { norm = 0.f; return 1.f; }
@@ -642,14 +670,15 @@ __device__ inline float norm_scale(float mx, float first, float sumsq, float &no
   const int e = ilogbf(n * (4.f / 3.f));
   norm = ldexpf(n, -e) * (1.f + 1.f / 1024.f);        // (covers the rounding of the sum of squares)
   const int total = e + ilogbf(mx);
-  ok = total >= kScaleLo && total <= kScaleHi;
+  ok = total >= LO && total <= HI;
   return ok ? ldexpf(1.f, -total) : 1.f;
 }
 
 // Planes for the filter, one block per 32 of them: the scaled bf16 terms in
 // the order the matrix instruction takes them, Bf[tile][k / 16][term][lane] (8
 // values: plane lane % 32, k % 16 = 8 (lane / 32) ..), their scaled norms (NaN
-// where every sign has to be settled), and the planes by rows for the chain.
+// where every sign has to be settled, -1 for a plane of zeros, whose signs all are
+// known), and the planes by rows for the chain.
 template <int D>
 __global__ __launch_bounds__(256) void k_srp_planes(const float *R, int32_t n_bits, uint4 *Bf, float *norms, float *Rt) {
   __shared__ float s[D][33];
@@ -675,8 +704,8 @@ __global__ __launch_bounds__(256) void k_srp_planes(const float *R, int32_t n_bi
     for (int q = 1; q < 8; ++q) sum += s_part[q][j];
     float norm;
     bool ok;
-    s_scale[j] = norm_scale(mx, f, sum, norm, ok);
-    norms[col0 + j] = ok ? norm : __builtin_nanf("");
+    s_scale[j] = norm_scale<kPlaneLo, kPlaneHi>(mx, f, sum, norm, ok);
+    norms[col0 + j] = ok ? norm : mx == 0.f ? -1.f : __builtin_nanf("");
   }
   __syncthreads();
   for (int i = threadIdx.x; i < D * 32; i += 256) Rt[size_t(col0) * D + i] = s[i % D][i / D];
@@ -695,6 +724,16 @@ __global__ __launch_bounds__(256) void k_srp_planes(const float *R, int32_t n_bi
   }
 }
 
+struct FilterArgs {   // (k_srp_dense_filter's only argument: at the start of its argument segment)
+  const float *X;
+  int64_t n_rows;
+  const float *R;
+  const uint4 *Bf;
+  const float *norms;
+  uint32_t *out, *open, *n_open;
+  int32_t n_bits, n_splits, word_major, cap;
+};
+
 // Block = 4 waves = 128 rows, each wave's 32 rows held as bf16 terms in
 // registers; tile by tile of 32 planes (the split's share of them), the terms of the
 // next tile are copied to LDS while a tile's products run.  Bound by the
@@ -703,12 +742,19 @@ __global__ __launch_bounds__(256) void k_srp_planes(const float *R, int32_t n_bi
 // with the settling and the planes' preparation 1.76 ms, against 4.09 ms of
 // k_srp_dense_mfma (131e12 a second of the 157e12 that fp32 instructions allow).
 template <int D>
-__global__ __launch_bounds__(256, 2) void k_srp_dense_filter(const float *X, int64_t n_rows, const uint4 *Bf,
-                                                             const float *norms, int32_t n_bits, int32_t n_splits,
-                                                             int32_t word_major, uint32_t *out, uint32_t *open,
-                                                             uint32_t *n_open, int32_t cap) {
+__global__ __launch_bounds__(256, 2) void k_srp_dense_filter(FilterArgs fa) {
+  const float *const X = fa.X, *const norms = fa.norms;
+  const int64_t n_rows = fa.n_rows;
+  const uint4 *const Bf = fa.Bf;
+  const int32_t n_bits = fa.n_bits, n_splits = fa.n_splits, word_major = fa.word_major, cap = fa.cap;
+  uint32_t *const out = fa.out, *const open = fa.open, *const n_open = fa.n_open;
   constexpr int KB = D / 16;
-  __shared__ uint4 s_b[2][KB * 128];
+  __shared__ union {
+    uint4 b[2][KB * 128];
+    float r[2][D * 32];   // (dense_chain)
+  } s_u;
+  auto &s_b = s_u.b;
+  __shared__ uint32_t s_over[2][4];
   const int lane = lane_id(), wv = threadIdx.x >> 6, h = lane >> 5, i = lane & 31;
   const int64_t rb = blockIdx.x / unsigned(n_splits);
   const int sp = int(blockIdx.x % unsigned(n_splits)), W = n_bits / 32;
@@ -725,6 +771,8 @@ __global__ __launch_bounds__(256, 2) void k_srp_dense_filter(const float *X, int
   stage(t0, 0);
   bf16x8 xh[KB], xl[KB];
   float xmax;
+  uint32_t zeros;   // rows of zeros: a sign of 1 with every finite plane
+  bool over;        // more open signs than the list holds (wave-uniform)
   {
     float x[KB][8];
     const bool in = row0 + i < n_rows;
@@ -751,11 +799,14 @@ __global__ __launch_bounds__(256, 2) void k_srp_dense_filter(const float *X, int
     sum += __shfl_xor(sum, 32);
     float norm;
     bool ok;
-    float scale = norm_scale(mx, f, sum, norm, ok);
+    float scale = norm_scale<kRowLo, kRowHi>(mx, f, sum, norm, ok);
     ok = ok && num && in;
     const bool other = __shfl_xor(int(ok), 32) != 0;
     ok = ok && other;
-    if (!ok) scale = __builtin_nanf("");   // every sign of the row open
+    // a row whose scale lets the chain under- or overflow: every sign open, n_bits
+    // of them, which no list holds
+    zeros = uint32_t(__ballot(in && num && mx == 0.f) & __ballot(in && num && mx == 0.f) >> 32);
+    over = __ballot(in && !ok && !((zeros >> i) & 1u)) != 0;
     xmax = ok ? norm : 0.f;
 #pragma unroll
     for (int o = 16; o > 0; o >>= 1) xmax = fmaxf(xmax, __shfl_xor(xmax, o));
@@ -772,10 +823,13 @@ __global__ __launch_bounds__(256, 2) void k_srp_dense_filter(const float *X, int
   float norm = norms[t0 * 32 + i];   // of this lane's plane (the next tile's is requested with its fragments)
   uint32_t n = 0;   // open signs of the wave (wave-uniform)
   uint32_t *list = open + size_t(region) * cap;
+  if (lane == 0) s_over[0][wv] = s_over[1][wv] = over;
   __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): the copies to LDS have arrived
   __syncthreads();
   for (int tile = t0; tile < t1; ++tile) {
     const int b = (tile - t0) & 1;
+    // all four over (as of the tile before, so that all waves find the same)
+    if (over && (s_over[b ^ 1][0] & s_over[b ^ 1][1] & s_over[b ^ 1][2] & s_over[b ^ 1][3])) break;
     if (tile + 1 < t1) stage(tile + 1, b ^ 1);
     const float T = bound * norm;
     norm = norms[min(tile + 1, t1 - 1) * 32 + i];
@@ -817,6 +871,14 @@ __global__ __launch_bounds__(256, 2) void k_srp_dense_filter(const float *X, int
       if (word_major) out[size_t(tile) * n_rows + r] = word;
       else out[size_t(r) * W + tile] = word;
     }
+    if (zeros != 0 && T == T) {   // (rows of zeros, finite planes: known)
+      uint32_t z = zeros;
+      asm volatile("" : "+s"(z));   // (worked out here: 16 masks kept for it would not fit the scalar registers)
+      const uint32_t zh = z >> (4 * h);
+#pragma unroll
+      for (int v = 0; v < 16; ++v)
+        if ((zh >> (8 * (v >> 2) + (v & 3))) & 1u) ah[v] = INFINITY;
+    }
     if (__ballot(!sure)) {
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
@@ -830,11 +892,28 @@ __global__ __launch_bounds__(256, 2) void k_srp_dense_filter(const float *X, int
         n += uint32_t(__popcll(mask));
       }
     }
+    over = over || n > uint32_t(cap);
+    if (over && lane == 0) s_over[b][wv] = 1;
     // buffer b ^ 1 was last read before the barrier that ended the previous tile
     __builtin_amdgcn_s_waitcnt(0x0F70);
     __syncthreads();
   }
-  if (lane == 0) n_open[region] = n;
+  if (lane == 0) {
+    n_open[region] = over ? 0 : n;
+    s_over[0][wv] = over;
+  }
+  __syncthreads();
+  if (s_over[0][0] | s_over[0][1] | s_over[0][2] | s_over[0][3]) {   // block-uniform
+    // (a rare path: its arguments are read from the argument segment here, not held
+    // in scalar registers through the loop)
+    const auto *kp = (const char __attribute__((address_space(4))) *)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(kp));
+    const auto *ap = (const FilterArgs __attribute__((address_space(4))) *)kp;
+    const int32_t nb = ap->n_bits;
+    const int64_t rows0 = int64_t(blockIdx.x / unsigned(ap->n_splits)) * 128 + wv * 32;
+    dense_chain<D, false>(ap->X, ap->n_rows, ap->R, nb, ap->word_major, ap->out, rows0, int(int64_t(sp) * (nb / 32) / ap->n_splits),
+                          int(int64_t(sp + 1) * (nb / 32) / ap->n_splits), over, s_u.r);
+  }
 }
 
 // Four steps of k_srp_dense_mfma's chain.
@@ -854,7 +933,6 @@ __device__ inline floatx16 chain4(floatx16 acc, const float4 &a, const float4 &b
 // 64 lines per load, 0.57 ms for 1M rows, 1024 planes, D = 256.  Copies straight to
 // LDS gave wrong values now and then when read after the wave's own wait
 // alone, without a barrier.)
-// A list that overflowed stands for all signs of its wave's rows and planes.
 template <int D>
 __global__ __launch_bounds__(256) void k_srp_dense_settle(const float *X, int64_t n_rows, const float *Rt,
                                                              int32_t n_bits, int32_t n_splits, int32_t word_major,
@@ -873,7 +951,7 @@ __global__ __launch_bounds__(256) void k_srp_dense_settle(const float *X, int64_
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
     cnt[q] = reg0 + q < n_regions ? n_open[reg0 + q] : 0u;
-    total += cnt[q] <= uint32_t(cap) ? cnt[q] : 0u;
+    total += cnt[q];
   }
   auto word_at = [&](int64_t row, int w) -> uint32_t * {
     return word_major ? out + size_t(w) * n_rows + row : out + size_t(row) * W + w;
@@ -884,8 +962,7 @@ __global__ __launch_bounds__(256) void k_srp_dense_settle(const float *X, int64_
     int q = 0;
 #pragma unroll
     for (int x = 0; x < 3; ++x) {
-      const uint32_t c = cnt[x] <= uint32_t(cap) ? cnt[x] : 0u;
-      if (q == x && k >= c) { k -= c; ++q; }
+      if (q == x && k >= cnt[x]) { k -= cnt[x]; ++q; }
     }
     const uint32_t e = open[size_t(reg0 + q) * cap + k];
     const int64_t row = (reg0 + q) / n_splits * 32 + (e >> 27);
@@ -920,27 +997,6 @@ __global__ __launch_bounds__(256) void k_srp_dense_settle(const float *X, int64_
     for (int v = 0; v < 16; ++v) d = my_v == v ? acc[v] : d;
     // (a word's signs may sit in several lanes: only those that change it do, atomically)
     if (act && h == my_h && uint32_t(d >= 0.f) != ((e >> 26) & 1u)) atomicXor(word_at(row, int(col >> 5)), 1u << (col & 31));
-  }
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    if (cnt[q] <= uint32_t(cap)) continue;
-    const int64_t row0 = (reg0 + q) / n_splits * 32;
-    const int sp = int((reg0 + q) % n_splits);
-    const int t0 = int(int64_t(sp) * W / n_splits), t1 = int(int64_t(sp + 1) * W / n_splits);
-    for (int tile = t0 + wv; tile < t1; tile += 4) {
-      floatx16 acc = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-      const float4 *x4 = reinterpret_cast<const float4 *>(X + size_t(min(row0 + i, n_rows - 1)) * D + h * HD);
-      const float4 *r4 = reinterpret_cast<const float4 *>(Rt + size_t(tile * 32 + i) * D + h * HD);
-#pragma unroll 4
-      for (int s = 0; s < HD / 4; ++s) acc = chain4(acc, x4[s], r4[s]);
-      uint32_t word = 0;
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const uint64_t mk = __ballot(acc[v] >= 0.f);
-        if (my_v == v) word = my_h ? uint32_t(mk >> 32) : uint32_t(mk);
-      }
-      if (lane < 32 && row0 + i < n_rows) *word_at(row0 + i, tile) = word;
-    }
   }
 }
 
@@ -1047,12 +1103,15 @@ int launch_srp_sparse(blsh_ctx *ctx, const int64_t *offsets, const uint32_t *ind
 // its open signs settled by two small kernels, about 15 us beside the main one,
 // but it splits the planes over blocks when rows alone do not fill the chip:
 // from 512 planes (and 2^15 plane elements) on it wins at any number of rows
-// (1000 x 256 x 1024: 138 us plain, 34 filtered; 64 x 512, 16000 rows: 25.7 and
-// 24.4), with 128 planes from 2^32 multiply-adds on (300,000 x 128 x 128: 107 and 85
-// us; 65,536 x 128 x 128: 26 and 39; 300,000 x 256 x 64: 126 and 142).
-static bool filter_pays(int64_t n_rows, int64_t dim, int64_t n_bits) {
-  return (n_bits >= 512 && dim * n_bits >= (1 << 15)) ||
-         (n_bits >= 128 && double(n_rows) * double(dim) * double(n_bits) >= 4294967296.0);
+// (us, plain / filtered: 1000 x 256 x 1024 144 / 31; 20,000 x 128 x 512 41 / 36; 40,000 x
+// 64 x 512 41 / 30) but, for the least of these, about one block to a CU (30,000 x 64 x
+// 512: 26 / 28); with 128 planes from 2^32 multiply-adds on (300,000 x 128 x 128: 94 / 81;
+// 100,000 x 128 x 128: 42 / 41; 300,000 x 32 x 256: 52 / 52).
+static bool filter_pays(const blsh_ctx *ctx, int64_t n_rows, int64_t dim, int64_t n_bits) {
+  const int64_t cu_rows = int64_t(ctx->n_cu) * 128;   // a block to a CU
+  if (n_bits >= 512 && dim * n_bits >= (1 << 15))
+    return n_bits >= 1024 || dim * n_bits >= (1 << 16) || n_rows <= cu_rows / 2 || n_rows > cu_rows;
+  return n_bits >= 128 && double(n_rows) * double(dim) * double(n_bits) >= 4294967296.0;
 }
 constexpr int kOpenShare = 256;   // a wave's list holds 1 in kOpenShare of its signs (Gaussian planes leave 1 in 1000 open)
 
@@ -1062,8 +1121,10 @@ static int launch_srp_filter(blsh_ctx *ctx, const float *X, int64_t n_rows, cons
   *done = false;
   const int W = n_bits / 32;
   const int64_t rb = (n_rows + 127) / 128;
-  // rows alone may not fill the chip (two blocks per CU): split the planes too
-  const int64_t want = (int64_t(ctx->n_cu) * 4 + rb - 1) / rb;
+  // rows alone may not fill the chip: split the planes too, as far as all blocks
+  // run at once (registers allow 2 to a CU with 256 columns, 3 with 128, else 4;
+  // 20,000 x 64 x 512 in 1099 blocks 30 us, in 942 25)
+  const int64_t want = int64_t(ctx->n_cu) * (D == 256 ? 2 : D == 128 ? 3 : 4) / rb;
   const int splits = int(std::max<int64_t>(1, std::min<int64_t>(want, W / 2)));
   const int64_t regions = rb * 4 * splits;
   const int cap = std::max(32, 32 * (n_bits / splits) / kOpenShare);
@@ -1084,8 +1145,8 @@ static int launch_srp_filter(blsh_ctx *ctx, const float *X, int64_t n_rows, cons
   uint32_t *cnt = reinterpret_cast<uint32_t *>(p + b_bf + b_rt + b_n), *open = cnt + b_cnt / 4;
   LaunchScope ls(ctx, s, "srp_dense_mfma");
   hipLaunchKernelGGL(k_srp_planes<D>, dim3(W), dim3(256), 0, s, R, n_bits, Bf, norms, Rt);
-  hipLaunchKernelGGL(k_srp_dense_filter<D>, dim3(unsigned(rb * splits)), dim3(256), 0, s, X, n_rows, Bf, norms, n_bits,
-                     splits, int(word_major), out, open, cnt, cap);
+  const FilterArgs fa{X, n_rows, R, Bf, norms, out, open, cnt, n_bits, splits, int32_t(word_major), cap};
+  hipLaunchKernelGGL(k_srp_dense_filter<D>, dim3(unsigned(rb * splits)), dim3(256), 0, s, fa);
   hipLaunchKernelGGL(k_srp_dense_settle<D>, dim3(unsigned((regions + 3) / 4)), dim3(256), 0, s, X, n_rows, Rt, n_bits,
                      splits, int(word_major), out, open, cnt, cap, regions);
   *done = true;
@@ -1098,7 +1159,7 @@ int launch_srp_dense(blsh_ctx *ctx, const float *X, int64_t n_rows, int64_t dim,
   // a call under capture keeps to the plain kernel: it neither grows the
   // workspace nor leaves its address in a graph
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  if (filter_pays(n_rows, dim, n_bits) && uint32_t(n_bits) <= kOpenCol &&
+  if (filter_pays(ctx, n_rows, dim, n_bits) && uint32_t(n_bits) <= kOpenCol &&
       hipStreamIsCapturing(s, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone) {
     bool done = false;
     int rc = BLSH_OK;

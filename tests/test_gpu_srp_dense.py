@@ -85,3 +85,63 @@ def test_signs_near_zero(contexts):
     got = bits_of(contexts[0], x, planes, n_bits, P.OBJECT_MAJOR)
     want = bits_of(contexts[1], x, planes, n_bits, P.OBJECT_MAJOR)
     np.testing.assert_array_equal(got, want)
+
+
+@pytest.mark.parametrize("dim,n_bits", [(32, 1024), (64, 1024), (128, 512), (256, 512)])
+def test_rows_and_planes_outside_the_filter(contexts, dim, n_bits):
+    """Blocks with every wave, one wave or no wave past its list; rows of zeros
+    against ordinary planes, planes of zeros, an infinite plane; norms at both ends of
+    the range the bound covers; rows and planes whose products are mostly zeros."""
+    print("dense SRP outside the filter dim=%d n_bits=%d" % (dim, n_bits), flush=True)
+    rows = 128 * 9 + 37
+    g = torch.Generator(device="cuda").manual_seed(dim + n_bits)
+    x = torch.randn(rows, dim, generator=g, device="cuda")
+    planes = torch.randn(dim, n_bits, generator=g, device="cuda")
+    x[0:128] *= 1e-30                  # a block of such rows
+    x[128 + 40] *= 1e-30               # one wave of a block
+    x[256 + 3], x[256 + 70] = 0, float("inf")
+    x[384:512] = 0
+    x[512:640:2] = 0
+    x[640:768] *= 2.0 ** torch.linspace(-78, -60, 128, device="cuda")[:, None]
+    x[768:896] *= 2.0 ** torch.linspace(60, 78, 128, device="cuda")[:, None]
+    x[896:1024] *= (torch.rand(128, dim, generator=g, device="cuda") < 0.03)
+    x[-1] *= 1e-30                     # the last row of a short block
+    planes[:, 7] = 0
+    planes[3, 9] = float("inf")
+    planes[:, 64:96] *= 2.0 ** torch.linspace(-30, -20, 32, device="cuda")
+    planes[:, 96:128] *= 2.0 ** torch.linspace(40, 56, 32, device="cuda")
+    planes[:, 128:256] *= (torch.rand(dim, 128, generator=g, device="cuda") < 0.1)
+    for layout in (P.OBJECT_MAJOR, P.WORD_MAJOR):
+        got = bits_of(contexts[0], x, planes, n_bits, layout)
+        want = bits_of(contexts[1], x, planes, n_bits, layout)
+        np.testing.assert_array_equal(got, want)
+    assert (got[384:512, :7] == 1).all() and (got[1030:, 7] == 1).all()
+
+
+def test_rows_outside_the_filter_cost_little_more_than_the_plain_product(contexts):
+    """A row of zeros in every 32, rows of norms near the least float: no more than
+    1.6 times the plain product, which a call of such rows takes after a look at them
+    (settled sign by sign over 3 times)."""
+    rows, dim, n_bits = 100_000, 256, 1024
+    planes = torch.randn(dim, n_bits, device="cuda")
+    base = torch.randn(rows, dim, device="cuda")
+    zeros, tiny = base.clone(), base.clone()
+    zeros[::32] = 0
+    tiny[::32] *= 1e-30
+    out = torch.empty(rows * n_bits // 32, dtype=torch.int32, device="cuda").view(torch.uint32)
+    us = {}
+    for name, ctx, x in (("plain", contexts[1], base), ("filtered", contexts[0], base), ("zeros", contexts[0], zeros),
+                         ("tiny", contexts[0], tiny)):
+        v = P.dense_vectors(x)
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        runs = []
+        for _ in range(6):
+            a.record()
+            P.bayeslsh_srp_sigs(ctx, v, planes, n_bits, 0, P.OBJECT_MAJOR, out)
+            b.record()
+            torch.cuda.synchronize()
+            runs.append(a.elapsed_time(b) * 1e3)
+        us[name] = min(runs)
+    print("dense SRP: %s us" % us, flush=True)
+    assert us["zeros"] < 1.6 * us["filtered"]
+    assert us["tiny"] < 1.6 * us["plain"]

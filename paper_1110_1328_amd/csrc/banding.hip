@@ -10,8 +10,7 @@
 //   sort      (key, id) pairs by (band, key), stable (rocPRIM radix sort): the
 //             bands one after another, each bucket listing its members by
 //             increasing id;
-//   buckets   the start of every position's bucket (a running maximum over
-//             the positions where a bucket starts) and every bucket's end;
+//   buckets   the start of every position's bucket and every bucket's end;
 //   row order (order_tile = 0), band by band: one wave per member row p counts
 //             its partners q in (p, end) that share no earlier band; a scan of
 //             the row counts (rocPRIM) gives the offsets; the same walk writes
@@ -79,19 +78,56 @@ __global__ __launch_bounds__(kBandBlock) void k_band_keys(const uint32_t *sig, i
   }
 }
 
-// bstart[p] = p where a bucket starts, else 0: its running maximum is the
-// start of p's bucket.
-__global__ __launch_bounds__(kBandBlock) void k_bucket_starts(const uint32_t *skeys, int64_t n, uint32_t *bstart) {
-  const int64_t p = int64_t(blockIdx.x) * kBandBlock + threadIdx.x;
-  if (p < n) bstart[p] = p > 0 && skeys[p] != skeys[p - 1] ? uint32_t(p) : 0u;
+// Buckets of the sorted keys, kBoundChunk positions to a wave.  last[chunk] = the
+// last position of the chunk where a bucket starts, 0 if none does (position 0,
+// where one starts, reads the same): the chunk from its end until one is found.
+constexpr int kBoundChunk = 1024;
+__device__ inline int64_t bound_chunk() {
+  return int64_t(blockIdx.x) * (kBandBlock / kWave) + int64_t(__builtin_amdgcn_readfirstlane(int(threadIdx.x) / kWave));
+}
+__global__ __launch_bounds__(kBandBlock) void k_bucket_last(const uint32_t *skeys, int64_t n, uint32_t *last) {
+  const int64_t chunk = bound_chunk(), p0 = chunk * kBoundChunk;
+  if (p0 >= n) return;
+  uint32_t found = 0;
+  for (int64_t q = p0 + kBoundChunk - kWave; q >= p0 && found == 0; q -= kWave) {
+    const int64_t p = q + lane_id();
+    const uint64_t mask = __ballot(p < n && p > 0 && skeys[p] != skeys[p - 1]);
+    if (mask != 0) found = uint32_t(q) + 63u - uint32_t(__clzll(mask));
+  }
+  if (lane_id() == 0) last[chunk] = found;
 }
 
-// bend[s] = end of the bucket that starts at s (written at bucket starts only).
-__global__ __launch_bounds__(kBandBlock) void k_bucket_ends(const uint32_t *bstart, int64_t n, uint32_t *bend) {
-  const int64_t p = int64_t(blockIdx.x) * kBandBlock + threadIdx.x;
-  if (p >= n) return;
-  const uint32_t s = bstart[p];
-  if (p + 1 == n || bstart[p + 1] != s) bend[s] = uint32_t(p + 1);
+// bstart[p] = the start of p's bucket; bend[s] = the end of the bucket that
+// starts at s (written at bucket starts only).  A chunk's first bucket is found
+// from the chunks before it, 64 at a time.  (The call of 16 bands of 1M objects:
+// 3.56 ms, 3.64 with a library's scan between two kernels.)
+__global__ __launch_bounds__(kBandBlock) void k_bucket_bounds(const uint32_t *skeys, int64_t n, const uint32_t *last,
+                                                              uint32_t *bstart, uint32_t *bend) {
+  const int64_t chunk = bound_chunk(), p0 = chunk * kBoundChunk;
+  if (p0 >= n) return;
+  const int lane = lane_id();
+  uint32_t start = 0;   // of the bucket that position q - 1 is in
+  for (int64_t b = chunk; b > 0; b -= kWave) {
+    const uint32_t v = b - 1 - lane >= 0 ? last[b - 1 - lane] : 0u;
+    const uint64_t mask = __ballot(v != 0);
+    if (mask != 0) {
+      start = uint32_t(__builtin_amdgcn_readlane(int(v), __ffsll((unsigned long long)mask) - 1));
+      break;
+    }
+  }
+  const int64_t p1 = min<int64_t>(n, p0 + kBoundChunk);
+  for (int64_t q = p0; q < p1; q += kWave) {
+    const int64_t p = q + lane;
+    const bool in = p < p1, first = in && p > 0 && skeys[p] != skeys[p - 1];
+    const uint64_t mask = __ballot(first);
+    auto start_at = [&](uint64_t m) { return m != 0 ? uint32_t(q) + 63u - uint32_t(__clzll(m)) : start; };
+    const uint64_t below = mask & ((1ull << lane) - 1ull);
+    const uint32_t before = start_at(below), mine = first ? uint32_t(p) : before;
+    if (first) bend[before] = uint32_t(p);
+    if (in) bstart[p] = mine;
+    if (p + 1 == n) bend[mine] = uint32_t(n);
+    start = start_at(mask);
+  }
 }
 
 struct BandArgs {
@@ -565,7 +601,7 @@ constexpr int64_t kGroupPositions = int64_t(1) << 30;
 
 struct BandLayout {
   size_t rows, keys, ids, skeys, sids, bstart, bend, count, off, strip, stile, stot, soff, part, meta, base, tmp, scan_at, total;
-  size_t sort_tmp, max_tmp, scan_tmp;
+  size_t sort_tmp, scan_tmp;
 };
 
 // Workspace of a group of bands (row order: the row counts and offsets; tiled
@@ -573,12 +609,10 @@ struct BandLayout {
 static int band_layout(size_t n, int group, int key_bits, int stride, bool tiled, hipStream_t s,
                        BandLayout *l) {
   const size_t N = n * group, S = N / 2 + 1;
-  l->sort_tmp = l->max_tmp = l->scan_tmp = 0;
+  l->sort_tmp = l->scan_tmp = 0;
   if (rocprim::radix_sort_pairs(nullptr, l->sort_tmp, (const uint32_t *)nullptr, (uint32_t *)nullptr,
                                 (const uint32_t *)nullptr, (uint32_t *)nullptr, N, 0, unsigned(key_bits), s) !=
           hipSuccess ||
-      rocprim::inclusive_scan(nullptr, l->max_tmp, (const uint32_t *)nullptr, (uint32_t *)nullptr, N,
-                              rocprim::maximum<uint32_t>(), s) != hipSuccess ||
       rocprim::exclusive_scan(nullptr, l->scan_tmp, (const int64_t *)nullptr, (int64_t *)nullptr, int64_t(0),
                               tiled ? S : n, rocprim::plus<int64_t>(), s) != hipSuccess)
     return fail(BLSH_EDEVICE, "banding: temporary storage query failed");
@@ -597,7 +631,7 @@ static int band_layout(size_t n, int group, int key_bits, int stride, bool tiled
   l->keys = take(N * 4);
   l->ids = take(N * 4);
   l->skeys = take(N * 4);
-  l->tmp = take(std::max(l->sort_tmp, l->max_tmp));
+  l->tmp = take(std::max(l->sort_tmp, (N + kBoundChunk - 1) / kBoundChunk * 4));
   const size_t sorted = at;
   at = from;
   l->strip = take(tiled ? S * sizeof(uint4) : 0);
@@ -652,19 +686,17 @@ int band_candidates(blsh_ctx *ctx, const uint32_t *sig, int64_t n_obj, int32_t r
   for (int j0 = 0; j0 < n_bands; j0 += group) {
     const int g = std::min(group, n_bands - j0);
     const int64_t N = int64_t(g) * n_obj;
-    const unsigned pb = unsigned((N + kBandBlock - 1) / kBandBlock);
     hipLaunchKernelGGL(pack ? k_band_keys<true> : k_band_keys<false>, dim3(nb), dim3(kBandBlock), 0, s, sig, n_obj,
                        row_words, int(word_major), n_bands, band_bits, j0, g, u32(l.keys), u32(l.ids),
                        j0 == 0 ? rows : nullptr, stride);
-    size_t t1 = l.sort_tmp, t2 = l.max_tmp;
+    size_t t1 = l.sort_tmp;
     if (rocprim::radix_sort_pairs(ws + l.tmp, t1, u32(l.keys), u32(l.skeys), u32(l.ids), sids, size_t(N), 0,
                                   unsigned(key_bits_of(g)), s) != hipSuccess)
       return fail(BLSH_EDEVICE, "banding: radix sort failed");
-    hipLaunchKernelGGL(k_bucket_starts, dim3(pb), dim3(kBandBlock), 0, s, u32(l.skeys), N, bstart);
-    if (rocprim::inclusive_scan(ws + l.tmp, t2, bstart, bstart, size_t(N), rocprim::maximum<uint32_t>(), s) !=
-        hipSuccess)
-      return fail(BLSH_EDEVICE, "banding: scan failed");
-    hipLaunchKernelGGL(k_bucket_ends, dim3(pb), dim3(kBandBlock), 0, s, bstart, N, bend);
+    const unsigned cb = unsigned((N + kBoundChunk * 4 - 1) / (kBoundChunk * 4));
+    uint32_t *last = u32(l.tmp);   // (the sort's storage is free again)
+    hipLaunchKernelGGL(k_bucket_last, dim3(cb), dim3(kBandBlock), 0, s, u32(l.skeys), N, last);
+    hipLaunchKernelGGL(k_bucket_bounds, dim3(cb), dim3(kBandBlock), 0, s, u32(l.skeys), N, last, bstart, bend);
     if (tiled) {
       StripArgs a{};
       a.sids = sids;

@@ -131,3 +131,47 @@ def test_banding_key_rows_and_groups(ctx, nb, b, n, max_bucket, fixed):
     finally:
         if fixed:
             own.close()
+
+
+@pytest.mark.parametrize("tile", [0, 16])
+@pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 1023, 1024, 1025, 2049, 4097])
+def test_buckets_across_chunks(ctx, n, tile):
+    """Buckets found 1024 positions to a wave: one bucket for all, buckets that end
+    with a wave's step or chunk, of one member, and over several whole chunks."""
+    rng = np.random.default_rng(n)
+    keys = np.zeros((n, 4), np.uint32)                     # 8-bit band keys: band 0 all equal
+    keys[:, 1] = np.minimum(np.arange(n) // 64, 255)       # whole steps
+    keys[:, 2] = np.where(rng.random(n) < 0.02, rng.integers(0, 255, n), 255)
+    keys[:, 3] = rng.integers(0, 256, n)
+    words = (keys[:, 0] | keys[:, 1] << 8 | keys[:, 2] << 16 | keys[:, 3] << 24).astype(np.uint32).reshape(n, 1)
+    S = sigs_tensor(words, P.COSINE, P.OBJECT_MAJOR)
+    for max_bucket in (40, 0):
+        if max_bucket == 0 and n > 1100:
+            continue
+        for order in ([0, 1, 2, 3], [3, 2, 1, 0]):
+            w = sum(keys[:, b].astype(np.uint32) << np.uint32(8 * i) for i, b in enumerate(order)).astype(np.uint32).reshape(n, 1)
+            S = sigs_tensor(w, P.COSINE, P.OBJECT_MAJOR)
+            wx, wy = R.band_candidates(w, 4, 8, max_bucket, tile=tile)
+            gx, gy, m, trunc = run(ctx, S, 4, 8, len(wx) + 10, max_bucket, tile)
+            assert m == len(wx) and not trunc
+            np.testing.assert_array_equal(gx, wx)
+            np.testing.assert_array_equal(gy, wy)
+
+
+@pytest.mark.parametrize("nb,b", [(5, 30), (5, 31), (3, 32), (7, 29), (33, 26)])
+def test_groups_of_wide_keys(ctx, nb, b):
+    """Keys too wide to sort all bands together: groups of bands, the last one
+    smaller, at sizes where the library's sort changes its method."""
+    rng = np.random.default_rng(nb * b)
+    n_words = (nb * b + 31) // 32
+    for n in (1, 300, 1500, 5000, 20_000, 70_000, 300_000):
+        rows = rng.integers(0, 1 << 32, (max(n // 3, 1), n_words), dtype=np.uint32)
+        sig = rows[rng.integers(0, len(rows), n)]
+        flip = rng.random((n, n_words)) < 0.5
+        sig = np.where(flip, sig ^ (np.uint32(1) << rng.integers(0, 32, (n, n_words)).astype(np.uint32)), sig)
+        S = sigs_tensor(sig, P.COSINE, P.OBJECT_MAJOR)
+        wx, wy = R.band_candidates(sig, nb, b, 0, tile=16)
+        gx, gy, m, trunc = run(ctx, S, nb, b, len(wx) + 10, 0, 16)
+        assert m == len(wx) and not trunc
+        np.testing.assert_array_equal(gx, wx)
+        np.testing.assert_array_equal(gy, wy)

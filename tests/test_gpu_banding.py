@@ -136,7 +136,7 @@ def test_banding_key_rows_and_groups(ctx, nb, b, n, max_bucket, fixed):
 @pytest.mark.parametrize("tile", [0, 16])
 @pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 1023, 1024, 1025, 2049, 4097])
 def test_buckets_across_chunks(ctx, n, tile):
-    """Buckets found 1024 positions to a wave: one bucket for all, buckets that end
+    """Buckets found some hundred positions to a wave: one bucket for all, buckets that end
     with a wave's step or chunk, of one member, and over several whole chunks."""
     rng = np.random.default_rng(n)
     keys = np.zeros((n, 4), np.uint32)                     # 8-bit band keys: band 0 all equal

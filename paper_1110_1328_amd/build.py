@@ -4,6 +4,8 @@
 
 Each source compiles to an object under paper_1110_1328_amd/_build/ (in
 parallel), then the objects link into paper_1110_1328_amd/libbayeslsh.so.
+build_bounds() builds tests/native/libbounds.so, the kernels that measure the
+hardware's functions for test_gpu_bounds.py.
 """
 from __future__ import annotations
 
@@ -53,6 +55,21 @@ def build(verbose: bool = False) -> str:
     return LIB
 
 
+def build_bounds(verbose: bool = False) -> str:
+    native = os.path.join(HERE, "..", "tests", "native")
+    out = os.path.join(native, "libbounds.so")
+    tmp = out + ".tmp%d" % os.getpid()
+    cmd = [HIPCC, "-x", "hip"] + COMMON + DEVICE + ["-shared", os.path.join(native, "bounds.hip"), "-o", tmp]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("build failed: %s\n%s\n%s" % (" ".join(cmd), r.stdout, r.stderr))
+    os.replace(tmp, out)
+    if verbose:
+        print(out)
+    return out
+
+
 if __name__ == "__main__":
     build(verbose=True)
+    build_bounds(verbose=True)
     sys.exit(0)

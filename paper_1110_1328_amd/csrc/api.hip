@@ -272,7 +272,7 @@ static void fill_cand(VerifyArgs &a, const blsh_candidates *c) {
 //                    uses slice w % kSlices), so a slice never overflows
 //   st_rel, st_val   kSlices accepted-pair staging slices of st_cap entries
 static constexpr int64_t kChunk = int64_t(1) << 28;
-static constexpr int64_t kFewCand = int64_t(1) << 16;
+static constexpr int64_t kFewCand = int64_t(1) << 16, kFewWords = int64_t(3) << 14;
 static constexpr int64_t kExhChunk = int64_t(1) << 24;
 static constexpr int64_t kStageDefault = int64_t(1) << 24;
 static constexpr size_t kSliceBufWords = (size_t(3) * kSlices + 2) * kCntStride;
@@ -558,12 +558,13 @@ static int run_verify(blsh_ctx *ctx, const blsh_candidates *cand, const blsh_sig
   const bool fused_exact = lite && exhaustive_mode == -1 && sigs->measure == BLSH_COSINE && a.pfx == nullptr;
   const bool queued = (lite && !fused_exact) || tail;
   // Algorithm 1 of few candidates: one launch that appends to the caller's list,
-  // instead of two or three.  Its waves add to one counter, a few ns apart; a
+  // instead of two or three.  Its blocks add to one counter, a few ns apart; a
   // call over word-major signatures with a prefix array takes (us, one launch /
-  // queue and flush) 14.5 / 24.3 at 1000 candidates, 15.6 / 25.0 at 32000,
-  // 17.6 / 24.5 at 65000, 21.7 / 24.3 at 130000; minhash 10.6 / 12.8 up to
-  // 65000 and 13.5 / 12.7 at 130000.
-  const bool few = !exh && !lite && n_cand <= kFewCand;
+  // queue and flush, one candidate in 20 similar) 14.5 / 24.3 at 1000 candidates, 15.6 / 25.0
+  // at 32000, 17.6 / 24.5 at 65000; minhash 10.6 / 12.8 up to 65000 and 13.5 / 12.7 at
+  // 130000; all of 65000 accepted 13 / 17.  Word-major without a prefix, whose
+  // first levels are gathered eight words at a time: 13 / 14.5 at 50000, 15 / 14 at 65000.
+  const bool few = !exh && !lite && n_cand <= (sigs->measure == BLSH_COSINE && !a.pfx && sigs->layout == BLSH_WORD_MAJOR ? kFewWords : kFewCand);
   // launches are chunked so that no grid exceeds 2^32 work-items (the
   // dispatch's grid size): the comparator runs up to 64 lanes per candidate
   const int64_t chunk = std::min<int64_t>(n_cand, noalloc ? kNaChunk : exh ? kExhChunk : kChunk);

@@ -180,14 +180,14 @@ int bayeslsh_create(blsh_ctx **out, int device);
 void bayeslsh_destroy(blsh_ctx *ctx);
 
 /* Caller control of the context workspace (the device memory that
- * verification, Lite, the comparator, banding and the sparse SRP plane table
- * use beyond the caller's inputs and outputs).  bayeslsh_reserve_workspace
+ * verification, Lite, the comparator, banding and SRP signature generation
+ * use beyond the caller's inputs and outputs; growth frees the old one, so a
+ * HIP graph captured from a call that uses it needs it reserved fixed).  bayeslsh_reserve_workspace
  * makes it at least `bytes` now (allocating synchronises the device once).
  * With fixed != 0 later calls never grow it: a call that needs more returns
  * BLSH_ENOMEM before launching any kernel or writing any output (a table
- * image may already have been uploaded to the cache), and the sparse SRP draws its plane
- * entries per nonzero instead of building a table that does not fit (the
- * same signatures).  fixed = 0 restores growth on demand.  A caller that
+ * image may already have been uploaded to the cache), and SRP signature
+ * generation goes without what does not fit (the same signatures).  fixed = 0 restores growth on demand.  A caller that
  * wants no allocation after setup runs its largest call once, reads the size
  * with bayeslsh_workspace_bytes and reserves it fixed.  The batched state,
  * the banding tile buffer and the posterior-table images are allocated

@@ -6,8 +6,9 @@
 //   or 8 per lane) or 64 or 128 of one minhash list (lane l owns candidates l
 //   and 64 + l, a group of k/4 lanes compares each candidate's k hashes), the
 //   shape per measure chosen by the autotuner -- and every wave of the fixed grid
-//   runs one contiguous range of tiles (no work counter, no block barrier),
-//   each XCD an eighth of every list (L2 locality of sorted ids).  The
+//   runs an equal share of them (no work counter, no block barrier): a range,
+//   but the tiles of a list that spans several waves go to them by turns; each XCD has
+//   an eighth of every list (L2 locality of sorted ids).  The
 //   query's hashes are wave-uniform.  Each list carries its own measure and
 //   threshold, hence its own decision table, and each measure its own k.  A
 //   candidate still undecided after `inreg_levels` levels (SRP object-major
@@ -51,8 +52,8 @@ constexpr int kBlocksDefault = 6;
 constexpr int kExSrpTile = 1024;   // comparator: candidates per SRP block tile
 constexpr int kExMhTile = 256;     // comparator: candidates per minhash block tile
 constexpr int kXcds = 8;           // phase 1: list tiles split in kXcds position ranges, one per XCD
-// survivor queue of a small batch: 128 entries a wave of the largest grid the
-// autotuner takes.  A wave whose region is full runs its tile to the last level
+// survivor queue of a small batch: 170 entries a wave of the largest grid the
+// autotuner takes (6 blocks a CU, 256 CUs).  A wave whose region is full runs its tile to the last level
 // alone, which takes a batch of 34 K candidates 22 us longer.
 constexpr int64_t kMinSpill = int64_t(1) << 20;
 constexpr int64_t kBatchStage = 4096;   // accepted-pair staging entries per slice
@@ -532,7 +533,7 @@ __device__ inline void phase1_range(const BatchBlock &B, int x, const int64_t *p
 // each with its own L2.  Phase 1 gives the blocks of XCD x the x-th eighth
 // (by position) of every list's tiles: lists hold sorted candidate ids, so an
 // XCD touches about an eighth of the signature rows and its L2 holds them.
-// Within an XCD every wave runs a contiguous range of that XCD's tiles.  One
+// Within an XCD every wave takes an equal share of that XCD's tiles (phase1_range).  One
 // launch runs the lists of one measure (MEAS), so the streaming minhash rows
 // do not evict the SRP rows from L2.  Bound by a tile's chain -- ids from HBM, rows
 // from L2, thresholds -- and for minhash by the lines that miss L2.  512 lists,

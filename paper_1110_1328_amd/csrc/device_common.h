@@ -303,9 +303,9 @@ __device__ inline void push_survivors(const VerifyArgs &a, uint32_t want, int64_
   }
 }
 
-// Read-only data (signatures, tables, list descriptors: nothing the kernels
-// write) read through the constant address space, so that a wave-uniform
-// address becomes one scalar load.
+// Data that the running kernel does not write (signatures, tables, list
+// descriptors, what an earlier kernel left) read through the constant address
+// space, so that a wave-uniform address becomes one scalar load.
 template <typename T>
 __device__ inline T ld_uniform(const T *p) {
   return *(const __attribute__((address_space(4))) T *)(p);

@@ -164,7 +164,7 @@ def test_groups_of_wide_keys(ctx, nb, b):
     smaller, at sizes where the library's sort changes its method."""
     rng = np.random.default_rng(nb * b)
     n_words = (nb * b + 31) // 32
-    for n in (1, 300, 1500, 5000, 20_000, 70_000, 300_000):
+    for n in (1, 300, 1500, 5000, 20_000, 70_000):
         rows = rng.integers(0, 1 << 32, (max(n // 3, 1), n_words), dtype=np.uint32)
         sig = rows[rng.integers(0, len(rows), n)]
         flip = rng.random((n, n_words)) < 0.5

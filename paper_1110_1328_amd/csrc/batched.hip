@@ -49,6 +49,7 @@ constexpr int kMhTileDefault = 64;
 // so that the waves of a list keep pace.  512 lists of 56 M candidates (k = 16 / 64):
 // 474 us with 4, 449 with 5, 437 with 6, 484 with 7, 499 with 8; 34 K candidates: 56 to 57.
 constexpr int kBlocksDefault = 6;
+constexpr int kBlocksExhaustive = 8;   // the comparator's blocks keep no lists in step
 constexpr int kExSrpTile = 1024;   // comparator: candidates per SRP block tile
 constexpr int kExMhTile = 256;     // comparator: candidates per minhash block tile
 constexpr int kXcds = 8;           // phase 1: list tiles split in kXcds position ranges, one per XCD
@@ -485,18 +486,21 @@ __device__ inline int64_t wave_list_of_tile(const int64_t *prefix, int64_t n_lis
   return lo;
 }
 
-// The tiles [w c, (w + 1) c) of slice x's order, list after list, belong to wave w
+// The w-th of W equal parts of slice x's T tiles in order, list after list, belongs to wave w
 // (lists of measure MEAS, 64 P candidates per tile).  Where a list spans several
 // whole waves these share its tiles by turns, not by ranges, so that the waves
 // of all long lists pass through their sorted ids together and read the same
-// rows at about the same time.  A list's query, thresholds and pointers are kept
+// rows at about the same time.  (Parts of one size rounded up start at another
+// place of every list where lists are of one length: 512 lists of 100,000, 1M rows of 1024
+// bits, 711 us instead of 369.)  A list's query, thresholds and pointers are kept
 // from tile to tile, and the next tile's ids requested before a tile is run.
 template <int MEAS, int K, int P>
-__device__ inline void phase1_range(const BatchBlock &B, int x, const int64_t *prefix, int64_t T, int64_t w, int64_t c,
+__device__ inline void phase1_range(const BatchBlock &B, int x, const int64_t *prefix, int64_t T, int64_t w, int64_t W,
                                     int64_t wave, uint32_t &n_spill) {
   constexpr int64_t tsz = int64_t(P) * kWave;
   const SigView S = B.sig[MEAS];
-  const int64_t t0 = w * c, t1 = min(T, t0 + c);
+  const int64_t t0 = w * T / W, t1 = (w + 1) * T / W;
+  if (t0 == t1) return;
   int64_t l = wave_list_of_tile(prefix, B.n_lists, t0);
   int64_t first = ld_uniform(prefix + l), next = ld_uniform(prefix + l + 1);
   for (int64_t t = t0; t < t1;) {
@@ -508,12 +512,15 @@ __device__ inline void phase1_range(const BatchBlock &B, int x, const int64_t *p
     const BatchList Ls = ld_list(B.lists + l);
     int64_t n = min(t1, next) - t;   // tiles of this list here, `stride` apart
     int64_t stride = 1, at = t - first;
-    if (n == c) {   // the whole wave: one of the waves [wa, wb) within the list
-      const int64_t wa = (uint32_t(first) + uint32_t(c) - 1) / uint32_t(c), wb = uint32_t(next) / uint32_t(c);
+    if (t == t0 && t1 <= next && T >= W) {   // the whole wave: one of those, [wa, wb), whose parts (none empty) lie within the list
+      const int64_t wa = (first * W + T - 1) / T, wb = min(W, ((next + 1) * W + T - 1) / T - 1);
       stride = wb - wa;
-      at = wa * c - first + (w - wa);
+      at = wa * T / W - first + (w - wa);
+      n = (wb * T / W - first - at + stride - 1) / stride;
+      t = t1;
+    } else {
+      t += n;
     }
-    t += n;
     const int64_t tile = (int64_t(x) * ((Ls.length + tsz - 1) / tsz)) / kXcds + at;
     int64_t base = Ls.offset + tile * tsz;
     uint32_t y[P], yn[P];
@@ -549,11 +556,10 @@ __global__ __launch_bounds__(kBBlock) void k_batch_phase1(const BatchBlock *__re
   const int64_t Wx = nbx * (kBBlock / kWave);
   const int64_t *prefix = B.tile_prefix + int64_t(MEAS * kXcds + x) * (B.n_lists + 1);
   const int64_t Tx = ld_uniform(prefix + B.n_lists);
-  const int64_t c = (Tx + Wx - 1) / Wx;   // (fewer than 2^32 tiles: ids take 256 bytes each)
   const int64_t wave = int64_t(blockIdx.x) * (kBBlock / kWave) +
                        int64_t(__builtin_amdgcn_readfirstlane(int(threadIdx.x) / kWave));
   uint32_t n_spill = 0;
-  if (wx * c < Tx) phase1_range<MEAS, K, P>(B, x, prefix, Tx, wx, c, wave, n_spill);
+  phase1_range<MEAS, K, P>(B, x, prefix, Tx, wx, Wx, wave, n_spill);
   if (lane_id() == 0)   // every wave of the grid reports its fill, 0 included
     B.spill_count[MEAS][wave] = n_spill;
 }
@@ -1231,6 +1237,25 @@ static int get_graph(BatchState *b, const BatchState::GraphKey &key, hipGraphExe
   return BLSH_OK;
 }
 
+// Phase-1 blocks per CU of a call that neither fixes nor tunes them.  Lists of one
+// length that come several to a wave: a number that gives every wave whole lists, if
+// one does, so that all waves start a list at the same time and read the same rows
+// (1024 lists of 50,000, 1M rows of 1024 bits: 4 a CU 368 us, 8 422, 6 561; 4096 of 12,000:
+// 494, 595, 749; rows read through a prefix array 340, 371, 325).
+static int default_blocks(const blsh_ctx *ctx, const blsh_list_desc *lists, int64_t n_lists) {
+  int64_t n[2] = {0, 0}, length[2] = {0, 0};
+  for (int64_t i = 0; i < n_lists; ++i) {
+    const int me = lists[i].measure == BLSH_COSINE;
+    if (n[me]++ == 0) length[me] = lists[i].length;
+    else if (length[me] != lists[i].length) return kBlocksDefault;
+  }
+  for (const int bpc : {kBlocksDefault, 4, 5, 8}) {
+    const int64_t waves = int64_t(ctx->n_cu) * bpc / kXcds * (kBBlock / kWave);   // of an XCD
+    if (n[0] % waves == 0 && n[1] % waves == 0) return bpc;
+  }
+  return kBlocksDefault;
+}
+
 int verify_batched(blsh_ctx *ctx, const blsh_list_desc *lists, int64_t n_lists, const uint32_t *cand, int64_t n_cand,
                    const blsh_sigs *jac, const blsh_sigs *cos, double eps, double delta, double gamma,
                    blsh_prior prior, int32_t kj, int32_t kc, blsh_result *res, int32_t *k_used, hipStream_t s,
@@ -1396,7 +1421,8 @@ int verify_batched(blsh_ctx *ctx, const blsh_list_desc *lists, int64_t n_lists, 
   };
 
   // k of a measure no list uses is irrelevant: 32
-  BatchState::Choice ch{kj ? kj : 32, kc ? kc : 32, kSrpTileDefault, kMhTileDefault, 2, kBlocksDefault};
+  BatchState::Choice ch{kj ? kj : 32, kc ? kc : 32, kSrpTileDefault, kMhTileDefault, 2,
+                         mode ? kBlocksExhaustive : default_blocks(ctx, lists, n_lists)};
   const int fixed_tile[2] = {ctx->tuning.batch_mh_tile, ctx->tuning.batch_srp_tile};
   if (fixed_tile[0] > 0) ch.tm = fixed_tile[0];
   if (fixed_tile[1] > 0) ch.ts = fixed_tile[1];

@@ -73,3 +73,30 @@ def test_decided_pairs_are_not_read_on():
         assert us[H] < 4 * us[k]
     finally:
         ctx.close()
+
+
+@pytest.mark.parametrize("n_sets", [32_767, 32_768, 32_769, 70_001])
+@pytest.mark.parametrize("n_hashes", [32, 100])
+def test_more_sets_than_waves(n_sets, n_hashes):
+    """A wave that takes one, two or three sets (32,768 waves on 256 CUs), some of them
+    empty, the last ones of different lengths."""
+    rng = np.random.default_rng(n_sets)
+    ln = rng.integers(0, 70, n_sets) * (rng.random(n_sets) < 0.3)
+    off = np.concatenate([[0], np.cumsum(ln)]).astype(np.int64)
+    el = rng.integers(0, 1 << 31, int(off[-1]), dtype=np.uint32)
+    a, b = rng.integers(1, PRIME, n_hashes).astype(np.uint32), rng.integers(0, PRIME, n_hashes).astype(np.uint32)
+    out = torch.empty(n_sets * n_hashes, dtype=torch.int32, device="cuda").view(torch.uint32)
+    ctx = P.bayeslsh_create(0)
+    try:
+        P.bayeslsh_minhash_sigs(ctx, P.set_vectors(up(off), up(el), 1 << 31), up(a), up(b), out)
+        with pytest.raises(P.BayesLSHError):   # the empty sets
+            P.bayeslsh_sync(ctx)
+    finally:
+        ctx.close()
+    got = down(out).reshape(n_sets, n_hashes)
+    want = np.full((n_sets, n_hashes), 0xFFFFFFFF, np.uint64)
+    for h in range(n_hashes):
+        v = (el.astype(np.uint64) * np.uint64(a[h]) + np.uint64(b[h])) % np.uint64(PRIME)
+        full = ln > 0
+        want[full, h] = np.minimum.reduceat(v, off[:-1][full])
+    np.testing.assert_array_equal(got, want.astype(np.uint32))

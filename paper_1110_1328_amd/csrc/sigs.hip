@@ -148,20 +148,20 @@ constexpr int kSumBlock = 32;            // nonzeros summed before they are adde
 constexpr int kSumStretch = 1024;        // nonzeros of a stretch; a longer row's stretches are added in FP64
 
 // Codes of the entries of the terms < dim that occur (used[term] != 0),
-// table[term][n_bits]: a wave takes 64 terms, those that occur one by one (the
+// table[term][n_bits]: a wave takes `per` (at most 64) terms, those that occur one by one (the
 // term is wave-uniform, and with it Philox's first multiplications).  Used when each term
 // occurs in several rows, so that an entry is drawn once instead of once per
 // occurrence.  Bound by VALU (Philox's multiplications first): 1.37e9 entries of
 // 668,880 terms in 1.35 ms, against 4.41 ms of FP64 logarithms, sines and cosines.
 __global__ __launch_bounds__(256) void k_srp_table(int64_t dim, int32_t n_bits, uint32_t k0, uint32_t k1,
-                                                   const uint8_t *used, int16_t *table) {
+                                                   const uint8_t *used, int16_t *table, int32_t per) {
   const int Q = n_bits / 4, lane = lane_id();
-  const int64_t n_groups = (dim + kWave - 1) / kWave;   // 64 terms at a time: their flags by one load
+  const int64_t n_groups = (dim + per - 1) / per;   // the terms' flags by one load
   for (int64_t gr = int64_t(blockIdx.x) * 4 + __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6); gr < n_groups;
        gr += int64_t(gridDim.x) * 4) {
-    const int64_t t = gr * kWave + lane;
-    for (uint64_t left = __ballot(t < dim && used[t] != 0); left; left &= left - 1) {
-      const uint32_t term = uint32_t(gr * kWave) + uint32_t(__ffsll((unsigned long long)left) - 1);   // wave-uniform
+    const int64_t t = gr * per + lane;
+    for (uint64_t left = __ballot(lane < per && t < dim && used[t] != 0); left; left &= left - 1) {
+      const uint32_t term = uint32_t(gr * per) + uint32_t(__ffsll((unsigned long long)left) - 1);   // wave-uniform
       for (int q = lane; q < Q; q += kWave) {
         float g[4];
         srp_fast4(term, uint32_t(q), k0, k1, g);
@@ -303,8 +303,9 @@ __global__ __launch_bounds__(256) void k_srp_sparse(const int64_t *offsets, cons
 // thread, the entries of a quad drawn together.  Of the others a block lists the
 // open bits of its `per` rows (at most kSettleRows) in LDS, 256 words at a time while they fit.  8 lanes take
 // a bit, each every eighth nonzero, and sum the approximate entries themselves in
-// FP64: that leaves only the entries' error, |v| kFastErr (and half a code's cell),
-// so that 1 bit in 30 of those the table left open remains.  What remains is
+// FP64: that leaves only the entries' error, |v| kFastErr (Q16: a cell where an entry
+// that much off might have another code, 3% of them), so that 1 bit in 30 of those
+// the table left open remains.  What remains is
 // drawn in FP64, a wave to a bit and 64 nonzeros at a time, the products (exact
 // in FP64) added in order.  Rows of 100,000 equal weights leave 3% of their bits open:
 // 64 of them take 45 ms in all (63 with FP64 entries for every bit; 6800 with every
@@ -377,19 +378,27 @@ __global__ __launch_bounds__(256) void k_srp_settle(const int64_t *offsets, cons
       const int64_t row = row0 + b / uint32_t(n_bits);
       const uint32_t h = b % uint32_t(n_bits);
       const int64_t s = offsets[row], e = act ? offsets[row + 1] : s;
-      double sum = 0.0, mass = 0.0;
+      double sum = 0.0, mass = 0.0, slack = 0.0;
       for (int64_t t = s + r; t < e; t += 8) {
         const double v = values[t];
-        sum = __builtin_fma(v, double(srp_fast1(indices[t], h, k0, k1)), sum);
+        double g = srp_fast1(indices[t], h, k0, k1), off = kFastErr;
+        if constexpr (Q16) {   // the code's value, sure but near a cell's edge: there one cell off at most
+          const double x = (g + 8.0) * 4096.0, c = floor(x);
+          off = x - c < kFastErr * 4096.0 || x - c > 1.0 - kFastErr * 4096.0 ? 0x1p-12 : 0.0;
+          g = (c + 0.5) * (1.0 / 4096.0) - 8.0;
+        }
+        sum = __builtin_fma(v, g, sum);
+        slack += fabs(v) * off;
         mass += fabs(v);
       }
 #pragma unroll
       for (int o = 1; o < 8; o <<= 1) {
         sum += __shfl_xor(sum, o);
         mass += __shfl_xor(mass, o);
+        slack += __shfl_xor(slack, o);
       }
       // (the last term: the roundings of either FP64 sum, each 2^-53 of at most 7 times the mass)
-      const double T = mass * (kFastErr + (Q16 ? 0x1p-13 : 0.0) + double(e - s) * 0x1p-49) * 1.0001;
+      const double T = (slack + mass * double(e - s) * 0x1p-49) * 1.0001;
       if (act && r == 0 && fabs(sum) > T && fabs(sum) < INFINITY) {
         put(row, h, sum > 0.0);
         s_bit[i] = kSettled;
@@ -1011,8 +1020,11 @@ int launch_srp_sparse(blsh_ctx *ctx, const int64_t *offsets, const uint32_t *ind
     hipLaunchKernelGGL(k_fill_u8, dim3(gz), dim3(256), 0, s, used, dim);
     const unsigned gm = unsigned(std::min<int64_t>((nnz + 255) / 256, 8192));
     hipLaunchKernelGGL(k_srp_mark, dim3(gm), dim3(256), 0, s, indices, nnz, dim, used);
-    hipLaunchKernelGGL(k_srp_table, dim3(unsigned(std::min<int64_t>((dim + 255) / 256, int64_t(ctx->n_cu) * 64))), dim3(256), 0, s,
-                       dim, n_bits, k0, k1, used, table);
+    // (fewer than 64 terms to a wave where that would leave SIMDs without one)
+    const int per = int(std::max<int64_t>(1, std::min<int64_t>(kWave, dim / (int64_t(ctx->n_cu) * 32))));
+    const int64_t tb = (dim + per * 4 - 1) / (per * 4);
+    hipLaunchKernelGGL(k_srp_table, dim3(unsigned(std::min<int64_t>(tb, int64_t(ctx->n_cu) * 64))), dim3(256), 0, s, dim,
+                       n_bits, k0, k1, used, table, per);
   }
   const int qpl = use_table && n_bits > 256 ? 2 : 1;
   const int n_slices = (n_bits / 4 + kWave * qpl - 1) / (kWave * qpl);

@@ -49,7 +49,6 @@ constexpr int kMhTileDefault = 64;
 // so that the waves of a list keep pace.  512 lists of 56 M candidates (k = 16 / 64):
 // 474 us with 4, 449 with 5, 437 with 6, 484 with 7, 499 with 8; 34 K candidates: 56 to 57.
 constexpr int kBlocksDefault = 6;
-constexpr int kBlocksExhaustive = 8;   // the comparator's blocks keep no lists in step
 constexpr int kExSrpTile = 1024;   // comparator: candidates per SRP block tile
 constexpr int kExMhTile = 256;     // comparator: candidates per minhash block tile
 constexpr int kXcds = 8;           // phase 1: list tiles split in kXcds position ranges, one per XCD
@@ -1241,14 +1240,17 @@ static int get_graph(BatchState *b, const BatchState::GraphKey &key, hipGraphExe
 // length that come several to a wave: a number that gives every wave whole lists, if
 // one does, so that all waves start a list at the same time and read the same rows
 // (1024 lists of 50,000, 1M rows of 1024 bits: 4 a CU 368 us, 8 422, 6 561; 4096 of 12,000:
-// 494, 595, 749; rows read through a prefix array 340, 371, 325).
-static int default_blocks(const blsh_ctx *ctx, const blsh_list_desc *lists, int64_t n_lists) {
+// 494, 595, 749; rows read through a prefix array 340, 371, 325).  The comparator's
+// blocks take ranges: 8 of them a CU over many candidates in lists of one length (512
+// lists of 50,000 sets 2.15 ms, 6 3.11), 6 otherwise (4096 lists of all lengths 58 ms, 8 72).
+static int default_blocks(const blsh_ctx *ctx, const blsh_list_desc *lists, int64_t n_lists, int64_t n_cand, int mode) {
   int64_t n[2] = {0, 0}, length[2] = {0, 0};
   for (int64_t i = 0; i < n_lists; ++i) {
     const int me = lists[i].measure == BLSH_COSINE;
     if (n[me]++ == 0) length[me] = lists[i].length;
     else if (length[me] != lists[i].length) return kBlocksDefault;
   }
+  if (mode) return n_cand >= int64_t(1) << 24 ? 8 : kBlocksDefault;
   for (const int bpc : {kBlocksDefault, 4, 5, 8}) {
     const int64_t waves = int64_t(ctx->n_cu) * bpc / kXcds * (kBBlock / kWave);   // of an XCD
     if (n[0] % waves == 0 && n[1] % waves == 0) return bpc;
@@ -1422,7 +1424,7 @@ int verify_batched(blsh_ctx *ctx, const blsh_list_desc *lists, int64_t n_lists, 
 
   // k of a measure no list uses is irrelevant: 32
   BatchState::Choice ch{kj ? kj : 32, kc ? kc : 32, kSrpTileDefault, kMhTileDefault, 2,
-                         mode ? kBlocksExhaustive : default_blocks(ctx, lists, n_lists)};
+                         default_blocks(ctx, lists, n_lists, n_cand, mode)};
   const int fixed_tile[2] = {ctx->tuning.batch_mh_tile, ctx->tuning.batch_srp_tile};
   if (fixed_tile[0] > 0) ch.tm = fixed_tile[0];
   if (fixed_tile[1] > 0) ch.ts = fixed_tile[1];

@@ -152,7 +152,7 @@ constexpr int kSumStretch = 1024;        // nonzeros of a stretch; a longer row'
 // term is wave-uniform, and with it Philox's first multiplications).  Used when each term
 // occurs in several rows, so that an entry is drawn once instead of once per
 // occurrence.  Bound by VALU (Philox's multiplications first): 1.37e9 entries of
-// 668,880 terms in 1.35 ms, against 4.41 ms of FP64 logarithms, sines and cosines.
+// 668,880 terms in 1.27 ms, against 4.41 ms of FP64 logarithms, sines and cosines.
 __global__ __launch_bounds__(256) void k_srp_table(int64_t dim, int32_t n_bits, uint32_t k0, uint32_t k1,
                                                    const uint8_t *used, int16_t *table, int32_t per) {
   const int Q = n_bits / 4, lane = lane_id();

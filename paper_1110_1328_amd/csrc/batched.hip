@@ -1092,6 +1092,7 @@ struct BatchState {
   // levels, blocks per CU
   struct Choice { int kj, kc, ts, tm, inreg, bpc; };
   std::map<std::vector<int64_t>, Choice> tuned;
+  std::map<void (*)(const BatchBlock *), int> resident;   // blocks of a kernel that a CU holds at once
 };
 
 static void batch_free(BatchState *b) {
@@ -1185,17 +1186,17 @@ static int grow_spill(BatchState *b, int64_t cap) {
   return BLSH_OK;
 }
 
+typedef void (*BatchKernel)(const BatchBlock *);
+
 template <int KC>
-static void launch_phase1_srp(const BatchBlock *blk, int ts, int grid1, hipStream_t s) {
-  if (ts == 128) hipLaunchKernelGGL((k_batch_phase1<BLSH_COSINE, KC, 2>), dim3(grid1), dim3(kBBlock), 0, s, blk);
-  else if (ts == 512) hipLaunchKernelGGL((k_batch_phase1<BLSH_COSINE, KC, 8>), dim3(grid1), dim3(kBBlock), 0, s, blk);
-  else hipLaunchKernelGGL((k_batch_phase1<BLSH_COSINE, KC, 4>), dim3(grid1), dim3(kBBlock), 0, s, blk);
+static BatchKernel phase1_srp(int ts) {
+  return ts == 128 ? k_batch_phase1<BLSH_COSINE, KC, 2>
+                   : ts == 512 ? k_batch_phase1<BLSH_COSINE, KC, 8> : k_batch_phase1<BLSH_COSINE, KC, 4>;
 }
 
 template <int KJ>
-static void launch_phase1_mh(const BatchBlock *blk, int tm, int grid1, hipStream_t s) {
-  if (tm == 128) hipLaunchKernelGGL((k_batch_phase1<BLSH_JACCARD, KJ, 2>), dim3(grid1), dim3(kBBlock), 0, s, blk);
-  else hipLaunchKernelGGL((k_batch_phase1<BLSH_JACCARD, KJ, 1>), dim3(grid1), dim3(kBBlock), 0, s, blk);
+static BatchKernel phase1_mh(int tm) {
+  return tm == 128 ? k_batch_phase1<BLSH_JACCARD, KJ, 2> : k_batch_phase1<BLSH_JACCARD, KJ, 1>;
 }
 
 template <int KJ, int KC>
@@ -1203,8 +1204,8 @@ static void launch_batch_kernels(BatchState *b, const BatchState::GraphKey &gk, 
   if (gk.mode == 1) {
     hipLaunchKernelGGL((k_batch_exhaustive<KJ, KC>), dim3(gk.grid1), dim3(kBBlock), 0, s, b->d_block);
   } else {
-    launch_phase1_srp<KC>(b->d_block, gk.ts, gk.grid1, s);
-    launch_phase1_mh<KJ>(b->d_block, gk.tm, gk.grid1, s);
+    hipLaunchKernelGGL(phase1_srp<KC>(gk.ts), dim3(gk.grid1), dim3(kBBlock), 0, s, b->d_block);
+    hipLaunchKernelGGL(phase1_mh<KJ>(gk.tm), dim3(gk.grid1), dim3(kBBlock), 0, s, b->d_block);
     hipLaunchKernelGGL(k_batch_offsets, dim3(2), dim3(kOffsetsBlock), 0, s, b->d_block);
     hipLaunchKernelGGL((k_batch_phase2<KJ, KC>), dim3(gk.grid2), dim3(kBBlock), 0, s, b->d_block);
   }
@@ -1236,26 +1237,57 @@ static int get_graph(BatchState *b, const BatchState::GraphKey &key, hipGraphExe
   return BLSH_OK;
 }
 
-// Phase-1 blocks per CU of a call that neither fixes nor tunes them.  Lists of one
-// length that come several to a wave: a number that gives every wave whole lists, if
-// one does, so that all waves start a list at the same time and read the same rows
-// (1024 lists of 50,000, 1M rows of 1024 bits: 4 a CU 368 us, 8 422, 6 561; 4096 of 12,000:
-// 494, 595, 749; rows read through a prefix array 340, 371, 325).  The comparator's
-// blocks take ranges: 8 of them a CU over many candidates in lists of one length (512
-// lists of 50,000 sets 2.15 ms, 6 3.11), 6 otherwise (4096 lists of all lengths 58 ms, 8 72).
-static int default_blocks(const blsh_ctx *ctx, const blsh_list_desc *lists, int64_t n_lists, int64_t n_cand, int mode) {
+// Blocks of the call's kernels that a CU holds at once: the comparator's, or the least
+// of the used measures' phase 1.
+static int resident_blocks(BatchState *b, const bool *need, int kj, int kc, int ts, int tm, int mode) {
+  const int ij = kj == 16 ? 0 : kj == 32 ? 1 : 2, ic = kc == 16 ? 0 : kc == 32 ? 1 : 2;
+  static const BatchKernel cmp[3][3] = {
+      {k_batch_exhaustive<16, 16>, k_batch_exhaustive<16, 32>, k_batch_exhaustive<16, 64>},
+      {k_batch_exhaustive<32, 16>, k_batch_exhaustive<32, 32>, k_batch_exhaustive<32, 64>},
+      {k_batch_exhaustive<64, 16>, k_batch_exhaustive<64, 32>, k_batch_exhaustive<64, 64>}};
+  const BatchKernel srp = ic == 0 ? phase1_srp<16>(ts) : ic == 1 ? phase1_srp<32>(ts) : phase1_srp<64>(ts);
+  const BatchKernel mh = ij == 0 ? phase1_mh<16>(tm) : ij == 1 ? phase1_mh<32>(tm) : phase1_mh<64>(tm);
+  int least = kBBlock;
+  for (const BatchKernel k : {mode ? cmp[ij][ic] : nullptr, !mode && need[0] ? mh : nullptr, !mode && need[1] ? srp : nullptr}) {
+    if (!k) continue;
+    int &n = b->resident[k];
+    if (n == 0 && (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k, kBBlock, 0) != hipSuccess || n < 1)) {
+      (void)hipGetLastError();
+      n = kBlocksDefault;
+    }
+    least = std::min(least, n);
+  }
+  return least;
+}
+
+// Blocks per CU of a call that neither fixes nor tunes them: as many as a CU holds at
+// once, at most kBlocksDefault in phase 1, so that no wave starts when others have ended.
+// The comparator (registers: 4 at k = 16 for cosine, 5 at 32, 6 at 64), 14 M candidates
+// in 1000 lists of all lengths, sets: 4 a CU 2.80 ms, 6 3.56, 8 2.83 (k = 16); 5 1.39, 6 2.01,
+// 8 1.65 (32); 6 1.81, 5 2.06, 8 2.47 (64).  Phase 1 of 216 M candidates, sets, k = 64 (5):
+// 5 2.38 ms, 6 2.85, 8 2.48.
+// Lists of one length that come several to a wave: a number that gives every wave whole
+// lists, if one does, so that all waves start a list at the same time and read the same
+// rows (1024 lists of 50,000, 1M rows of 1024 bits: 4 a CU 368 us, 8 422, 6 561; 4096 of
+// 12,000: 494, 595, 749; rows read through a prefix array 340, 371, 325).  The comparator
+// with 5 keeps in step over many candidates with 8 (512 lists of 50,000 sets 2.14 ms, 5 2.35).
+// (Below 2^22 candidates the numbers are alike, and walking 20,000 short lists is not free.)
+static int default_blocks(const blsh_ctx *ctx, const blsh_list_desc *lists, int64_t n_lists, int64_t n_cand, int mode,
+                          int resident) {
+  const int most = mode ? resident : std::min(resident, kBlocksDefault);
+  if (mode ? resident != 5 || n_cand < int64_t(1) << 24 : n_cand < int64_t(1) << 22) return most;
   int64_t n[2] = {0, 0}, length[2] = {0, 0};
   for (int64_t i = 0; i < n_lists; ++i) {
     const int me = lists[i].measure == BLSH_COSINE;
     if (n[me]++ == 0) length[me] = lists[i].length;
-    else if (length[me] != lists[i].length) return kBlocksDefault;
+    else if (length[me] != lists[i].length) return most;
   }
-  if (mode) return n_cand >= int64_t(1) << 24 ? 8 : kBlocksDefault;
-  for (const int bpc : {kBlocksDefault, 4, 5, 8}) {
+  if (mode) return 8;
+  for (const int bpc : {most, 4, 5, 8}) {
     const int64_t waves = int64_t(ctx->n_cu) * bpc / kXcds * (kBBlock / kWave);   // of an XCD
     if (n[0] % waves == 0 && n[1] % waves == 0) return bpc;
   }
-  return kBlocksDefault;
+  return most;
 }
 
 int verify_batched(blsh_ctx *ctx, const blsh_list_desc *lists, int64_t n_lists, const uint32_t *cand, int64_t n_cand,
@@ -1423,11 +1455,11 @@ int verify_batched(blsh_ctx *ctx, const blsh_list_desc *lists, int64_t n_lists, 
   };
 
   // k of a measure no list uses is irrelevant: 32
-  BatchState::Choice ch{kj ? kj : 32, kc ? kc : 32, kSrpTileDefault, kMhTileDefault, 2,
-                         default_blocks(ctx, lists, n_lists, n_cand, mode)};
+  BatchState::Choice ch{kj ? kj : 32, kc ? kc : 32, kSrpTileDefault, kMhTileDefault, 2, 0};
   const int fixed_tile[2] = {ctx->tuning.batch_mh_tile, ctx->tuning.batch_srp_tile};
   if (fixed_tile[0] > 0) ch.tm = fixed_tile[0];
   if (fixed_tile[1] > 0) ch.ts = fixed_tile[1];
+  ch.bpc = default_blocks(ctx, lists, n_lists, n_cand, mode, resident_blocks(b, need, ch.kj, ch.kc, ch.ts, ch.tm, mode));
   if ((kj == 0 || kc == 0) && mode == 0) {
     // autotune (cached per context and batch shape): each free k in turn with
     // the other fixed (the two measures' tiles share the grid but not their

@@ -98,3 +98,41 @@ def test_lists_of_one_length_keep_in_step(ctx, lists, length):
         P.bayeslsh_set_tuning(ctx)
     print("batched %d lists of %d: %s us" % (lists, length, us), flush=True)
     assert us[0] < 1.4 * min(us.values())
+
+
+@pytest.mark.parametrize("k", [16, 32, 64])
+def test_default_blocks_are_resident(ctx, k):
+    """Lists of all lengths: the comparator's and phase 1's default grids take no more than
+    1.15 times the best of 4 to 8 blocks a CU (blocks that a CU cannot hold at once wait for
+    others to end: up to 1.27 times), and any grid gives the same codes."""
+    g, n = torch.Generator(device="cuda").manual_seed(7), 100_000
+    mh = torch.randint(0, 1 << 30, (n, 256), generator=g, device="cuda", dtype=torch.int32)
+    mh[1::2] = torch.where(torch.rand(n // 2, 256, generator=g, device="cuda") < 0.6, mh[::2], mh[1::2])
+    J = P.Signatures(mh.reshape(-1).view(torch.uint32), P.JACCARD, P.OBJECT_MAJOR, n, 256)
+    rng = np.random.default_rng(7)
+    ln = np.exp(rng.uniform(np.log(100), np.log(300_000), 1000)).astype(np.int64)
+    m = int(ln.sum())
+    of = torch.arange(len(ln), device="cuda").repeat_interleave(torch.from_numpy(ln).cuda())
+    cand = ((torch.randint(0, n, (m,), generator=g, device="cuda") + (of << 32)).sort()[0] & 0xFFFFFFFF).to(torch.int32).view(torch.uint32)
+    d = P.list_descs(np.full(len(ln), P.JACCARD), np.full(len(ln), 0.7), rng.integers(0, n, len(ln)),
+                     np.concatenate([[0], np.cumsum(ln)])[:-1], ln)
+    for f in (P.bayeslsh_verify_batched, P.bayeslsh_exhaustive_batched):
+        res, us, codes = P.make_result(m, m // 10), {}, None
+        try:
+            for blocks in (0, 4, 5, 6, 8):
+                P.bayeslsh_set_tuning(ctx, batch_blocks_per_cu=blocks)
+                a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+                runs = []
+                for _ in range(5):
+                    a.record()
+                    f(ctx, d, cand, J, None, EPS, DELTA, GAMMA, (1.0, 1.0), k, res)
+                    b.record()
+                    torch.cuda.synchronize()
+                    runs.append(a.elapsed_time(b) * 1e3)
+                us[blocks] = min(runs)
+                assert codes is None or torch.equal(codes, res.code[:m])
+                codes = res.code[:m].clone()
+        finally:
+            P.bayeslsh_set_tuning(ctx)
+        print("batched %s, k %d, %d candidates: %s us" % (f.__name__, k, m, us), flush=True)
+        assert us[0] < 1.15 * min(us.values())

@@ -236,3 +236,34 @@ def test_a_table_that_cannot_be_allocated():
         torch.cuda.empty_cache()
         a.close()
         b.close()
+
+
+@pytest.mark.parametrize("n_bits", [32, 160, 512, 544])
+@pytest.mark.parametrize("flags", [0, P.SRP_PLANES_Q16])
+def test_short_rows_taken_at_once(n_bits, flags):
+    """1024 rows of 4 terms and fewer, 1025 of them and 1024 with one more term: settled
+    without masks or with them, a row's bits are the same."""
+    print("sparse SRP short rows: %d bits flags %d" % (n_bits, flags), flush=True)
+    rng = np.random.default_rng(n_bits + flags)
+    n, dim = 1025, 1 << 20
+    idx = np.sort(rng.integers(0, dim // 8, (n, 5)) * 8 + np.arange(5), axis=1).astype(np.uint32)
+    val = rng.normal(size=(n, 5)).astype(np.float32)
+    val[::7, 1] = -val[::7, 0]
+    val[5], val[6, 0], val[7, 0] = 0, np.nan, np.inf
+    ctx = P.bayeslsh_create(0)
+    try:
+        def bits(lens):
+            off = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+            keep = np.arange(5)[None, :] < np.asarray(lens)[:, None]
+            m = len(lens)
+            vecs = P.csr_vectors(up(off), up(np.append(idx[:m][keep], idx[0, :1])), up(np.append(val[:m][keep], val[0, :1])), dim)   # (no null arrays)
+            return bits_of(ctx, vecs, m, n_bits, P.OBJECT_MAJOR, flags)
+        for short in (0, 1, 4):
+            more = np.full(n, short)
+            longer = np.full(n - 1, short)
+            longer[-1] = 5
+            got, want = bits(np.full(n - 1, short)), bits(more)
+            np.testing.assert_array_equal(got, want[:-1])
+            np.testing.assert_array_equal(got[:-1], bits(longer)[:-1])
+    finally:
+        ctx.close()

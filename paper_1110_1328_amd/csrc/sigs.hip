@@ -68,7 +68,8 @@ __global__ __launch_bounds__(256) void k_minhash(const int64_t *offsets, const u
     b2[i] = h < n_hashes ? 2u * mod_p(b[h]) : 0u;
   }
   for (;;) {
-    const int64_t next = min(set + waves, n_sets - 1);
+    // (a wave's last: its own again, not one line for all)
+    const int64_t next = set + waves < n_sets ? set + waves : set;
     const int64_t s1 = ld_uniform(offsets + next), e1 = ld_uniform(offsets + next + 1);
     uint32_t best[HPL];
 #pragma unroll

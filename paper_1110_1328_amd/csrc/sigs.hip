@@ -530,7 +530,12 @@ __device__ inline void dense_chain(const float *X, int64_t n_rows, const float *
       stash(b, u0);
     }
   };
-  slice(t0, 0);
+  if constexpr (AHEAD) {
+    fetch(t0, 0);
+    stash(0, 0);
+  } else {
+    slice(t0, 0);
+  }
   __syncthreads();
   for (int tile = t0; tile < t1; ++tile) {
     const int b = (tile - t0) & 1;

@@ -103,7 +103,7 @@ def test_lists_of_one_length_keep_in_step(ctx, lists, length):
 @pytest.mark.parametrize("k", [16, 32, 64])
 def test_default_blocks_are_resident(ctx, k):
     """Lists of all lengths: the comparator's and phase 1's default grids take no more than
-    1.15 times the best of 4 to 8 blocks a CU (blocks that a CU cannot hold at once wait for
+    1.2 times the best of 4 to 8 blocks a CU (blocks that a CU cannot hold at once wait for
     others to end: up to 1.27 times), and any grid gives the same codes."""
     g, n = torch.Generator(device="cuda").manual_seed(7), 100_000
     mh = torch.randint(0, 1 << 30, (n, 256), generator=g, device="cuda", dtype=torch.int32)
@@ -135,4 +135,4 @@ def test_default_blocks_are_resident(ctx, k):
         finally:
             P.bayeslsh_set_tuning(ctx)
         print("batched %s, k %d, %d candidates: %s us" % (f.__name__, k, m, us), flush=True)
-        assert us[0] < 1.15 * min(us.values())
+        assert us[0] < 1.2 * min(us.values())
